@@ -131,26 +131,17 @@ __device__ __forceinline__ auto get(const Raw<TY>& r, int b) {
   }
 }
 
-template <int TY>
-__device__ __forceinline__ auto load_elem(const void* data, uint64_t row) {
-  if constexpr (TY == T_I8) return (int32_t)gptr<int8_t>(data)[row];
-  else if constexpr (TY == T_I16) return (int32_t)gptr<int16_t>(data)[row];
-  else if constexpr (TY == T_I32) return (int32_t)gptr<int32_t>(data)[row];
-  else return (int64_t)gptr<int64_t>(data)[row];
-}
-
 __device__ __forceinline__ uint64_t row_of(uint64_t tb, uint32_t lane, int b) {
   return tb + 256u * (uint32_t)(b >> 2) + 4u * lane + (uint32_t)(b & 3);
 }
 
-// Predicate bits of one lane's 32 rows: bit b = pred(value of row b).  The
-// word is built highest row first as P = 2P + bit, one add-with-carry per
-// row after the compare.
-template <int TY, bool FULL, bool NT = true, class Pred>
-__device__ __forceinline__ uint32_t pred_bits(const void* data, uint64_t tb, uint32_t lane,
-                                              uint64_t nrows, Pred pred) {
+// Predicate bits of one lane's 32 rows of a whole tile: bit b = pred(value
+// of row b).  The word is built highest row first as P = 2P + bit, one
+// add-with-carry per row after the compare.
+template <int TY, bool NT = true, class Pred>
+__device__ __forceinline__ uint32_t pred_bits(const void* data, uint64_t tb, uint32_t lane, Pred pred) {
   uint32_t P = 0;
-  if constexpr (FULL && TY == T_I64) {
+  if constexpr (TY == T_I64) {
 #pragma unroll
     for (int h = 1; h >= 0; --h) {
       Raw<TY> r;
@@ -158,20 +149,11 @@ __device__ __forceinline__ uint32_t pred_bits(const void* data, uint64_t tb, uin
 #pragma unroll
       for (int b = 15; b >= 0; --b) P = (P << 1) + (uint32_t)pred(get<TY>(r, b), 16 * h + b);
     }
-  } else if constexpr (FULL) {
+  } else {
     Raw<TY> r;
     load_full<TY, NT>(r, data, tb, lane);
 #pragma unroll
     for (int b = 31; b >= 0; --b) P = (P << 1) + (uint32_t)pred(get<TY>(r, b), b);
-  } else {
-    // the one partial tile of a table: element loads, kept rolled
-#pragma unroll 1
-    for (int b = 31; b >= 0; --b) {
-      const uint64_t row = row_of(tb, lane, b);
-      uint32_t bit = 0;
-      if (row < nrows) bit = (uint32_t)pred(load_elem<TY>(data, row), b);
-      P = (P << 1) + bit;
-    }
   }
   return P;
 }
@@ -193,64 +175,136 @@ __device__ __forceinline__ uint32_t valid_bits(const uint32_t* valid, uint64_t t
 }
 
 __device__ __forceinline__ uint32_t inrange_bits(uint64_t tb, uint32_t lane, uint64_t nrows) {
+  const int rows = nrows - tb < (uint64_t)kTileRows ? (int)(nrows - tb) : kTileRows;
   uint32_t m = 0;
-#pragma unroll 1
-  for (int b = 0; b < 32; ++b) m |= (uint32_t)(row_of(tb, lane, b) < nrows) << b;
+#pragma unroll
+  for (int j = 0; j < kSteps; ++j)
+    m |= ((1u << min(max(rows - (int)(256u * (uint32_t)j + 4u * lane), 0), 4)) - 1u) << (4 * j);
   return m;
 }
 
 // Values of rows 8q .. 8q + 7 of the lane (steps 2q, 2q + 1), as int64:
-// wide loads on a full tile as for a range test, element loads (0 past the
-// table) on the partial one.
+// wide loads on a whole tile as for a range test; on the table's last,
+// partial tile the same wide loads through a buffer resource bounded to its
+// rows, past which they return zero without touching memory.  The bound is
+// in whole dwords, since the hardware zeroes a dword that crosses it; the
+// bytes up to the next 4-byte boundary may be read.
 template <int TY, bool FULL, bool NT>
 __device__ __forceinline__ void load8(const void* data, uint64_t tb, uint32_t lane, uint64_t nrows, int q,
                                       int64_t (&x)[8]) {
-  if constexpr (FULL) {
+  constexpr uint32_t width = TY == T_I8 ? 1u : TY == T_I16 ? 2u : TY == T_I32 ? 4u : 8u;
+  const char* base = (const char*)data + tb * width;
+  const uint32_t rows = nrows - tb < (uint64_t)kTileRows ? (uint32_t)(nrows - tb) : (uint32_t)kTileRows;
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)uni((rows * width + 3u) & ~3u), 0x00020000);
 #pragma unroll
-    for (int js = 0; js < 2; ++js) {
-      const int j = 2 * q + js;
-      if constexpr (TY == T_I8) {
-        const uint32_t w = ldg<NT>(gptr<uint32_t>((const int8_t*)data + tb) + lane + 64 * j);
+  for (int js = 0; js < 2; ++js) {
+    const uint32_t at = width * (256u * (uint32_t)(2 * q + js) + 4u * lane);   // byte offset of the lane's four rows
+    if constexpr (TY == T_I8) {
+      uint32_t w;
+      if constexpr (FULL) w = ldg<NT>((const GLOBAL uint32_t*)(gptr<char>(base) + at));
+      else w = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)at, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[4 * js + i] = (int64_t)(int8_t)(w >> (8 * i));
-      } else if constexpr (TY == T_I16) {
-        const v2i w = ldg<NT>(gptr<v2i>((const int16_t*)data + tb) + lane + 64 * j);
+      for (int i = 0; i < 4; ++i) x[4 * js + i] = (int64_t)(int8_t)(w >> (8 * i));
+    } else if constexpr (TY == T_I16) {
+      v2i w;
+      if constexpr (FULL) w = ldg<NT>((const GLOBAL v2i*)(gptr<char>(base) + at));
+      else w = (v2i)__builtin_amdgcn_raw_buffer_load_b64(rs, (int)at, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[4 * js + i] = (int64_t)(int16_t)((uint32_t)w[i >> 1] >> (16 * (i & 1)));
-      } else if constexpr (TY == T_I32) {
-        const v4i w = ldg<NT>(gptr<v4i>((const int32_t*)data + tb) + lane + 64 * j);
+      for (int i = 0; i < 4; ++i) x[4 * js + i] = (int64_t)(int16_t)((uint32_t)w[i >> 1] >> (16 * (i & 1)));
+    } else if constexpr (TY == T_I32) {
+      v4i w;
+      if constexpr (FULL) w = ldg<NT>((const GLOBAL v4i*)(gptr<char>(base) + at));
+      else w = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[4 * js + i] = (int64_t)w[i];
-      } else {
-        const GLOBAL v4i* p = gptr<v4i>((const int64_t*)data + tb) + 2 * lane + 128 * j;
-        const v4i w0 = ldg<NT>(p), w1 = ldg<NT>(p + 1);
-        x[4 * js + 0] = (int64_t)(((uint64_t)(uint32_t)w0[1] << 32) | (uint32_t)w0[0]);
-        x[4 * js + 1] = (int64_t)(((uint64_t)(uint32_t)w0[3] << 32) | (uint32_t)w0[2]);
-        x[4 * js + 2] = (int64_t)(((uint64_t)(uint32_t)w1[1] << 32) | (uint32_t)w1[0]);
-        x[4 * js + 3] = (int64_t)(((uint64_t)(uint32_t)w1[3] << 32) | (uint32_t)w1[2]);
+      for (int i = 0; i < 4; ++i) x[4 * js + i] = (int64_t)w[i];
+    } else {
+      v4i w[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if constexpr (FULL) w[h] = ldg<NT>((const GLOBAL v4i*)(gptr<char>(base) + at) + h);
+        else w[h] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)(at + 16u * (uint32_t)h), 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const v4i& v = w[i >> 1];
+        x[4 * js + i] = (int64_t)(((uint64_t)(uint32_t)v[2 * (i & 1) + 1] << 32) | (uint32_t)v[2 * (i & 1)]);
       }
     }
-  } else {
+  }
+}
+
+// One leaf on the partial last tile of its table, eight rows of a lane at a
+// time (rows past the table test a zero and are not counted).  The values are
+// widened to int64, so that one short body serves every type and test: the
+// wide bodies of whole tiles are not doubled, and keep their registers.
+// Four loads in turn per leaf; element loads, one row of a lane after
+// another, were 32 (six leaves over 10 007 rows: 37 us, with these 19 us).
+// SCAN: a scan's leaf, whose flags are DevFlags (a batch's copies of the
+// leaves reuse that word, and read an IN list through its sorted values).
+template <bool SCAN>
+__device__ __forceinline__ uint32_t partial_leaf(CInstr I, uint32_t ty, uint64_t tb, uint32_t lane, uint64_t nrows) {
+  const uint32_t op = I->op;
+  const void* data = I->data;
+  const int64_t lo = I->lo;
+  const uint64_t span = I->span;
+  uint32_t P = 0;
+#pragma unroll 1
+  for (int q = 3; q >= 0; --q) {
+    int64_t x[8];
+    switch (ty) {
+      case T_I8: load8<T_I8, false, true>(data, tb, lane, nrows, q, x); break;
+      case T_I16: load8<T_I16, false, true>(data, tb, lane, nrows, q, x); break;
+      case T_I32: load8<T_I32, false, true>(data, tb, lane, nrows, q, x); break;
+      default: load8<T_I64, false, true>(data, tb, lane, nrows, q, x); break;
+    }
+    if (op == D_RANGE) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint64_t row = row_of(tb, lane, 8 * q + k);
-      x[k] = row < nrows ? (int64_t)load_elem<TY>(data, row) : 0;
+      for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)((uint64_t)x[k] - (uint64_t)lo <= span);
+    } else if (op == D_BITMAP) {
+      const GLOBAL uint32_t* bits = gptr<uint32_t>(I->aux);
+#pragma unroll
+      for (int k = 7; k >= 0; --k) {
+        const uint64_t d = (uint64_t)x[k] - (uint64_t)lo;
+        const uint32_t at = d < span ? (uint32_t)d : 0u;   // nbits <= 2^32
+        P = (P << 1) + ((uint32_t)(d < span) & ((bits[at >> 5] >> (at & 31)) & 1u));
+      }
+    } else if (SCAN && (I->flags & F_HASHED)) {
+      const uint32_t f = I->flags, b = in_hash_bits(f);
+      const uint32_t c1 = kInHashMul[in_hash_pair(f)][0], c2 = kInHashMul[in_hash_pair(f)][1];
+      const GLOBAL int64_t* T = gptr<int64_t>(I->aux) + I->n;
+#pragma unroll
+      for (int k = 7; k >= 0; --k) {
+        const int64_t h1 = T[in_hash(x[k], c1, b)], h2 = T[(1u << b) + in_hash(x[k], c2, b)];
+        P = (P << 1) + ((uint32_t)(h1 == x[k]) | (uint32_t)(h2 == x[k]));
+      }
+    } else {  // D_INLIST: lower bound in the sorted list
+      const GLOBAL int64_t* list = gptr<int64_t>(I->aux);
+      uint32_t base[8] = {};
+      for (uint32_t len = I->n; len > 1;) {
+        const uint32_t half = len >> 1;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) base[k] = list[base[k] + half] <= x[k] ? base[k] + half : base[k];
+        len -= half;
+      }
+#pragma unroll
+      for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)(list[base[k]] == x[k]);
     }
   }
+  return P;
 }
 
 // IN-list test of a lane's 32 rows against a sorted list of n values (in
 // LDS or device memory): wide loads of the column as for a range test, then
 // a branch-free lower bound that moves the eight rows of two steps one
 // search step at a time, so that their list reads are in flight together.
-template <int TY, bool FULL, bool NT = true, class List>
-__device__ __forceinline__ uint32_t inlist_bits(const void* data, uint64_t tb, uint32_t lane,
-                                                uint64_t nrows, List list, uint32_t n, uint32_t need) {
+template <int TY, bool NT = true, class List>
+__device__ __forceinline__ uint32_t inlist_bits(const void* data, uint64_t tb, uint32_t lane, List list, uint32_t n, uint32_t need) {
   uint32_t P = 0;
 #pragma unroll 1
   for (int q = 3; q >= 0; --q) {   // bits 8q .. 8q + 7: steps 2q, 2q + 1
     int64_t x[8];
-    load8<TY, FULL, NT>(data, tb, lane, nrows, q, x);
+    load8<TY, true, NT>(data, tb, lane, tb + kTileRows, q, x);
     uint32_t base[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) base[k] = 0;
@@ -271,15 +325,14 @@ __device__ __forceinline__ uint32_t inlist_bits(const void* data, uint64_t tb, u
 // then T + 2^b, in LDS or device memory): a value is in the list if and
 // only if it sits in its slot of either table, so two reads per row answer
 // it (empty slots hold a list value, which can only match a member).
-template <int TY, bool FULL, bool NT = true, class Tab>
-__device__ __forceinline__ uint32_t inhash_bits(const void* data, uint64_t tb, uint32_t lane, uint64_t nrows,
-                                                Tab T, uint32_t b, uint32_t c1, uint32_t c2, uint32_t need) {
+template <int TY, bool NT = true, class Tab>
+__device__ __forceinline__ uint32_t inhash_bits(const void* data, uint64_t tb, uint32_t lane, Tab T, uint32_t b, uint32_t c1, uint32_t c2, uint32_t need) {
   const uint32_t m = 1u << b;
   uint32_t P = 0;
 #pragma unroll 1
   for (int q = 3; q >= 0; --q) {
     int64_t x[8];
-    load8<TY, FULL, NT>(data, tb, lane, nrows, q, x);
+    load8<TY, true, NT>(data, tb, lane, tb + kTileRows, q, x);
 #pragma unroll
     for (int k = 7; k >= 0; --k) {
       const bool hit = T[in_hash(x[k], c1, b)] == x[k] || T[m + in_hash(x[k], c2, b)] == x[k];
@@ -290,33 +343,29 @@ __device__ __forceinline__ uint32_t inhash_bits(const void* data, uint64_t tb, u
 }
 
 // ---------------------------------------------------------------- leaves --
-// SCAN: called by the scan kernels, whose leaves carry DevFlags (a batch's
-// copies of the leaves reuse the flags word for their own guard marks, and
-// read an IN list through its sorted values only).
-template <int TY, bool FULL, bool NT = true, bool SCAN = true>
-__device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb, uint32_t lane,
-                                              uint64_t nrows, uint32_t need, const StageView& sv) {
+// A scan's leaf on a whole tile.
+template <int TY, bool NT>
+__device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb, uint32_t lane, uint32_t need,
+                                              const StageView& sv) {
   const void* data = I->data;
   const int64_t lo = I->lo;
   const uint64_t span = I->span;
   if (op == D_INLIST) {
     const uint32_t f = I->flags;
-    if (SCAN && (f & F_HASHED)) {
+    if (f & F_HASHED) {
       // the cuckoo tables after the sorted list: their LDS copy if staged
       const uint32_t b = in_hash_bits(f), c1 = kInHashMul[in_hash_pair(f)][0], c2 = kInHashMul[in_hash_pair(f)][1];
       const uint32_t* tabs = (const uint32_t*)I->aux + 2 * I->n;
       for (uint32_t k = 0; k < sv.n; ++k)
         if (sv.list[k].src == tabs)
-          return inhash_bits<TY, FULL, NT>(data, tb, lane, nrows, (const int64_t*)(sv.lds + sv.list[k].lds_word),
-                                           b, c1, c2, need);
-      return inhash_bits<TY, FULL, NT>(data, tb, lane, nrows, gptr<int64_t>(tabs), b, c1, c2, need);
+          return inhash_bits<TY, NT>(data, tb, lane, (const int64_t*)(sv.lds + sv.list[k].lds_word), b, c1, c2, need);
+      return inhash_bits<TY, NT>(data, tb, lane, gptr<int64_t>(tabs), b, c1, c2, need);
     }
     // the list's LDS copy if the scan staged it
     for (uint32_t k = 0; k < sv.n; ++k)
       if (sv.list[k].src == (const uint32_t*)I->aux)
-        return inlist_bits<TY, FULL, NT>(data, tb, lane, nrows, (const int64_t*)(sv.lds + sv.list[k].lds_word),
-                                     I->n, need);
-    return inlist_bits<TY, FULL, NT>(data, tb, lane, nrows, gptr<int64_t>(I->aux), I->n, need);
+        return inlist_bits<TY, NT>(data, tb, lane, (const int64_t*)(sv.lds + sv.list[k].lds_word), I->n, need);
+    return inlist_bits<TY, NT>(data, tb, lane, gptr<int64_t>(I->aux), I->n, need);
   }
   if (op == D_BITMAP && sv.n) {
     uint32_t off = kNoLds, z = 0;
@@ -333,14 +382,14 @@ __device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb
       // int32 (the host stages only such bitmaps)
       const uint32_t* bm = sv.lds + off;
       if constexpr (TY == T_I64) {
-        return pred_bits<TY, FULL, NT>(data, tb, lane, nrows, [=](int64_t x, int b) -> uint32_t {
+        return pred_bits<TY, NT>(data, tb, lane, [=](int64_t x, int b) -> uint32_t {
           const uint64_t d = (uint64_t)x - (uint64_t)lo;
           const uint32_t k = ((need >> b) & 1u) && d < z ? (uint32_t)d : z;
           return (bm[k >> 5] >> (k & 31)) & 1u;
         });
       } else {
         const uint32_t lo32 = (uint32_t)lo;
-        return pred_bits<TY, FULL, NT>(data, tb, lane, nrows, [=](int32_t x, int b) -> uint32_t {
+        return pred_bits<TY, NT>(data, tb, lane, [=](int32_t x, int b) -> uint32_t {
           const uint32_t d = (uint32_t)x - lo32;
           const uint32_t k = ((need >> b) & 1u) && d < z ? d : z;
           return (bm[k >> 5] >> (k & 31)) & 1u;
@@ -350,12 +399,12 @@ __device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb
   }
   if (op == D_RANGE) {
     if constexpr (TY == T_I64) {
-      return pred_bits<TY, FULL, NT>(data, tb, lane, nrows, [=](int64_t x, int) {
+      return pred_bits<TY, NT>(data, tb, lane, [=](int64_t x, int) {
         return (uint64_t)x - (uint64_t)lo <= span;
       });
     } else {
       const uint32_t lo32 = (uint32_t)lo, span32 = (uint32_t)span;
-      return pred_bits<TY, FULL, NT>(data, tb, lane, nrows, [=](int32_t x, int) {
+      return pred_bits<TY, NT>(data, tb, lane, [=](int32_t x, int) {
         return (uint32_t)x - lo32 <= span32;
       });
     }
@@ -364,7 +413,7 @@ __device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb
     // word 0 and are masked: no branch, so all 32 lookups issue together
     const GLOBAL uint32_t* bits = gptr<uint32_t>(I->aux);
     if constexpr (TY == T_I64) {
-      return pred_bits<TY, FULL, NT>(data, tb, lane, nrows, [=](int64_t x, int b) -> uint32_t {
+      return pred_bits<TY, NT>(data, tb, lane, [=](int64_t x, int b) -> uint32_t {
         const uint64_t d = (uint64_t)x - (uint64_t)lo;
         const bool ok = d < span && ((need >> b) & 1u);
         const uint32_t k = ok ? (uint32_t)d : 0u;  // nbits <= 2^32
@@ -373,7 +422,7 @@ __device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb
     } else {
       // x - lo in 64 bits: a negative key must not alias a bit when nbits
       // exceeds 2^31
-      return pred_bits<TY, FULL, NT>(data, tb, lane, nrows, [=](int32_t x, int b) -> uint32_t {
+      return pred_bits<TY, NT>(data, tb, lane, [=](int32_t x, int b) -> uint32_t {
         const uint64_t d = (uint64_t)((int64_t)x - lo);
         const bool ok = d < span && ((need >> b) & 1u);
         const uint32_t k = ok ? (uint32_t)d : 0u;
@@ -404,11 +453,15 @@ __device__ __forceinline__ void eval_leaf(uint32_t op, CInstr I, uint64_t tb, ui
   if (flags & F_GUARD_AND) need = ~tos_f;
   else if (flags & F_GUARD_OR) need = ~tos_t;
   uint32_t P;
-  switch (I->type) {
-    case T_I8: P = leaf_pred<T_I8, FULL, NT>(op, I, tb, lane, nrows, need, sv); break;
-    case T_I16: P = leaf_pred<T_I16, FULL, NT>(op, I, tb, lane, nrows, need, sv); break;
-    case T_I32: P = leaf_pred<T_I32, FULL, NT>(op, I, tb, lane, nrows, need, sv); break;
-    default: P = leaf_pred<T_I64, FULL, NT>(op, I, tb, lane, nrows, need, sv); break;
+  if constexpr (!FULL) {
+    P = partial_leaf<true>(I, I->type, tb, lane, nrows);
+  } else {
+    switch (I->type) {
+      case T_I8: P = leaf_pred<T_I8, NT>(op, I, tb, lane, need, sv); break;
+      case T_I16: P = leaf_pred<T_I16, NT>(op, I, tb, lane, need, sv); break;
+      case T_I32: P = leaf_pred<T_I32, NT>(op, I, tb, lane, need, sv); break;
+      default: P = leaf_pred<T_I64, NT>(op, I, tb, lane, need, sv); break;
+    }
   }
   t = P & V;
   f = ~P & V;
@@ -547,17 +600,32 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
   int np = 0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) { pend[k] = 0; pidx[k] = 0; }
-  // each wave takes runs of tps consecutive tiles, W runs apart
+  // Each wave takes runs of tps consecutive whole tiles, W runs apart.  A
+  // partial last tile goes to the last wave, which has the fewest, before its
+  // others: at the end of the scan every other wave would wait for it.
   const uint64_t tps = a.tiles_per_step ? a.tiles_per_step : 1;
   const uint64_t wid = uni64((uint64_t)blockIdx.x * nw + (threadIdx.x >> 6));
-  for (uint64_t step = wid * tps; step < a.ntiles; step += W * tps)
-  for (uint64_t tile = step; tile < step + tps && tile < a.ntiles; ++tile) {
+  const uint64_t nfull = a.nrows / kTileRows;
+  uint64_t run = wid * tps;
+  uint32_t k = 0;
+  bool partial = wid == W - 1 && nfull < a.ntiles;
+  for (;;) {
+    uint64_t tile = nfull;
+    if (!partial) {
+      if (k == tps) {
+        run += W * tps;
+        k = 0;
+      }
+      tile = run + k++;
+      if (tile >= nfull) break;
+    }
     const uint64_t tb = tile * kTileRows;
     uint32_t T;
-    if (tb + kTileRows <= a.nrows) {
+    if (!partial) {
       T = eval_tile<true, NT>(prog, a.nins, tb, lane, a.nrows, sv);
     } else {
       T = eval_tile<false, NT>(prog, a.nins, tb, lane, a.nrows, sv) & inrange_bits(tb, lane, a.nrows);
+      partial = false;
     }
     cnt += __builtin_popcount(T);
     if constexpr (MODE == M_MASK) {
@@ -1120,19 +1188,28 @@ __device__ __forceinline__ void tab_leaves(const Seg& r, const CONSTANT BatchCol
 // A sparse IN-list leaf of the batched kernel: rows one at a time (its
 // registers are spent on the column pipeline), loop kept rolled.
 template <int TY>
-__device__ __noinline__ uint32_t inlist_rows(CInstr I, uint64_t tb, uint32_t lane, uint64_t nrows) {
+__device__ __noinline__ uint32_t inlist_rows(CInstr I, uint64_t tb, uint32_t lane) {
   const GLOBAL int64_t* list = gptr<int64_t>(I->aux);
   const uint32_t n = I->n;
-  return pred_bits<TY, false>(I->data, tb, lane, nrows, [=](auto x, int) -> uint32_t {
-    const int64_t xx = (int64_t)x;
+  const void* data = I->data;
+  uint32_t P = 0;
+#pragma unroll 1
+  for (int b = 31; b >= 0; --b) {
+    const uint64_t row = row_of(tb, lane, b);
+    int64_t x;
+    if constexpr (TY == T_I8) x = gptr<int8_t>(data)[row];
+    else if constexpr (TY == T_I16) x = gptr<int16_t>(data)[row];
+    else if constexpr (TY == T_I32) x = gptr<int32_t>(data)[row];
+    else x = gptr<int64_t>(data)[row];
     uint32_t base = 0, len = n;
     while (len > 1) {
       const uint32_t half = len >> 1;
-      base = list[base + half] <= xx ? base + half : base;
+      base = list[base + half] <= x ? base + half : base;
       len -= half;
     }
-    return list[base] == xx ? 1u : 0u;
-  });
+    P = (P << 1) + (list[base] == x ? 1u : 0u);
+  }
+  return P;
 }
 
 // Every leaf of one segment; truth words go to the wave's slots.  An int64
@@ -1151,7 +1228,7 @@ __device__ __forceinline__ void seg_leaves(const Seg& r, const CONSTANT BatchCol
     CInstr I = leaves + lb + k;
     const uint32_t op = I->op;
     if (op == D_INLIST) {
-      if (TY != T_I64 || h == 1) put_leaf(wl, lane, I->slot, inlist_rows<TY>(I, tb, lane, tb + kTileRows));
+      if (TY != T_I64 || h == 1) put_leaf(wl, lane, I->slot, inlist_rows<TY>(I, tb, lane));
       continue;
     }
     const uint32_t P = seg_leaf<TY>(r, op, I, bmlds, wl, lane, TY == T_I64 && h == 0 ? 16 : 0);
@@ -1241,13 +1318,7 @@ __device__ __forceinline__ void entry_leaves_partial(const CONSTANT BatchTable* 
     if (vs != kNoSlot) wl[vs * kWave + lane] = valid_bits<false>(C->valid, tb, lane, nrows);
     for (uint32_t k = 0; k < ln; ++k) {
       CInstr I = leaves + lb + k;
-      uint32_t P;
-      switch (C->type) {
-        case T_I8: P = leaf_pred<T_I8, false, true, false>(I->op, I, tb, lane, nrows, ~0u, StageView{}); break;
-        case T_I16: P = leaf_pred<T_I16, false, true, false>(I->op, I, tb, lane, nrows, ~0u, StageView{}); break;
-        case T_I32: P = leaf_pred<T_I32, false, true, false>(I->op, I, tb, lane, nrows, ~0u, StageView{}); break;
-        default: P = leaf_pred<T_I64, false, true, false>(I->op, I, tb, lane, nrows, ~0u, StageView{}); break;
-      }
+      const uint32_t P = partial_leaf<false>(I, C->type, tb, lane, nrows);
       put_leaf(wl, lane, I->slot, P);
     }
   }

@@ -1,0 +1,73 @@
+"""The kernels' paths at the sizes where each can go wrong (edges of tiles,
+remainders, smallest and largest of a range), bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+import datagen
+import oracle
+from tests.gpu_common import UINT64_MAX, as_u32, ids_tensor, say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sel():
+    if not torch.cuda.is_available():
+        pytest.fail("gpu test run without a GPU")
+    from paper_1806_08384_amd import sel as s
+    return s
+
+
+@pytest.fixture(scope="module")
+def ctx(sel):
+    c = sel.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def check(sel, ctx, dt, orc, tree):
+    prog = ctx.program(dt, tree)
+    want = orc.rowids(tree)
+    assert ctx.count(dt, prog) == len(want), tree
+    out = ids_tensor(len(want) + 1, torch)
+    st, cnt = ctx.pushdown_rowids(dt, prog, UINT64_MAX, out)
+    got = as_u32(out)
+    assert st == sel.SEL_OK and cnt == len(want)
+    np.testing.assert_array_equal(got[:cnt], want)
+    assert got[cnt] == 0xDEADBEEF, "written past the count"
+
+
+@pytest.mark.parametrize("tail", [1, 2, 3, 5, 255, 257, 1023, 2046, 2047])
+@pytest.mark.parametrize("tiles", [0, 2, 13])
+def test_partial_tile(sel, ctx, tiles, tail):
+    """The table's last, partial tile: every column type (a dword of a narrow
+    column may hold rows on both sides of the end), range, bitmap, hashed and
+    plain sparse list and NULL tests, alone and after whole tiles, and
+    selections of the last row alone."""
+    n = 2048 * tiles + tail
+    say(f"partial tile: {tiles} whole tiles + {tail} rows")
+    rng = np.random.default_rng(n)
+    t = datagen.random_table(rng, n, grid=False, null_rate=0.3)
+    far = rng.integers(-2 ** 62, 2 ** 62, n)
+    t.columns.append(datagen.Column("far", "i64", far))
+    t.columns.append(datagen.Column("row", "i32", np.arange(n, dtype=np.int32)))
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+    some = tuple(int(v) for v in rng.choice(far, min(n, 40)))
+    many = tuple(int(v) for v in rng.integers(-2 ** 62, 2 ** 62, 2000)) + some
+    last = ("cmp", 5, "=", n - 1)
+    trees = [last, ("not", last), ("in", 4, some), ("in", 4, many), ("or", ("in", 4, many), last)]
+    for k in range(4):
+        trees += [("between", k, -5, 9), ("in", k, (-3, 0, 7, 20)), ("isnull", k), ("not", ("cmp", k, "<", 0)),
+                  ("codeset", k, 20, datagen.words_from_codes(range(0, 20, 3), 20))]
+    trees.append(("and", *[("cmp", k, "<>", 1) for k in range(4)]))
+    for tree in trees:
+        check(sel, ctx, dt, orc, tree)
+    # the batch kernels' partial tile
+    pairs = [(dt, ctx.program(dt, tree)) for tree in trees]
+    assert ctx.count_batch(pairs) == [orc.count(tree) for tree in trees]
+    leaf = ("or", ("isunknown", ("cmp", 1, "<", 3)), ("in", 4, many))   # kept off the lookup tables
+    assert ctx.count_batch([(dt, ctx.program(dt, leaf))]) == [orc.count(leaf)]
