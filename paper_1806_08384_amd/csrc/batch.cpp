@@ -21,14 +21,13 @@ struct sel_batch {
   std::vector<const sel_table*> tabs;         // per caller index
   std::vector<const sel_program*> slot_prog;  // per caller index
   BatchPlan plan;
-  void* dev = nullptr;                        // descriptors | acc | out | slot | tables
+  void* dev = nullptr;                        // descriptors | acc | slot | tables
   size_t desc_cap = 0, gtab_cap = 0;
   uint32_t* d_gtab = nullptr;
   const TableBuild* d_builds = nullptr;       // as captured
   uint32_t nbuilds = 0;
   uint64_t table_entries = 0;
   unsigned long long* d_acc = nullptr;
-  unsigned long long* d_out = nullptr;
   DevSlot* d_slot = nullptr;
   unsigned long long* h_out = nullptr;        // pinned
   hipStream_t stream = nullptr;
@@ -119,16 +118,12 @@ void batch_shape(sel_ctx* ctx, uint32_t nprogs, const BatchPlan& bp, uint32_t& g
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Workspace after the descriptors: accumulator lines, counts, slot.
-size_t tail_bytes(uint32_t n) {
-  return up256((size_t)n * kBatchAccStride * 8) + up256((size_t)n * 8) + 256;
-}
+// Workspace after the descriptors: accumulator lines, slot.
+size_t tail_bytes(uint32_t n) { return up256((size_t)n * kBatchAccStride * 8) + 256; }
 
-void place_tail(char* base, size_t desc_cap, uint32_t n, unsigned long long*& acc,
-                unsigned long long*& out, DevSlot*& slot) {
+void place_tail(char* base, size_t desc_cap, uint32_t n, unsigned long long*& acc, DevSlot*& slot) {
   acc = (unsigned long long*)(base + desc_cap);
-  out = (unsigned long long*)(base + desc_cap + up256((size_t)n * kBatchAccStride * 8));
-  slot = (DevSlot*)((char*)out + up256((size_t)n * 8));
+  slot = (DevSlot*)(base + desc_cap + up256((size_t)n * kBatchAccStride * 8));
 }
 
 // Writes the plan's descriptors to `dev` in stream order and fills `a`.
@@ -149,8 +144,8 @@ void release(sel_batch* b) {
   delete b;
 }
 
-// Captures the persistent kernel, then the copy of the counts to pinned host
-// memory; no memset node (the kernel leaves its accumulators zero).
+// Captures the persistent kernels, the last of which writes the counts to
+// pinned host memory; no memset node (they leave their accumulators zero).
 sel_status capture(sel_batch* b) {
   sel_ctx* ctx = b->ctx;
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
@@ -162,10 +157,8 @@ sel_status capture(sel_batch* b) {
   do {
     if ((e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal)) != hipSuccess) { where = "hipStreamBeginCapture"; break; }
     int le = b->plan.launch(b->args, b->d_builds, b->grid, b->block, b->stream);
-    hipError_t ce = hipMemcpyAsync(b->h_out, b->d_out, (size_t)b->n * 8, hipMemcpyDeviceToHost, b->stream);
     e = hipStreamEndCapture(b->stream, &b->graph);
     if (le) { e = (hipError_t)le; where = "batch launch (capture)"; break; }
-    if (ce != hipSuccess) { e = ce; where = "hipMemcpyAsync (capture)"; break; }
     if (e != hipSuccess) { where = "hipStreamEndCapture"; break; }
     if ((e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0)) != hipSuccess) { where = "hipGraphInstantiate"; break; }
   } while (0);
@@ -195,7 +188,7 @@ sel_status rebuild(sel_batch* b) {
     HIP_TRY(ctx, hipMemsetAsync(b->dev, 0, total, ctx->stream), "hipMemsetAsync(batch)");
     b->desc_cap = cap;
     b->gtab_cap = gcap;
-    place_tail((char*)b->dev, cap, b->n, b->d_acc, b->d_out, b->d_slot);
+    place_tail((char*)b->dev, cap, b->n, b->d_acc, b->d_slot);
     b->d_gtab = (uint32_t*)((char*)b->dev + cap + tail_bytes(b->n));
   }
   BatchArgs a{};
@@ -205,7 +198,7 @@ sel_status rebuild(sel_batch* b) {
   a.acc = b->d_acc;
   a.done = nullptr;
   a.ndone = b->n;
-  a.out = b->d_out;
+  a.out = b->h_out;
   a.slot = b->d_slot;
   uint32_t grid, block;
   batch_shape(ctx, b->n, b->plan, grid, block);
@@ -273,9 +266,8 @@ sel_status sel_count_batch(sel_ctx* ctx, uint32_t n, const sel_table* const* tab
   char* base = (char*)ctx->batch_mem;
   BatchArgs a{};
   unsigned long long* acc;
-  unsigned long long* outp;
   DevSlot* slot;
-  place_tail(base, desc, n, acc, outp, slot);
+  place_tail(base, desc, n, acc, slot);
   // the accumulators move with the descriptor size: clear this call's lines
   int e = sel_launch_fill((uint32_t*)acc, (size_t)n * kBatchAccStride * 2, 0u, ctx->stream);
   if (e) return hip_err(ctx, (hipError_t)e, "accumulator clear");
@@ -285,7 +277,8 @@ sel_status sel_count_batch(sel_ctx* ctx, uint32_t n, const sel_table* const* tab
   a.acc = acc;
   a.done = nullptr;
   a.ndone = n;
-  a.out = outp;
+  a.out = ctx->hbatch;
+  for (uint32_t i = 0; i < n; ++i) ctx->hbatch[i] = kPending;
   a.slot = ctx->slot;
   uint32_t grid, block;
   batch_shape(ctx, n, bp, grid, block);
@@ -295,9 +288,8 @@ sel_status sel_count_batch(sel_ctx* ctx, uint32_t n, const sel_table* const* tab
     tl.done();
   }
   if (e) return hip_err(ctx, (hipError_t)e, "batch launch");
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->hbatch, a.out, n * 8, hipMemcpyDeviceToHost, ctx->stream),
-          "hipMemcpyAsync(batch counts)");
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+  st = wait_words(ctx, ctx->hbatch, n, ctx->stream);
+  if (st != SEL_OK) return st;
   for (uint32_t i = 0; i < n; ++i) out_counts[i] = ctx->hbatch[i];
   return SEL_OK;
 }
@@ -367,12 +359,14 @@ sel_status sel_batch_run(sel_batch* b, uint64_t* out_counts) {
     ev = take_events(ctx);
     HIP_TRY(ctx, hipEventRecord(ev.a, b->stream), "hipEventRecord");
   }
+  for (uint32_t i = 0; i < b->n; ++i) b->h_out[i] = kPending;
   HIP_TRY(ctx, hipGraphLaunch(b->exec, b->stream), "hipGraphLaunch");
   if (timed) {
     HIP_TRY(ctx, hipEventRecord(ev.b, b->stream), "hipEventRecord");
     ctx->pending.push_back({SEL_K_BATCH, ev});
   }
-  HIP_TRY(ctx, hipStreamSynchronize(b->stream), "hipStreamSynchronize");
+  const sel_status st = wait_words(ctx, b->h_out, b->n, b->stream);
+  if (st != SEL_OK) return st;
   for (uint32_t i = 0; i < b->n; ++i) out_counts[i] = b->h_out[i];
   return SEL_OK;
 }

@@ -539,9 +539,20 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
          (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
 }
 
-// Block sum, one device atomic per workgroup, and the last workgroup (by
-// ticket) publishes the total and resets the slot for the next launch.
-__device__ void finish(DevSlot* slot, unsigned long long* out, uint32_t c0, uint32_t c1, bool two) {
+// A result word in pinned host memory: a system-scope store, so that a host
+// thread polling the word sees it without waiting for the launch to retire.
+__device__ __forceinline__ void put_host(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Block sum and one device atomic per workgroup, which adds its count and
+// takes its ticket at once (kSlotTicket): the workgroup that sees all other
+// tickets also holds the total, publishes it and resets the slot for the next
+// launch.  Separate atomics (add, wait, ticket, read back) were four memory
+// latencies at the end of every launch instead of one.  The second count
+// (rare: out-of-range keys and ids) is added before the ticket.
+__device__ void finish(DevSlot* slot, unsigned long long* out, unsigned long long* host, uint32_t c0, uint32_t c1,
+                       bool two) {
   __shared__ unsigned long long red0[16], red1[16];
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t s0 = wave_sum(c0);
@@ -551,17 +562,23 @@ __device__ void finish(DevSlot* slot, unsigned long long* out, uint32_t c0, uint
   if (threadIdx.x == 0) {
     unsigned long long b0 = 0, b1 = 0;
     for (uint32_t w = 0; w < (blockDim.x >> 6); ++w) { b0 += red0[w]; b1 += red1[w]; }
-    if (b0) atomicAdd(&slot->acc, b0);
-    if (b1) atomicAdd(&slot->acc2, b1);
-    atomics_done();
-    const unsigned int ticket = atomicAdd(&slot->ticket, 1u);
-    if (ticket == gridDim.x - 1) {
-      out[0] = atomicAdd(&slot->acc, 0ull);
-      if (two) out[1] = atomicAdd(&slot->acc2, 0ull);
-      atomicExch(&slot->acc, 0ull);
-      atomicExch(&slot->acc2, 0ull);
+    if (b1) {
+      atomicAdd(&slot->acc2, b1);
       atomics_done();
-      atomicExch(&slot->ticket, 0u);
+    }
+    const unsigned long long old = atomicAdd(&slot->acc, kSlotTicket + b0);
+    if (old / kSlotTicket == gridDim.x - 1) {
+      const unsigned long long total = old % kSlotTicket + b0;
+      const unsigned long long second = two ? atomicExch(&slot->acc2, 0ull) : 0ull;
+      if (out) {
+        out[0] = total;
+        if (two) out[1] = second;
+      }
+      if (host) {
+        if (two) put_host(host + 1, second);
+        put_host(host, total);
+      }
+      atomicExch(&slot->acc, 0ull);
     }
   }
 }
@@ -668,7 +685,7 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
     for (int k = 0; k < 8; ++k)
       if (k < np && pend[k]) __builtin_nontemporal_store(pend[k], &a.mask[pidx[k]]);
   }
-  finish(a.slot, a.out, cnt, oor, MODE == M_KEYBITMAP);
+  finish(a.slot, a.out, a.host, cnt, oor, MODE == M_KEYBITMAP);
 }
 
 // Exclusive scan of the tile counts in two levels.  k_chunk_scan: one
@@ -922,7 +939,7 @@ __global__ void __launch_bounds__(256) k_gather(GatherArgs a) {
       }
     }
   }
-  finish(a.slot, a.out, 0u, bad, true);
+  finish(a.slot, nullptr, a.host, 0u, bad, true);
 }
 
 // --------------------------------------------------------- batched count --
@@ -1572,7 +1589,7 @@ __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
   if (last) {
     for (uint32_t k = threadIdx.x; k < a.ndone; k += blockDim.x) {
       const uint64_t line = a.done ? a.done[k] : k;
-      a.out[k] = atomicExch(&a.acc[line * kBatchAccStride], 0ull);
+      put_host(&a.out[k], atomicExch(&a.acc[line * kBatchAccStride], 0ull));
     }
     atomics_done();
     __syncthreads();
@@ -2391,7 +2408,7 @@ __global__ void __launch_bounds__(lbatch_threads<D>()) k_lbatch(LutArgs a) {
   if (last) {
     for (uint32_t k = threadIdx.x; k < a.ndone; k += blockDim.x) {
       const uint64_t line = a.done ? a.done[k] : k;
-      a.out[k] = atomicExch(&a.acc[line * kBatchAccStride], 0ull);
+      put_host(&a.out[k], atomicExch(&a.acc[line * kBatchAccStride], 0ull));
     }
     atomics_done();
     __syncthreads();
@@ -2430,6 +2447,7 @@ int sel_noalloc_scratch(int device, void** ptr) {
 }
 
 int sel_launch_scan(int mode, const ScanArgs& a, uint32_t grid, uint32_t block, void* stream) {
+  if (grid >= kSlotMaxGrid) return (int)hipErrorInvalidValue;
   hipStream_t s = (hipStream_t)stream;
   const uint32_t lds = a.nstage ? 4u * a.stage_words : 0u;
   const bool nt = !a.cached;
@@ -2465,6 +2483,7 @@ int sel_launch_compact(const CompactArgs& a, uint32_t grid, uint32_t block, void
 }
 
 int sel_launch_gather(const GatherArgs& a, uint32_t grid, uint32_t block, void* stream) {
+  if (grid >= kSlotMaxGrid) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL(k_gather, dim3(grid), dim3(block), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }

@@ -176,6 +176,9 @@ uint32_t type_bytes(uint32_t dt);
 sel_status ensure_scratch(sel_ctx* ctx, size_t bytes);
 sel_status stage_copy(sel_ctx* ctx, void* dst, const void* src, size_t n);
 sel_status read_out(sel_ctx* ctx, uint64_t* v0, uint64_t* v1);
+// A result word not written yet: no count reaches it.
+constexpr unsigned long long kPending = ~0ull;
+sel_status wait_words(sel_ctx* ctx, const unsigned long long* w, uint32_t n, hipStream_t stream);
 EventPair take_events(sel_ctx* ctx);
 uint64_t ntiles_of(uint64_t nrows);
 

@@ -87,12 +87,16 @@ struct DevInstr {          // 64 bytes, read with scalar loads
 };
 static_assert(sizeof(DevInstr) == 64, "DevInstr layout");
 
-// Per-launch completion slot: an accumulator and a ticket that the last
-// workgroup resets, so that no memset is needed between launches.
+// Per-launch completion slot: counters that the last workgroup resets, so
+// that no memset is needed between launches.  A scan's workgroups add their
+// counts and take their tickets in one word: the low 40 bits hold the count
+// (at most 2^32), the high 24 the workgroups done.
+constexpr unsigned long long kSlotTicket = 1ull << 40;
+constexpr uint32_t kSlotMaxGrid = 1u << 24;
 struct DevSlot {
-  unsigned long long acc;    // running count
+  unsigned long long acc;    // running count and tickets of a scan
   unsigned long long acc2;   // second counter (out-of-range keys)
-  unsigned int ticket;
+  unsigned int ticket;       // a batch launch's ticket
   unsigned int pad[3];
 };
 
@@ -109,7 +113,8 @@ struct ScanArgs {
   uint64_t nrows;
   uint64_t ntiles;
   DevSlot* slot;
-  unsigned long long* out;     // out[0] = count, out[1] = out-of-range keys
+  unsigned long long* out;     // device, may be null: out[0] = count, out[1] = out-of-range keys
+  unsigned long long* host;    // the same in pinned host memory, may be null
   // M_MASK: per tile, the result words that hold a TRUE row, packed at the
   // front of the tile's 64-word slot in lane order (the rest of the slot is
   // not written); the lanes they belong to; and the tile's TRUE rows
@@ -165,7 +170,7 @@ struct GatherArgs {
   uint64_t count;
   uint64_t nrows;
   DevSlot* slot;
-  unsigned long long* out;     // out[1]: ids >= nrows
+  unsigned long long* host;    // pinned host memory; host[1]: ids >= nrows
   uint32_t ncols, pad;
   GatherCol cols[kMaxGatherCols];
 };
@@ -334,7 +339,7 @@ struct BatchArgs {
   uint64_t total_tiles;        // a multiple of kBatchTileAlign
   unsigned long long* acc;     // accumulator lines (kBatchAccStride u64 each)
   // After the launch, the last workgroup moves accumulator done[k] to out[k]
-  // and zeroes it (k < ndone); done == nullptr means lines 0 .. ndone-1.
+  // (pinned host memory) and zeroes it (k < ndone); done == nullptr means lines 0 .. ndone-1.
   // Lines not listed keep accumulating across launches.
   const uint32_t* done;
   uint32_t ndone;

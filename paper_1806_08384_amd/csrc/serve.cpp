@@ -76,7 +76,7 @@ struct TableState {
 };
 
 struct RoundSlot {                          // per in-flight round
-  void* dev = nullptr;                      // descriptors | out | device tables
+  void* dev = nullptr;                      // descriptors | device tables
   size_t dev_bytes = 0, host_bytes = 0;
   uint8_t* host = nullptr;                  // pinned staging for descriptors
   selrt::BatchPlan plan;                    // this round's descriptors
@@ -334,11 +334,11 @@ bool launch_round(sel_server* s) {
     waits.swap(s->round_waits);
   }
   for (hipEvent_t ev : waits) (void)hipStreamWaitEvent(s->stream, ev, 0);
-  // device: descriptors, the counts, the device tables; the descriptors are
-  // staged through pinned memory
+  // device: descriptors, the device tables; the descriptors are staged
+  // through pinned memory, and the counts written to it by the kernel
   auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
-  const size_t o_out = up(bp.bytes());
-  const size_t o_gtab = up(o_out + (size_t)ngroups * 8);
+  const size_t o_gtab = up(bp.bytes());
+  const size_t out_bytes = up((size_t)ngroups * 8);
   const size_t need_dev = o_gtab + bp.gtab_total() * 4;
   if (need_dev > rs.dev_bytes) {
     if (rs.dev) (void)hipFree(rs.dev);
@@ -352,13 +352,13 @@ bool launch_round(sel_server* s) {
     }
     rs.dev_bytes = want;
   }
-  if (o_gtab > rs.host_bytes) {
+  if (std::max(o_gtab, out_bytes) > rs.host_bytes) {
     if (rs.host) (void)hipHostFree(rs.host);
     if (rs.h_out) (void)hipHostFree(rs.h_out);
     rs.host = nullptr;
     rs.h_out = nullptr;
     rs.host_bytes = 0;
-    const size_t want = std::max(o_gtab * 2, size_t(1) << 16);
+    const size_t want = std::max(std::max(o_gtab, out_bytes) * 2, size_t(1) << 16);
     if (hipHostMalloc((void**)&rs.host, want, 0) != hipSuccess ||
         hipHostMalloc((void**)&rs.h_out, want, 0) != hipSuccess) {
       std::lock_guard<std::mutex> lk(s->mu);
@@ -373,7 +373,7 @@ bool launch_round(sel_server* s) {
   a.acc = s->d_acc;
   a.done = nullptr;                  // every line of the round is read out and reset
   a.ndone = ngroups;
-  a.out = (unsigned long long*)((char*)rs.dev + o_out);
+  a.out = rs.h_out;
   a.slot = rs.slot;
   const uint32_t block = bp.default_block();
   const uint32_t lds = bp.lds_bytes(block);
@@ -382,9 +382,8 @@ bool launch_round(sel_server* s) {
   const uint32_t grid = (uint32_t)std::max<uint64_t>(
       1, std::min<uint64_t>((uint64_t)std::min(occ, 2) * s->ctx->num_cus, (bp.total_tiles + 7) / 8));
   bool ok = hipEventRecord(rs.start_ev, s->stream) == hipSuccess;
-  ok = ok && hipMemcpyAsync(rs.dev, rs.host, o_out, hipMemcpyHostToDevice, s->stream) == hipSuccess;
+  ok = ok && hipMemcpyAsync(rs.dev, rs.host, o_gtab, hipMemcpyHostToDevice, s->stream) == hipSuccess;
   ok = ok && bp.launch(a, d_builds, grid, block, s->stream) == 0;
-  ok = ok && hipMemcpyAsync(rs.h_out, a.out, (size_t)ngroups * 8, hipMemcpyDeviceToHost, s->stream) == hipSuccess;
   ok = ok && hipEventRecord(rs.done_ev, s->stream) == hipSuccess;
   if (!ok) {
     std::lock_guard<std::mutex> lk(s->mu);

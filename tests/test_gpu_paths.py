@@ -71,3 +71,34 @@ def test_partial_tile(sel, ctx, tiles, tail):
     assert ctx.count_batch(pairs) == [orc.count(tree) for tree in trees]
     leaf = ("or", ("isunknown", ("cmp", 1, "<", 3)), ("in", 4, many))   # kept off the lookup tables
     assert ctx.count_batch([(dt, ctx.program(dt, leaf))]) == [orc.count(leaf)]
+
+
+def test_results_are_each_calls_own(sel, ctx):
+    """Counts come back through words that the kernels write to the host:
+    calls of every kind in turn, on two contexts with streams of their own,
+    each return their own result, an empty selection's 0 included."""
+    n = 2048 * 9 + 700
+    t = datagen.Table("own", n)
+    t.columns.append(datagen.Column("row", "i32", np.arange(n, dtype=np.int32)))
+    here = sel.device_table(ctx, t)
+    other = sel.Context(0, stream=torch.cuda.Stream())
+    there = sel.device_table(other, t)
+    trees = [("cmp", 0, "<", k) for k in (0, 1, 2047, 2048, 2049, n - 1, n)]
+    sides = []
+    for c, dt in ((ctx, here), (other, there)):
+        progs = [c.program(dt, tree) for tree in trees]
+        sides.append((c, dt, progs, c.batch([(dt, p) for p in progs])))
+    out = ids_tensor(n, torch)
+    bits = torch.zeros((n + 31) // 32, dtype=torch.int32, device="cuda")
+    want = [tree[3] for tree in trees]
+    for k in range(3 * len(trees)):
+        i = k % len(trees)
+        for c, dt, progs, batch in sides:
+            assert c.count(dt, progs[i]) == want[i]
+            assert c.pushdown_rowids(dt, progs[i], UINT64_MAX, out) == (sel.SEL_OK, want[i])
+            assert c.pushdown_keybitmap(dt, 0, 0, progs[-1 - i], bits, n) == (sel.SEL_OK, want[-1 - i])
+            assert c.star_count(dt, [0], [bits], [n]) == want[-1 - i]
+            assert c.count_batch([(dt, p) for p in progs]) == want
+            assert batch.run() == want
+    torch.cuda.synchronize()
+    other.close()
