@@ -165,6 +165,7 @@ sel_status run_scan(sel_ctx* ctx, int mode, uint32_t cls, ScanArgs& a, int kind,
   a.tiles_per_step = cfg.tiles_per_step ? cfg.tiles_per_step : 1;
   if (stage_end) limit_stage(a, *stage_end, cfg.stage_words);
   a.slot = ctx->slot;
+  a.order = mask_order(a.nrows, grid * (block / kWave), (uint32_t)a.tiles_per_step);
   TimedLaunch tl(ctx, kind, timed);
   int e = sel_launch_scan(mode, a, grid, block, ctx->stream);
   tl.done();
@@ -249,22 +250,14 @@ sel_status check_columns(sel_ctx* ctx, uint64_t nrows, uint32_t ncols, const sel
 // The row-id push-down over the workspace at sp (the context's grow-only
 // scratch, or the fixed array of the call that allocates nothing).  Every
 // word the kernels read there is written earlier in the same call: the mask
-// pass writes each tile's count and lane map and the mask words those maps
-// name, the tile scan writes every offset and chunk value the compaction
+// pass writes each tile's count, offset and word map and the mask words those
+// maps name, the tile scan writes every offset and chunk value the compaction
 // reads.  So nothing needs clearing between calls.
 sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_program* prog,
                                 uint64_t max_rows, uint32_t* d_out, uint64_t cap,
                                 uint64_t* out_count, char* sp, bool timed) {
   const uint64_t ntiles = ntiles_of(table->nrows);
   const RowidScratch L(ntiles);
-  const size_t mask_bytes = L.mask, counts_bytes = L.counts, chunk_bytes = L.chunk;
-  sel_status st;
-  uint32_t* mask = (uint32_t*)sp;
-  uint32_t* counts = (uint32_t*)(sp + mask_bytes);
-  uint32_t* offsets = (uint32_t*)(sp + mask_bytes + counts_bytes);
-  uint32_t* chunk_sums = (uint32_t*)(sp + mask_bytes + 2 * counts_bytes);
-  uint32_t* chunk_offs = (uint32_t*)(sp + mask_bytes + 2 * counts_bytes + chunk_bytes);
-  uint64_t* lanes = (uint64_t*)(sp + mask_bytes + 2 * counts_bytes + 2 * chunk_bytes);
   ScanArgs a{};
   a.prog = prog->dcode;
   a.nins = prog->nins;
@@ -273,37 +266,44 @@ sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_
   a.ntiles = ntiles;
   a.out = ctx->dout;
   a.host = ctx->hout;
-  a.mask = mask;
-  a.tile_lanes = lanes;
-  a.tile_counts = counts;
-  st = run_scan(ctx, M_MASK, prog->tune_class, a, SEL_K_MASK, timed, &prog->stage_end);
+  a.mask = (uint32_t*)sp;
+  a.tile_meta = (uint32_t*)(sp + L.o_meta());
+  a.tile_words = (uint64_t*)(sp + L.o_maps());
+  sel_status st = run_scan(ctx, M_MASK, prog->tune_class, a, SEL_K_MASK, timed, &prog->stage_end);
   if (st != SEL_OK) return st;
   // the scan of tile counts and the compaction are enqueued at once; the
   // compaction reads the published count and writes nothing if it exceeds
   // max_rows or cap, so one wait at the end gives the outcome
-  {
-    TimedLaunch tl(ctx, SEL_K_SCAN, timed);
-    int e = sel_launch_scan_tiles(counts, offsets, chunk_sums, chunk_offs, ntiles, ctx->stream);
-    tl.done();
-    if (e) return hip_err(ctx, (hipError_t)e, "tile scan launch");
-  }
   CompactArgs c{};
-  c.mask = mask;
-  c.tile_lanes = lanes;
-  c.offsets = offsets;
-  c.chunk_offs = chunk_offs;
-  c.ntiles = ntiles;
+  c.mask = a.mask;
+  c.tile_words = a.tile_words;
+  c.tile_meta = a.tile_meta;
+  c.order = a.order;
+  c.ntiles = (uint32_t)ntiles;
   c.out = d_out;
-  c.cap = cap;
   c.total = ctx->dout;
   c.limit = std::min(max_rows, cap);
-  // one wave per tile: compaction is latency-bound, so every tile gets a
-  // wave of its own rather than a grid-stride loop
-  const uint32_t block = 256;
-  const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((ntiles + 15) / 16, 1u << 20));
+  // A table of which each scan wave takes one tile: tiles are placed by their
+  // numbers, a wave's first id is at most a few KB of counts away, and a
+  // wave per tile keeps the short launch wide (16 scattered tiles a workgroup
+  // and two launches for the counts: 23 us for 1M rows, against 6 us).
+  // Larger ones take the counts' scan, and four tiles a wave.
+  if (ntiles <= a.order.waves && a.order.tps == 1) {
+    c.tiles_per_wave = 1;
+  } else {
+    uint32_t* offsets = (uint32_t*)(sp + L.o_offsets());
+    uint32_t* chunk_sums = (uint32_t*)(sp + L.o_chunks());
+    TimedLaunch tl(ctx, SEL_K_SCAN, timed);
+    int e = sel_launch_scan_tiles(a.order, a.tile_meta, offsets, chunk_sums, c.ntiles, ctx->stream);
+    tl.done();
+    if (e) return hip_err(ctx, (hipError_t)e, "tile scan launch");
+    c.offsets = offsets;
+    c.chunk_sums = chunk_sums;
+    c.tiles_per_wave = 4;
+  }
   {
     TimedLaunch tl(ctx, SEL_K_COMPACT, timed);
-    int e = sel_launch_compact(c, grid, block, ctx->stream);
+    int e = sel_launch_compact(c, ctx->stream);
     tl.done();
     if (e) return hip_err(ctx, (hipError_t)e, "compaction launch");
   }

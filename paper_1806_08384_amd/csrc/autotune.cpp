@@ -111,8 +111,8 @@ sel_status sel_autotune(sel_ctx* ctx, const sel_table* table, const sel_program*
     sel_status st = ensure_scratch(ctx, L.total());
     if (st != SEL_OK) return st;
     a.mask = (uint32_t*)ctx->scratch;
-    a.tile_counts = (uint32_t*)((char*)ctx->scratch + L.mask);
-    a.tile_lanes = (uint64_t*)((char*)ctx->scratch + L.mask + 2 * L.counts + 2 * L.chunk);
+    a.tile_meta = (uint32_t*)((char*)ctx->scratch + L.o_meta());
+    a.tile_words = (uint64_t*)((char*)ctx->scratch + L.o_maps());
   }
   Candidate b{256, 0};
   double ms = 0;
@@ -124,7 +124,9 @@ sel_status sel_autotune(sel_ctx* ctx, const sel_table* table, const sel_program*
     x.tiles_per_step = c.tiles_per_step ? c.tiles_per_step : 1;
     limit_stage(x, prog->stage_end, c.stage_words);
     const uint64_t need = (need_waves + c.block / kWave - 1) / (c.block / kWave);
-    return sel_launch_scan(mode, x, (uint32_t)std::min<uint64_t>(c.grid, need), c.block, ctx->stream);
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(c.grid, need);
+    x.order = mask_order(x.nrows, grid * (c.block / kWave), (uint32_t)x.tiles_per_step);
+    return sel_launch_scan(mode, x, grid, c.block, ctx->stream);
   };
   // the launch shape with the default knobs
   sel_status st = time_candidates(ctx, candidates(ctx, mode, nullptr), reps, [&](const Candidate& c) {

@@ -200,16 +200,20 @@ sel_status run_scan(sel_ctx* ctx, int mode, uint32_t cls, sel::ScanArgs& a, int 
                     bool timed = true, const std::vector<uint32_t>* stage_end = nullptr);
 
 // Byte layout of the row-id path's workspace for a table of ntiles tiles:
-// the packed mask words, tile counts, tile offsets, chunk sums, chunk
-// offsets and tile lane maps, in that order.
+// the packed mask words, tile counts and offsets in their streams, tile id
+// offsets, chunk sums, tile word maps, in that order.
 struct RowidScratch {
-  size_t mask, counts, chunk, lanes;
+  size_t mask, words, chunk, maps;
   explicit RowidScratch(uint64_t ntiles)
       : mask((size_t)ntiles * sel::kWave * 4),
-        counts(((size_t)ntiles * 4 + 255) & ~size_t(255)),
-        chunk(2048 * 4),
-        lanes(((size_t)ntiles * 8 + 255) & ~size_t(255)) {}
-  size_t total() const { return mask + 2 * counts + 2 * chunk + lanes; }
+        words(((size_t)ntiles * 4 + 255) & ~size_t(255)),
+        chunk(2 * 2048 * 4),
+        maps(((size_t)ntiles * 8 + 255) & ~size_t(255)) {}
+  size_t o_meta() const { return mask; }
+  size_t o_offsets() const { return mask + words; }
+  size_t o_chunks() const { return mask + 2 * words; }
+  size_t o_maps() const { return mask + 2 * words + chunk; }
+  size_t total() const { return o_maps() + maps; }
 };
 // The push-down of sel_pushdown_rowids with its workspace at `sp` (at least
 // RowidScratch(ntiles).total() bytes of device memory); arguments checked.

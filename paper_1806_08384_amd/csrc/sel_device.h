@@ -102,6 +102,62 @@ struct DevSlot {
 
 enum ScanMode : int { M_COUNT = 0, M_MASK = 1, M_KEYBITMAP = 2 };
 
+// The order in which a mask scan's waves take a table's tiles: runs of `tps`
+// consecutive whole tiles, `waves` runs apart, and a partial last tile first
+// of the last wave's.  The scan keeps each wave's results together (its
+// writes fill whole cache lines), so a tile's place among them is its wave's
+// first place plus its turn; places 0 .. ntiles - 1 are all taken.
+struct MaskOrder {
+  uint32_t waves, tps;
+  uint32_t nfull;              // whole tiles
+  uint32_t partial;            // 1: a partial tile follows them
+  uint32_t runs_q, runs_r;     // runs = runs_q * waves + runs_r
+  uint32_t last_wave;          // wave of the last run, which lacks `deficit` tiles
+  uint32_t deficit;
+};
+#ifdef __HIP__
+#define SEL_HD __host__ __device__
+#else
+#define SEL_HD
+#endif
+SEL_HD inline MaskOrder mask_order(uint64_t nrows, uint32_t waves, uint32_t tps) {
+  MaskOrder o{};
+  o.waves = waves;
+  o.tps = tps;
+  o.nfull = (uint32_t)(nrows / kTileRows);
+  o.partial = nrows % kTileRows ? 1u : 0u;
+  const uint32_t runs = (o.nfull + tps - 1) / tps;
+  o.runs_q = runs / waves;
+  o.runs_r = runs % waves;
+  o.last_wave = runs ? (runs - 1) % waves : 0u;
+  o.deficit = runs * tps - o.nfull;
+  return o;
+}
+// First place of wave w.
+SEL_HD inline uint32_t wave_place(const MaskOrder& o, uint32_t w) {
+  return o.tps * (w * o.runs_q + (w < o.runs_r ? w : o.runs_r)) - (w > o.last_wave ? o.deficit : 0u);
+}
+// Place of a tile, and its turn among its wave's tiles.
+SEL_HD inline uint32_t tile_place(const MaskOrder& o, uint32_t tile, uint32_t& turn) {
+  const uint32_t run = tile / o.tps, round = run / o.waves;
+  uint32_t w = run - round * o.waves;
+  turn = round * o.tps + (tile - run * o.tps);
+  if (tile == o.nfull) {         // the partial tile
+    w = o.waves - 1;
+    turn = 0;
+  } else if (o.partial && w == o.waves - 1) {
+    ++turn;
+  }
+  return wave_place(o, w) + turn;
+}
+// Tiles whose words share one packed stream: a wave packs the words of this
+// many turns one after another, so a tile's first word has 12 bits there.
+constexpr uint32_t kMaskGroup = 64;
+// Per tile: its TRUE rows (12 bits) and its first word's offset in its
+// group's stream (from bit 12).
+constexpr uint32_t kMetaCount = 0xFFFu;
+constexpr uint32_t kMetaShift = 12;
+
 struct BatchBitmap;
 
 struct ScanArgs {
@@ -115,12 +171,15 @@ struct ScanArgs {
   DevSlot* slot;
   unsigned long long* out;     // device, may be null: out[0] = count, out[1] = out-of-range keys
   unsigned long long* host;    // the same in pinned host memory, may be null
-  // M_MASK: per tile, the result words that hold a TRUE row, packed at the
-  // front of the tile's 64-word slot in lane order (the rest of the slot is
-  // not written); the lanes they belong to; and the tile's TRUE rows
+  // M_MASK, by place (MaskOrder): the result words (of 32 rows in table
+  // order) that hold a TRUE row, of each group of kMaskGroup turns one packed
+  // stream in turn and row order, at the 64-word slot of the group's first
+  // place (the rest is not written); per tile the map of its words that are
+  // there, and its count and offset
   uint32_t* mask;
-  uint64_t* tile_lanes;
-  uint32_t* tile_counts;
+  uint64_t* tile_words;
+  uint32_t* tile_meta;
+  MaskOrder order;
   // M_KEYBITMAP
   const void* key_data;
   uint32_t key_type;
@@ -140,12 +199,17 @@ constexpr uint32_t kScanStageWords = 12288;
 
 struct CompactArgs {
   const uint32_t* mask;        // packed nonzero result words (see ScanArgs)
-  const uint64_t* tile_lanes;  // the lanes they belong to
-  const uint32_t* offsets;     // exclusive prefix of tile counts within a chunk
-  const uint32_t* chunk_offs;  // exclusive prefix of chunk (1024 tiles) totals
-  uint64_t ntiles;
+  const uint64_t* tile_words;  // per tile, which of its 64 words they are
+  const uint32_t* tile_meta;   // counts and offsets
+  // exclusive prefix of tile counts within a chunk of 1024 tiles and the
+  // chunks' totals; null: few tiles, whose places are their numbers, and each
+  // wave adds up the counts before its own
+  const uint32_t* offsets;
+  const uint32_t* chunk_sums;
+  MaskOrder order;
+  uint32_t ntiles;
+  uint32_t tiles_per_wave;     // 1 or 4
   uint32_t* out;
-  uint64_t cap;
   // the count the mask pass published; the compaction writes nothing when
   // it is 0 or above `limit` (Algorithm 1's maxSize, or the capacity)
   const unsigned long long* total;
@@ -470,9 +534,9 @@ extern "C++" {
 // sel_pushdown_rowids_noalloc, looked up once per device.
 int sel_noalloc_scratch(int device, void** ptr);
 int sel_launch_scan(int mode, const sel::ScanArgs& a, uint32_t grid, uint32_t block, void* stream);
-int sel_launch_scan_tiles(const uint32_t* counts, uint32_t* offsets, uint32_t* chunk_sums,
-                          uint32_t* chunk_offs, uint64_t n, void* stream);
-int sel_launch_compact(const sel::CompactArgs& a, uint32_t grid, uint32_t block, void* stream);
+int sel_launch_scan_tiles(const sel::MaskOrder& order, const uint32_t* tile_meta, uint32_t* offsets,
+                          uint32_t* chunk_sums, uint32_t ntiles, void* stream);
+int sel_launch_compact(const sel::CompactArgs& a, void* stream);
 int sel_launch_gather(const sel::GatherArgs& a, uint32_t grid, uint32_t block, void* stream);
 int sel_launch_fill(uint32_t* p, uint64_t nwords, uint32_t value, void* stream);
 int sel_launch_tables(const sel::TableBuild* d_builds, uint32_t nbuilds, uint64_t nentries,

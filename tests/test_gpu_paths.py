@@ -102,3 +102,37 @@ def test_results_are_each_calls_own(sel, ctx):
             assert batch.run() == want
     torch.cuda.synchronize()
     other.close()
+
+
+@pytest.mark.parametrize("tiles", [1, 5, 3071, 3073, 4100])
+@pytest.mark.parametrize("most", [1, 16, 17, 40, 2048])
+def test_row_ids_by_density(sel, ctx, tiles, most):
+    """Row ids where a tile has up to `most` TRUE rows, from none to all:
+    four sparse tiles at once (up to 16 lanes with TRUE rows), a tile walked
+    bit by bit and a dense one, in tables of one tile per scan wave and of
+    more, with the partial tile at the end."""
+    n = 2048 * tiles + 1111
+    rng = np.random.default_rng(tiles + most)
+    hit = np.zeros(n, dtype=np.int8)
+    per = rng.integers(0, most + 1, tiles + 1)
+    if most == 2048:
+        per[::3] = 2048
+    for t in range(tiles + 1):
+        rows = min(2048, n - 2048 * t)
+        lanes = 2048 * t + rng.choice(rows, min(int(per[t]), rows), replace=False)
+        hit[lanes] = 1
+        if t % 7 == 3 and per[t] > 3:      # several rows of one lane
+            hit[2048 * t: 2048 * t + 4] = 1
+    table = datagen.Table("density", n)
+    table.columns.append(datagen.Column("hit", "i8", hit))
+    dt = sel.device_table(ctx, table)
+    want = np.flatnonzero(hit).astype(np.uint32)
+    say(f"density: {tiles} tiles, up to {most}: {len(want)} ids")
+    prog = ctx.program(dt, ("cmp", 0, "=", 1))
+    for shape in (None, dict(block=64, grid=3), dict(block=128, tiles_per_step=4)):
+        ctx.set_launch(**shape) if shape else ctx.set_launch()
+        out = ids_tensor(len(want) + 1, torch)
+        assert ctx.pushdown_rowids(dt, prog, UINT64_MAX, out) == (sel.SEL_OK, len(want))
+        np.testing.assert_array_equal(as_u32(out)[:-1], want)
+        assert as_u32(out)[-1] == 0xDEADBEEF
+    ctx.set_launch()
