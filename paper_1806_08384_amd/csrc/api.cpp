@@ -116,32 +116,38 @@ uint64_t tune_key(int kind, uint32_t cls, uint64_t ntiles) {
 // if the tuner recorded one, else the defaults: 12 resident waves per CU,
 // nontemporal loads, one tile per step, every planned bitmap staged (the
 // tuner's choices for the 300M-row fact-table scans).
-void scan_shape(sel_ctx* ctx, int mode, uint32_t cls, uint64_t ntiles, sel_launch& cfg, uint32_t& grid,
-                uint32_t& block) {
-  cfg = kDefaultLaunch;
-  if (ctx->launch_fixed) {
-    cfg = ctx->launch;
-  } else {
-    auto it = ctx->tune.find(tune_key(mode, cls, ntiles));
-    if (it != ctx->tune.end()) cfg = it->second;
-  }
-  block = cfg.block;
+static sel_launch scan_config(const sel_ctx* ctx, int mode, uint32_t cls, uint64_t ntiles) {
+  if (ctx->launch_fixed) return ctx->launch;
+  auto it = ctx->tune.find(tune_key(mode, cls, ntiles));
+  return it != ctx->tune.end() ? it->second : kDefaultLaunch;
+}
+
+int launch_scan(sel_ctx* ctx, int mode, ScanArgs& a, const sel_launch& cfg, const std::vector<uint32_t>* stage_end) {
+  const uint32_t block = cfg.block, wpb = block / kWave;
+  a.cached = cfg.cached;
+  a.tiles_per_step = cfg.tiles_per_step ? cfg.tiles_per_step : 1;
+  a.small = cfg.grid == 0 && block == 256 && !cfg.cached && a.tiles_per_step == 1 && a.nrows <= kSmallScanRows;
   uint64_t g = cfg.grid;
-  if (g == 0) {
-    int occ = 0;
-    if (block == 256) {
-      occ = ctx->occ[mode];
-    } else if (sel_scan_occupancy(mode, block, &occ) != 0) {
-      occ = 1;
+  uint32_t stage_words = cfg.stage_words;
+  if (a.small) {
+    a.ntiles = (a.nrows + 256 * kSmallSteps - 1) / (256 * kSmallSteps);
+    g = ~0ull;   // a wave for every quarter tile
+    if (!stage_words) stage_words = kSmallStageWords;
+  } else {
+    a.ntiles = ntiles_of(a.nrows);
+    if (g == 0) {
+      int occ = 0;
+      if (block == 256) occ = ctx->occ[mode];
+      else if (sel_scan_occupancy(mode, block, &occ) != 0) occ = 1;
+      g = (uint64_t)std::min(std::max(occ, 1), (int)(kScanWavesPerCu / wpb)) * ctx->num_cus;
     }
-    if (occ < 1) occ = 1;
-    const int per_cu = std::min(occ, (int)(kScanWavesPerCu / (block / kWave)));
-    g = (uint64_t)per_cu * ctx->num_cus;
   }
-  const uint32_t wpb = block / kWave;
-  uint64_t need = (ntiles + wpb - 1) / wpb;
-  if (need == 0) need = 1;
-  grid = (uint32_t)std::min<uint64_t>(need, std::max<uint64_t>(g, 1));
+  const uint64_t need = std::max<uint64_t>((a.ntiles + wpb - 1) / wpb, 1);
+  const uint32_t grid = (uint32_t)std::min<uint64_t>(need, std::max<uint64_t>(g, 1));
+  if (stage_end) limit_stage(a, *stage_end, stage_words);
+  a.slot = ctx->slot;
+  a.order = mask_order(a.nrows, grid * wpb, a.tiles_per_step, a.small != 0);
+  return sel_launch_scan(mode, a, grid, block, ctx->stream);
 }
 
 bool check_prog(sel_ctx* ctx, const sel_table* t, const sel_program* p) {
@@ -158,16 +164,9 @@ bool check_prog(sel_ctx* ctx, const sel_table* t, const sel_program* p) {
 
 sel_status run_scan(sel_ctx* ctx, int mode, uint32_t cls, ScanArgs& a, int kind, bool timed,
                     const std::vector<uint32_t>* stage_end) {
-  uint32_t grid, block;
-  sel_launch cfg;
-  scan_shape(ctx, mode, cls, a.ntiles, cfg, grid, block);
-  a.cached = cfg.cached;
-  a.tiles_per_step = cfg.tiles_per_step ? cfg.tiles_per_step : 1;
-  if (stage_end) limit_stage(a, *stage_end, cfg.stage_words);
-  a.slot = ctx->slot;
-  a.order = mask_order(a.nrows, grid * (block / kWave), (uint32_t)a.tiles_per_step);
+  const sel_launch cfg = scan_config(ctx, mode, cls, ntiles_of(a.nrows));
   TimedLaunch tl(ctx, kind, timed);
-  int e = sel_launch_scan(mode, a, grid, block, ctx->stream);
+  int e = launch_scan(ctx, mode, a, cfg, stage_end);
   tl.done();
   if (e != 0) return hip_err(ctx, (hipError_t)e, "scan kernel launch");
   return SEL_OK;
@@ -256,14 +255,12 @@ sel_status check_columns(sel_ctx* ctx, uint64_t nrows, uint32_t ncols, const sel
 sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_program* prog,
                                 uint64_t max_rows, uint32_t* d_out, uint64_t cap,
                                 uint64_t* out_count, char* sp, bool timed) {
-  const uint64_t ntiles = ntiles_of(table->nrows);
-  const RowidScratch L(ntiles);
+  const RowidScratch L(table->nrows);
   ScanArgs a{};
   a.prog = prog->dcode;
-  a.nins = prog->nins;
+  a.nins = prog->scan_nins;
   set_stage(a, prog);
   a.nrows = table->nrows;
-  a.ntiles = ntiles;
   a.out = ctx->dout;
   a.host = ctx->hout;
   a.mask = (uint32_t*)sp;
@@ -279,17 +276,20 @@ sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_
   c.tile_words = a.tile_words;
   c.tile_meta = a.tile_meta;
   c.order = a.order;
-  c.ntiles = (uint32_t)ntiles;
+  c.ntiles = (uint32_t)a.ntiles;
+  c.quarters = a.small;
   c.out = d_out;
   c.total = ctx->dout;
   c.limit = std::min(max_rows, cap);
   // A table of which each scan wave takes one tile: tiles are placed by their
   // numbers, a wave's first id is at most a few KB of counts away, and a
-  // wave per tile keeps the short launch wide (16 scattered tiles a workgroup
-  // and two launches for the counts: 23 us for 1M rows, against 6 us).
+  // wave per tile keeps the short launch wide (16 tiles a workgroup
+  // and two launches for the counts: 23 us for 1M rows, against 5 us).
   // Larger ones take the counts' scan, and four tiles a wave.
-  if (ntiles <= a.order.waves && a.order.tps == 1) {
-    c.tiles_per_wave = 1;
+  // (A quarter tile counts as a tile there, and four of them as one here.)
+  c.tiles_per_wave = 4;
+  if (a.ntiles <= a.order.waves && a.order.tps == 1) {
+    if (!a.small) c.tiles_per_wave = 1;
   } else {
     uint32_t* offsets = (uint32_t*)(sp + L.o_offsets());
     uint32_t* chunk_sums = (uint32_t*)(sp + L.o_chunks());
@@ -299,7 +299,6 @@ sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_
     if (e) return hip_err(ctx, (hipError_t)e, "tile scan launch");
     c.offsets = offsets;
     c.chunk_sums = chunk_sums;
-    c.tiles_per_wave = 4;
   }
   {
     TimedLaunch tl(ctx, SEL_K_COMPACT, timed);
@@ -367,14 +366,16 @@ sel_status sel_ctx_create(int device, void* hip_stream, sel_ctx** out) {
       ctx->own_stream = true;
     }
     void* dmem = nullptr;
-    const size_t dbytes = 256 + 129 * sizeof(DevInstr) + kMaxStage * sizeof(BatchBitmap);
+    // the slot, two result words, the program TRUE, the star program with
+    // its staged bitmaps
+    constexpr size_t o_dout = sizeof(DevSlot), o_true = o_dout + 128, o_star = o_true + sizeof(DevInstr);
+    const size_t dbytes = o_star + 128 * sizeof(DevInstr) + kMaxStage * sizeof(BatchBitmap);
     if ((e = hipMalloc(&dmem, dbytes)) != hipSuccess) { where = "hipMalloc(ctx)"; break; }
     ctx->slot = (DevSlot*)dmem;
     if ((e = hipMemset(dmem, 0, dbytes)) != hipSuccess) { where = "hipMemset(ctx)"; break; }
-    ctx->dout = (unsigned long long*)((char*)dmem + 128);
-    ctx->dstar = (DevInstr*)((char*)dmem + 256);
-    ctx->dtrue = ctx->dstar + 128;
-    ctx->dstage = (BatchBitmap*)(ctx->dtrue + 1);
+    ctx->dout = (unsigned long long*)((char*)dmem + o_dout);
+    ctx->dstar = (DevInstr*)((char*)dmem + o_star);
+    ctx->dtrue = (DevInstr*)((char*)dmem + o_true);
     if ((e = hipMalloc(&ctx->arena_mem, kArenaBytes)) != hipSuccess) { where = "hipMalloc(arena)"; break; }
     ctx->arena.init((char*)ctx->arena_mem, kArenaBytes);
     if ((e = hipHostMalloc((void**)&ctx->hout, 64, hipHostMallocDefault)) != hipSuccess) { where = "hipHostMalloc"; break; }
@@ -588,7 +589,9 @@ sel_status sel_program_compile(sel_ctx* ctx, const sel_table* table, const sel_i
   for (BatchBitmap& b : stage) b.src = (const uint32_t*)(blob_base + (uintptr_t)b.src);
   p->dstage = p->nstage ? (const BatchBitmap*)((char*)p->dev + code_bytes + blob_bytes) : nullptr;
   std::vector<uint8_t> host(total, 0);
-  std::memcpy(host.data(), L.code.data(), code_bytes);
+  const std::vector<DevInstr> scan = scan_code(L.code);
+  p->scan_nins = (uint32_t)scan.size();
+  std::memcpy(host.data(), scan.data(), scan.size() * sizeof(DevInstr));
   if (!L.blob.empty()) std::memcpy(host.data() + code_bytes, L.blob.data(), L.blob.size());
   if (!stage.empty())
     std::memcpy(host.data() + code_bytes + blob_bytes, stage.data(), stage.size() * sizeof(BatchBitmap));
@@ -645,10 +648,9 @@ sel_status sel_count_async(sel_ctx* ctx, const sel_table* table, const sel_progr
   DeviceGuard g(ctx->device);
   ScanArgs a{};
   a.prog = prog->dcode;
-  a.nins = prog->nins;
+  a.nins = prog->scan_nins;
   set_stage(a, prog);
   a.nrows = table->nrows;
-  a.ntiles = ntiles_of(table->nrows);
   a.out = (unsigned long long*)d_count;
   return run_scan(ctx, M_COUNT, prog->tune_class, a, SEL_K_COUNT, true, &prog->stage_end);
 }
@@ -660,10 +662,9 @@ sel_status sel_count(sel_ctx* ctx, const sel_table* table, const sel_program* pr
   DeviceGuard g(ctx->device);
   ScanArgs a{};
   a.prog = prog->dcode;
-  a.nins = prog->nins;
+  a.nins = prog->scan_nins;
   set_stage(a, prog);
   a.nrows = table->nrows;
-  a.ntiles = ntiles_of(table->nrows);
   a.host = ctx->hout;
   ctx->hout[0] = kPending;
   sel_status st = run_scan(ctx, M_COUNT, prog->tune_class, a, SEL_K_COUNT, true, &prog->stage_end);
@@ -692,7 +693,7 @@ sel_status sel_pushdown_rowids(sel_ctx* ctx, const sel_table* table, const sel_p
   if (!check_prog(ctx, table, prog)) return SEL_E_INVALID;
   if (!d_out && cap > 0) return set_err(ctx, SEL_E_INVALID, "d_out is NULL with cap > 0");
   DeviceGuard g(ctx->device);
-  sel_status st = ensure_scratch(ctx, RowidScratch(ntiles_of(table->nrows)).total());
+  sel_status st = ensure_scratch(ctx, RowidScratch(table->nrows).total());
   if (st != SEL_OK) return st;
   return pushdown_rowids_with(ctx, table, prog, max_rows, d_out, cap, out_count,
                               (char*)ctx->scratch, true);
@@ -704,7 +705,7 @@ sel_status sel_pushdown_rowids_noalloc(sel_ctx* ctx, const sel_table* table,
   if (!out_count) return set_err(ctx, SEL_E_INVALID, "out_count is NULL");
   if (!check_prog(ctx, table, prog)) return SEL_E_INVALID;
   if (!d_out && cap > 0) return set_err(ctx, SEL_E_INVALID, "d_out is NULL with cap > 0");
-  const size_t need = RowidScratch(ntiles_of(table->nrows)).total();
+  const size_t need = RowidScratch(table->nrows).total();
   if (need > kNoAllocScratchBytes)
     return set_err(ctx, SEL_E_INVALID,
                    "table of " + std::to_string(table->nrows) + " rows needs " + std::to_string(need) +
@@ -734,14 +735,13 @@ sel_status sel_pushdown_keybitmap(sel_ctx* ctx, const sel_table* dim, uint32_t k
   ScanArgs a{};
   if (prog) {
     a.prog = prog->dcode;
-    a.nins = prog->nins;
+    a.nins = prog->scan_nins;
     set_stage(a, prog);
   } else {
     a.prog = ctx->dtrue;
     a.nins = 1;
   }
   a.nrows = dim->nrows;
-  a.ntiles = ntiles_of(dim->nrows);
   a.host = ctx->hout;
   a.key_data = kc.data;
   a.key_type = dev_type(kc.type);
@@ -889,27 +889,28 @@ sel_status sel_star_count(sel_ctx* ctx, const sel_table* fact, const sel_program
   sel_status st = build_star_code(ctx, fact, fact_pred, nfk, fk_cols, d_bitmaps, nbits, code, bpr, depth);
   if (st != SEL_OK) return st;
   DeviceGuard g(ctx->device);
-  st = stage_copy(ctx, ctx->dstar, code.data(), code.size() * sizeof(DevInstr));
-  if (st != SEL_OK) return st;
   std::vector<BatchBitmap> stage;
   const uint32_t stage_words = plan_scan_stage(code, stage);
-  if (!stage.empty()) {
-    st = stage_copy(ctx, ctx->dstage, stage.data(), stage.size() * sizeof(BatchBitmap));
-    if (st != SEL_OK) return st;
-  }
+  // the program and its staged bitmaps in one copy
+  const std::vector<DevInstr> scan = scan_code(code);
+  const size_t code_bytes = scan.size() * sizeof(DevInstr), stage_bytes = stage.size() * sizeof(BatchBitmap);
+  std::vector<uint8_t> image(code_bytes + stage_bytes);
+  std::memcpy(image.data(), scan.data(), code_bytes);
+  if (stage_bytes) std::memcpy(image.data() + code_bytes, stage.data(), stage_bytes);
+  st = stage_copy(ctx, ctx->dstar, image.data(), image.size());
+  if (st != SEL_OK) return st;
   ScanArgs a{};
   a.prog = ctx->dstar;
-  a.nins = (uint32_t)code.size();
-  a.stage = ctx->dstage;
+  a.nins = (uint32_t)scan.size();
+  a.stage = (const BatchBitmap*)((const char*)ctx->dstar + code_bytes);
   a.nstage = (uint32_t)stage.size();
   a.stage_words = stage_words;
   a.nrows = fact->nrows;
-  a.ntiles = ntiles_of(fact->nrows);
   a.host = ctx->hout;
   ctx->hout[0] = kPending;
   std::vector<uint32_t> stage_end;
   for (const BatchBitmap& b : stage) stage_end.push_back(b.lds_word + b.words + 1);
-  st = run_scan(ctx, M_COUNT, tune_class_of(bpr, a.nins), a, SEL_K_STAR, true, &stage_end);
+  st = run_scan(ctx, M_COUNT, tune_class_of(bpr, (uint32_t)code.size()), a, SEL_K_STAR, true, &stage_end);
   if (st == SEL_OK) st = wait_words(ctx, ctx->hout, 1, ctx->stream);
   if (st == SEL_OK) *out_count = ctx->hout[0];
   return st;
@@ -958,7 +959,9 @@ sel_status sel_program_star(sel_ctx* ctx, const sel_table* fact, const sel_progr
   p->dcode = (DevInstr*)p->dev;
   p->dstage = p->nstage ? (const BatchBitmap*)((char*)p->dev + code_bytes) : nullptr;
   std::vector<uint8_t> image(bytes);
-  std::memcpy(image.data(), code.data(), code_bytes);
+  const std::vector<DevInstr> scan = scan_code(code);
+  p->scan_nins = (uint32_t)scan.size();
+  std::memcpy(image.data(), scan.data(), scan.size() * sizeof(DevInstr));
   if (!stage.empty()) std::memcpy(image.data() + code_bytes, stage.data(), stage.size() * sizeof(BatchBitmap));
   st = stage_copy(ctx, p->dev, image.data(), bytes);
   if (st != SEL_OK) {

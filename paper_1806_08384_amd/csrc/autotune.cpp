@@ -100,14 +100,12 @@ sel_status sel_autotune(sel_ctx* ctx, const sel_table* table, const sel_program*
   const uint64_t ntiles = ntiles_of(table->nrows);
   ScanArgs a{};
   a.prog = prog->dcode;
-  a.nins = prog->nins;
+  a.nins = prog->scan_nins;
   set_stage(a, prog);
   a.nrows = table->nrows;
-  a.ntiles = ntiles;
   a.out = ctx->dout;
-  a.slot = ctx->slot;
   if (with_mask) {
-    const RowidScratch L(ntiles);
+    const RowidScratch L(table->nrows);
     sel_status st = ensure_scratch(ctx, L.total());
     if (st != SEL_OK) return st;
     a.mask = (uint32_t*)ctx->scratch;
@@ -116,20 +114,16 @@ sel_status sel_autotune(sel_ctx* ctx, const sel_table* table, const sel_program*
   }
   Candidate b{256, 0};
   double ms = 0;
-  const uint64_t need_waves = std::max<uint64_t>(1, ntiles);
   sel_launch cfg = kDefaultLaunch;
   auto launch_with = [&](const sel_launch& c) {
     ScanArgs x = a;
-    x.cached = c.cached;
-    x.tiles_per_step = c.tiles_per_step ? c.tiles_per_step : 1;
-    limit_stage(x, prog->stage_end, c.stage_words);
-    const uint64_t need = (need_waves + c.block / kWave - 1) / (c.block / kWave);
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(c.grid, need);
-    x.order = mask_order(x.nrows, grid * (c.block / kWave), (uint32_t)x.tiles_per_step);
-    return sel_launch_scan(mode, x, grid, c.block, ctx->stream);
+    return launch_scan(ctx, mode, x, c, &prog->stage_end);
   };
-  // the launch shape with the default knobs
-  sel_status st = time_candidates(ctx, candidates(ctx, mode, nullptr), reps, [&](const Candidate& c) {
+  // the launch shape with the default knobs; for a small table, also the
+  // library's own (grid 0: a quarter tile at a time)
+  std::vector<Candidate> shapes = candidates(ctx, mode, nullptr);
+  if (table->nrows <= kSmallScanRows) shapes.insert(shapes.begin(), {kDefaultLaunch.block, 0});
+  sel_status st = time_candidates(ctx, shapes, reps, [&](const Candidate& c) {
     sel_launch l = cfg;
     l.block = c.block;
     l.grid = c.grid;

@@ -728,45 +728,72 @@ int BatchPlan::launch(const BatchArgs& a, const TableBuild* d_builds, uint32_t g
   return sel_launch_batch(a, grid, block, lds_bytes(block), stream);
 }
 
-uint32_t plan_scan_stage(const std::vector<DevInstr>& code, std::vector<BatchBitmap>& out) {
+std::vector<DevInstr> scan_code(const std::vector<DevInstr>& code) {
+  std::vector<DevInstr> out;
+  out.reserve(code.size());
+  constexpr uint32_t joined = F_THEN_AND | F_THEN_OR;
+  for (const DevInstr& I : code) {
+    // in postfix, what follows a leaf takes its value from the stack's top
+    DevInstr* leaf = !out.empty() && (out.back().op < D_AND || out.back().op >= D_TRUE) ? &out.back() : nullptr;
+    if (leaf && !(leaf->flags & joined)) {
+      if (I.op == D_NOT) {
+        leaf->flags ^= F_THEN_NOT;
+        continue;
+      }
+      if (I.op == D_AND || I.op == D_OR) {
+        leaf->flags |= I.op == D_AND ? F_THEN_AND : F_THEN_OR;
+        continue;
+      }
+    }
+    out.push_back(I);
+  }
+  return out;
+}
+
+uint32_t plan_scan_stage(std::vector<DevInstr>& code, std::vector<BatchBitmap>& out) {
   out.clear();
   uint32_t words = 0;
+  for (DevInstr& I : code) I.lds_word = kNoLds;
   // IN lists first, at even word offsets for their int64 values: the two
   // cuckoo tables of a hashed list (two reads per row), else the sorted
   // list (log2(n) reads per row)
-  for (const DevInstr& I : code) {
-    if (I.op != D_INLIST || I.n == 0 || out.size() == kMaxStage) continue;
+  // the staged copy of the same constants, if there is one
+  auto seen = [&](const uint32_t* src, uint64_t w, uint32_t mask) {
+    for (const BatchBitmap& b : out)
+      if (b.src == src && b.words == w && b.last_mask == mask) return b.lds_word;
+    return kNoLds;
+  };
+  for (DevInstr& I : code) {
+    if (I.op != D_INLIST || I.n == 0) continue;
     const bool hashed = (I.flags & F_HASHED) != 0;
     const uint32_t* src = (const uint32_t*)I.aux + (hashed ? 2 * I.n : 0);
-    bool seen = false;
-    for (const BatchBitmap& b : out) seen |= b.src == src;
-    if (seen) continue;
     const uint32_t w = hashed ? 4u << in_hash_bits(I.flags) : 2 * I.n;
+    I.lds_word = seen(src, w, ~0u);
+    if (I.lds_word != kNoLds || out.size() == kMaxStage) continue;
     const uint32_t at = (words + 1) & ~1u;
     if (at + w + 1 > kScanStageWords) continue;
     BatchBitmap b{};
     b.src = src;
     b.words = w;
     b.last_mask = ~0u;
-    b.lds_word = at;
+    I.lds_word = b.lds_word = at;
     out.push_back(b);
     words = at + w + 1;
   }
-  for (const DevInstr& I : code) {
-    if (I.op != D_BITMAP || I.span == 0 || out.size() == kMaxStage) continue;
+  for (DevInstr& I : code) {
+    if (I.op != D_BITMAP || I.span == 0) continue;
     if (I.type != T_I64 &&
         (I.lo < INT32_MIN || I.lo > INT32_MAX || I.span - 1 > (uint64_t)(INT32_MAX - I.lo)))
       continue;
-    bool seen = false;
-    for (const BatchBitmap& b : out) seen |= b.src == (const uint32_t*)I.aux;
-    if (seen) continue;
     const uint64_t w = (I.span + 31) / 32;
-    if (words + w + 1 > kScanStageWords) continue;
+    const uint32_t last = I.span % 32 ? (1u << (I.span % 32)) - 1u : ~0u;
+    I.lds_word = seen((const uint32_t*)I.aux, w, last);
+    if (I.lds_word != kNoLds || out.size() == kMaxStage || words + w + 1 > kScanStageWords) continue;
     BatchBitmap b{};
     b.src = (const uint32_t*)I.aux;
     b.words = (uint32_t)w;
-    b.last_mask = I.span % 32 ? (1u << (I.span % 32)) - 1u : ~0u;
-    b.lds_word = words;
+    b.last_mask = last;
+    I.lds_word = b.lds_word = words;
     out.push_back(b);
     words += (uint32_t)w + 1;
   }

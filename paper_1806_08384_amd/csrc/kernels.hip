@@ -54,25 +54,49 @@ __device__ __forceinline__ uint64_t uni64(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Bitmaps of the program staged in the workgroup's LDS: a leaf whose bitmap
-// address is listed reads the copy (followed by a zero word) instead.
+// Constants of the program staged in the workgroup's LDS: a leaf whose
+// lds_word lies in the staged words reads the copy there (of a bitmap,
+// followed by a zero word) instead.
 struct StageView {
-  const CONSTANT BatchBitmap* list;
-  uint32_t n;
   const uint32_t* lds;
+  uint32_t words;
 };
 
+// An instruction in scalar registers, from one 64-byte scalar load: read field
+// by field where each is needed, a leaf was a chain of eight scalar-cache
+// round trips, and they, not the columns' loads, took most of a short scan.
+struct Ins {
+  uint32_t op, type, flags, n;
+  const void* data;
+  const uint32_t* valid;
+  int64_t lo;
+  uint64_t span;
+  const void* aux;
+  uint32_t lds_word;
+};
+typedef uint32_t v16u __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ uint64_t pair64(v16u w, int k) { return ((uint64_t)w[k + 1] << 32) | w[k]; }
+__device__ __forceinline__ Ins decode(v16u w) {
+  return Ins{w[0], w[1], w[2], w[3], (const void*)pair64(w, 4), (const uint32_t*)pair64(w, 6), (int64_t)pair64(w, 8),
+             pair64(w, 10), (const void*)pair64(w, 12), w[15]};
+}
+__device__ __forceinline__ Ins load_ins(CInstr p) { return decode(*(const CONSTANT v16u*)p); }
+
 // ---------------------------------------------------------------- loads --
-// Raw storage of one lane's 32 rows of a column in a full tile.  All loads
-// of a column are issued before any is used, so each lane keeps 32 rows of
-// loads in flight; they are nontemporal (streamed once, not re-read).
-// int64 columns are loaded in two halves of four steps (16 rows per lane),
-// so one half's loads (8 x 16 B per lane) are in flight at a time.
-template <int TY> struct Raw;
-template <> struct Raw<T_I8> { uint32_t w[kSteps]; };
-template <> struct Raw<T_I16> { v2i w[kSteps]; };
-template <> struct Raw<T_I32> { v4i w[kSteps]; };
-template <> struct Raw<T_I64> { v4i w[kSteps]; };
+// A wave takes NS steps of 256 rows at a time: a whole 2048-row tile (NS =
+// kSteps), or in a small table a quarter of one (kSmallSteps), so that four
+// times as many waves share it.
+//
+// Raw storage of one lane's 4 NS rows of a column.  All loads of a column are
+// issued before any is used, so each lane keeps its rows' loads in flight;
+// a tile's are nontemporal (streamed once, not re-read).  int64 columns are
+// loaded in groups of at most four steps (8 x 16 B per lane).
+template <int TY, int NS> struct Raw;
+template <int NS> struct Raw<T_I8, NS> { uint32_t w[NS]; };
+template <int NS> struct Raw<T_I16, NS> { v2i w[NS]; };
+template <int NS> struct Raw<T_I32, NS> { v4i w[NS]; };
+constexpr int group64(int ns) { return ns < 4 ? ns : 4; }
+template <int NS> struct Raw<T_I64, NS> { v4i w[2 * group64(NS)]; };
 
 // A streamed load: nontemporal (NT, the default) or through the caches as
 // usual; which one is faster is left to the tuner.
@@ -82,39 +106,51 @@ __device__ __forceinline__ T ldg(const GLOBAL T* p) {
   else return *p;
 }
 
-template <int TY, bool NT = true>
-__device__ __forceinline__ void load_full(Raw<TY>& r, const void* data, uint64_t tb, uint32_t lane) {
-  if constexpr (TY == T_I8) {
-    const GLOBAL uint32_t* p = gptr<uint32_t>((const int8_t*)data + tb) + lane;
-#pragma unroll
-    for (int j = 0; j < kSteps; ++j) r.w[j] = ldg<NT>(p + 64 * j);
-  } else if constexpr (TY == T_I16) {
-    const GLOBAL v2i* p = gptr<v2i>((const int16_t*)data + tb) + lane;
-#pragma unroll
-    for (int j = 0; j < kSteps; ++j) r.w[j] = ldg<NT>(p + 64 * j);
-  } else if constexpr (TY == T_I32) {
-    const GLOBAL v4i* p = gptr<v4i>((const int32_t*)data + tb) + lane;
-#pragma unroll
-    for (int j = 0; j < kSteps; ++j) r.w[j] = ldg<NT>(p + 64 * j);
-  }
+template <int TY>
+constexpr uint32_t type_width() { return TY == T_I8 ? 1u : TY == T_I16 ? 2u : TY == T_I32 ? 4u : 8u; }
+
+// Buffer resource over rows [tb, min(tb + span, nrows)) of a column: 32-bit
+// offsets from row tb, and a read past the table's last row returns zero
+// without touching memory.  The bound is in whole dwords, since the hardware
+// zeroes a dword that crosses it; the bytes up to the next 4-byte boundary
+// may be read.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t col_rsrc(const void* data, uint32_t width, uint64_t tb,
+                                                           uint64_t nrows, uint32_t span) {
+  const uint32_t rows = nrows - tb < (uint64_t)span ? (uint32_t)(nrows - tb) : span;
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)data + tb * width), (short)0,
+                                           (int)uni((rows * width + 3u) & ~3u), 0x00020000);
 }
 
-// one half (steps 4h .. 4h+3) of an int64 column
-template <bool NT = true>
-__device__ __forceinline__ void load_half64(Raw<T_I64>& r, const void* data, uint64_t tb,
-                                            uint32_t lane, int h) {
-  const GLOBAL v4i* p = gptr<v4i>((const int64_t*)data + tb) + 2 * lane + 128 * 4 * h;
+// Steps j0 .. of a column: every load of r, whole tiles by global loads, the
+// small scan's quarters by bounded buffer loads (3 % slower in the mask scan
+// of 300M rows, but right for a table's last rows too).
+template <int TY, int NS, bool NT>
+__device__ __forceinline__ void load_raw(Raw<TY, NS>& r, const void* data, uint64_t tb, uint64_t nrows,
+                                         uint32_t lane, int j0) {
+  using W = std::remove_reference_t<decltype(r.w[0])>;
+  constexpr int N = sizeof(r.w) / sizeof(W);
+  if constexpr (NS == kSteps) {
+    const GLOBAL W* p = gptr<W>((const char*)data + tb * type_width<TY>());
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    r.w[2 * j] = ldg<NT>(p + 128 * j);
-    r.w[2 * j + 1] = ldg<NT>(p + 128 * j + 1);
+    for (int k = 0; k < N; ++k)
+      r.w[k] = TY == T_I64 ? ldg<NT>(p + 2 * lane + 128 * (j0 + (k >> 1)) + (k & 1)) : ldg<NT>(p + lane + 64 * (j0 + k));
+  } else {
+    const __amdgpu_buffer_rsrc_t rs = col_rsrc(data, type_width<TY>(), tb, nrows, 256u * NS);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const uint32_t off = TY == T_I64 ? 32u * lane + 2048u * (uint32_t)(j0 + (k >> 1)) + 16u * (uint32_t)(k & 1)
+                                       : type_width<TY>() * (4u * lane + 256u * (uint32_t)(j0 + k));
+      if constexpr (TY == T_I8) r.w[k] = (W)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0);
+      else if constexpr (TY == T_I16) r.w[k] = (W)__builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+      else r.w[k] = (W)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+    }
   }
 }
 
 // value of row bit b (= 4*j + i) from the raw registers; b is a constant
 // after unrolling.  Narrow types are sign-extended to int32.
-template <int TY>
-__device__ __forceinline__ auto get(const Raw<TY>& r, int b) {
+template <int TY, int NS>
+__device__ __forceinline__ auto get(const Raw<TY, NS>& r, int b) {
   const int j = b >> 2, i = b & 3;
   if constexpr (TY == T_I8) {
     return (int32_t)(int8_t)(r.w[j] >> (8 * i));
@@ -122,7 +158,7 @@ __device__ __forceinline__ auto get(const Raw<TY>& r, int b) {
     return (int32_t)(int16_t)((uint32_t)r.w[j][i >> 1] >> (16 * (i & 1)));
   } else if constexpr (TY == T_I32) {
     return (int32_t)r.w[j][i];
-  } else {  // b indexes the loaded half: 0..15
+  } else {  // b indexes the loaded group
     const v4i& q = r.w[2 * j + (i >> 1)];
     const int k = 2 * (i & 1);
     return (int64_t)(((uint64_t)(uint32_t)q[k + 1] << 32) | (uint32_t)q[k]);
@@ -133,31 +169,33 @@ __device__ __forceinline__ uint64_t row_of(uint64_t tb, uint32_t lane, int b) {
   return tb + 256u * (uint32_t)(b >> 2) + 4u * lane + (uint32_t)(b & 3);
 }
 
-// Predicate bits of one lane's 32 rows of a whole tile: bit b = pred(value
-// of row b).  The word is built highest row first as P = 2P + bit, one
-// add-with-carry per row after the compare.
-template <int TY, bool NT = true, class Pred>
-__device__ __forceinline__ uint32_t pred_bits(const void* data, uint64_t tb, uint32_t lane, Pred pred) {
+// Predicate bits of one lane's rows: bit b = pred(value of row b).  The word
+// is built highest row first as P = 2P + bit, one add-with-carry per row
+// after the compare.  Rows past the table (small scans) test a zero; the
+// caller drops them.
+template <int TY, int NS, bool NT, class Pred>
+__device__ __forceinline__ uint32_t pred_bits(const void* data, uint64_t tb, uint64_t nrows, uint32_t lane, Pred pred) {
   uint32_t P = 0;
   if constexpr (TY == T_I64) {
+    constexpr int G = group64(NS);
 #pragma unroll
-    for (int h = 1; h >= 0; --h) {
-      Raw<TY> r;
-      load_half64<NT>(r, data, tb, lane, h);
+    for (int h = NS / G - 1; h >= 0; --h) {
+      Raw<TY, NS> r;
+      load_raw<TY, NS, NT>(r, data, tb, nrows, lane, G * h);
 #pragma unroll
-      for (int b = 15; b >= 0; --b) P = (P << 1) + (uint32_t)pred(get<TY>(r, b), 16 * h + b);
+      for (int b = 4 * G - 1; b >= 0; --b) P = (P << 1) + (uint32_t)pred(get<TY, NS>(r, b), 4 * G * h + b);
     }
   } else {
-    Raw<TY> r;
-    load_full<TY, NT>(r, data, tb, lane);
+    Raw<TY, NS> r;
+    load_raw<TY, NS, NT>(r, data, tb, nrows, lane, 0);
 #pragma unroll
-    for (int b = 31; b >= 0; --b) P = (P << 1) + (uint32_t)pred(get<TY>(r, b), b);
+    for (int b = 4 * NS - 1; b >= 0; --b) P = (P << 1) + (uint32_t)pred(get<TY, NS>(r, b), b);
   }
   return P;
 }
 
 // Validity bits of the lane's rows (all ones for a column without NULLs).
-template <bool FULL>
+template <bool FULL, int NS = kSteps>
 __device__ __forceinline__ uint32_t valid_bits(const uint32_t* valid, uint64_t tb, uint32_t lane,
                                                uint64_t nrows) {
   if (valid == nullptr) return ~0u;
@@ -165,36 +203,33 @@ __device__ __forceinline__ uint32_t valid_bits(const uint32_t* valid, uint64_t t
   const uint32_t sh = 4 * (lane & 7);
   uint32_t V = 0;
 #pragma unroll
-  for (int j = 0; j < kSteps; ++j) {
+  for (int j = 0; j < NS; ++j) {
     if (FULL || tb + 256u * j + 4u * lane < nrows)
       V |= ((vw[8 * j] >> sh) & 0xFu) << (4 * j);
   }
   return V;
 }
 
+// The lane's rows that the table holds.
+template <int NS>
 __device__ __forceinline__ uint32_t inrange_bits(uint64_t tb, uint32_t lane, uint64_t nrows) {
-  const int rows = nrows - tb < (uint64_t)kTileRows ? (int)(nrows - tb) : kTileRows;
+  const int rows = nrows - tb < 256ull * NS ? (int)(nrows - tb) : 256 * NS;
   uint32_t m = 0;
 #pragma unroll
-  for (int j = 0; j < kSteps; ++j)
+  for (int j = 0; j < NS; ++j)
     m |= ((1u << min(max(rows - (int)(256u * (uint32_t)j + 4u * lane), 0), 4)) - 1u) << (4 * j);
   return m;
 }
 
 // Values of rows 8q .. 8q + 7 of the lane (steps 2q, 2q + 1), as int64:
-// wide loads on a whole tile as for a range test; on the table's last,
-// partial tile the same wide loads through a buffer resource bounded to its
-// rows, past which they return zero without touching memory.  The bound is
-// in whole dwords, since the hardware zeroes a dword that crosses it; the
-// bytes up to the next 4-byte boundary may be read.
+// wide loads on a whole tile as for a range test; where the table may end the
+// same loads through a bounded buffer resource.
 template <int TY, bool FULL, bool NT>
 __device__ __forceinline__ void load8(const void* data, uint64_t tb, uint32_t lane, uint64_t nrows, int q,
                                       int64_t (&x)[8]) {
-  constexpr uint32_t width = TY == T_I8 ? 1u : TY == T_I16 ? 2u : TY == T_I32 ? 4u : 8u;
+  constexpr uint32_t width = type_width<TY>();
   const char* base = (const char*)data + tb * width;
-  const uint32_t rows = nrows - tb < (uint64_t)kTileRows ? (uint32_t)(nrows - tb) : (uint32_t)kTileRows;
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)uni((rows * width + 3u) & ~3u), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs = col_rsrc(data, width, tb, nrows, (uint32_t)kTileRows);
 #pragma unroll
   for (int js = 0; js < 2; ++js) {
     const uint32_t at = width * (256u * (uint32_t)(2 * q + js) + 4u * lane);   // byte offset of the lane's four rows
@@ -241,11 +276,11 @@ __device__ __forceinline__ void load8(const void* data, uint64_t tb, uint32_t la
 // SCAN: a scan's leaf, whose flags are DevFlags (a batch's copies of the
 // leaves reuse that word, and read an IN list through its sorted values).
 template <bool SCAN>
-__device__ __forceinline__ uint32_t partial_leaf(CInstr I, uint32_t ty, uint64_t tb, uint32_t lane, uint64_t nrows) {
-  const uint32_t op = I->op;
-  const void* data = I->data;
-  const int64_t lo = I->lo;
-  const uint64_t span = I->span;
+__device__ __forceinline__ uint32_t partial_leaf(const Ins& I, uint32_t ty, uint64_t tb, uint32_t lane, uint64_t nrows) {
+  const uint32_t op = I.op;
+  const void* data = I.data;
+  const int64_t lo = I.lo;
+  const uint64_t span = I.span;
   uint32_t P = 0;
 #pragma unroll 1
   for (int q = 3; q >= 0; --q) {
@@ -260,26 +295,26 @@ __device__ __forceinline__ uint32_t partial_leaf(CInstr I, uint32_t ty, uint64_t
 #pragma unroll
       for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)((uint64_t)x[k] - (uint64_t)lo <= span);
     } else if (op == D_BITMAP) {
-      const GLOBAL uint32_t* bits = gptr<uint32_t>(I->aux);
+      const GLOBAL uint32_t* bits = gptr<uint32_t>(I.aux);
 #pragma unroll
       for (int k = 7; k >= 0; --k) {
         const uint64_t d = (uint64_t)x[k] - (uint64_t)lo;
         const uint32_t at = d < span ? (uint32_t)d : 0u;   // nbits <= 2^32
         P = (P << 1) + ((uint32_t)(d < span) & ((bits[at >> 5] >> (at & 31)) & 1u));
       }
-    } else if (SCAN && (I->flags & F_HASHED)) {
-      const uint32_t f = I->flags, b = in_hash_bits(f);
+    } else if (SCAN && (I.flags & F_HASHED)) {
+      const uint32_t f = I.flags, b = in_hash_bits(f);
       const uint32_t c1 = kInHashMul[in_hash_pair(f)][0], c2 = kInHashMul[in_hash_pair(f)][1];
-      const GLOBAL int64_t* T = gptr<int64_t>(I->aux) + I->n;
+      const GLOBAL int64_t* T = gptr<int64_t>(I.aux) + I.n;
 #pragma unroll
       for (int k = 7; k >= 0; --k) {
         const int64_t h1 = T[in_hash(x[k], c1, b)], h2 = T[(1u << b) + in_hash(x[k], c2, b)];
         P = (P << 1) + ((uint32_t)(h1 == x[k]) | (uint32_t)(h2 == x[k]));
       }
     } else {  // D_INLIST: lower bound in the sorted list
-      const GLOBAL int64_t* list = gptr<int64_t>(I->aux);
+      const GLOBAL int64_t* list = gptr<int64_t>(I.aux);
       uint32_t base[8] = {};
-      for (uint32_t len = I->n; len > 1;) {
+      for (uint32_t len = I.n; len > 1;) {
         const uint32_t half = len >> 1;
 #pragma unroll
         for (int k = 0; k < 8; ++k) base[k] = list[base[k] + half] <= x[k] ? base[k] + half : base[k];
@@ -292,17 +327,18 @@ __device__ __forceinline__ uint32_t partial_leaf(CInstr I, uint32_t ty, uint64_t
   return P;
 }
 
-// IN-list test of a lane's 32 rows against a sorted list of n values (in
+// IN-list test of a lane's rows against a sorted list of n values (in
 // LDS or device memory): wide loads of the column as for a range test, then
 // a branch-free lower bound that moves the eight rows of two steps one
 // search step at a time, so that their list reads are in flight together.
-template <int TY, bool NT = true, class List>
-__device__ __forceinline__ uint32_t inlist_bits(const void* data, uint64_t tb, uint32_t lane, List list, uint32_t n, uint32_t need) {
+template <int TY, int NS, bool NT, class List>
+__device__ __forceinline__ uint32_t inlist_bits(const void* data, uint64_t tb, uint64_t nrows, uint32_t lane,
+                                                List list, uint32_t n, uint32_t need) {
   uint32_t P = 0;
 #pragma unroll 1
-  for (int q = 3; q >= 0; --q) {   // bits 8q .. 8q + 7: steps 2q, 2q + 1
+  for (int q = NS / 2 - 1; q >= 0; --q) {   // bits 8q .. 8q + 7: steps 2q, 2q + 1
     int64_t x[8];
-    load8<TY, true, NT>(data, tb, lane, tb + kTileRows, q, x);
+    load8<TY, NS == kSteps, NT>(data, tb, lane, nrows, q, x);
     uint32_t base[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) base[k] = 0;
@@ -323,14 +359,15 @@ __device__ __forceinline__ uint32_t inlist_bits(const void* data, uint64_t tb, u
 // then T + 2^b, in LDS or device memory): a value is in the list if and
 // only if it sits in its slot of either table, so two reads per row answer
 // it (empty slots hold a list value, which can only match a member).
-template <int TY, bool NT = true, class Tab>
-__device__ __forceinline__ uint32_t inhash_bits(const void* data, uint64_t tb, uint32_t lane, Tab T, uint32_t b, uint32_t c1, uint32_t c2, uint32_t need) {
+template <int TY, int NS, bool NT, class Tab>
+__device__ __forceinline__ uint32_t inhash_bits(const void* data, uint64_t tb, uint64_t nrows, uint32_t lane, Tab T,
+                                                uint32_t b, uint32_t c1, uint32_t c2, uint32_t need) {
   const uint32_t m = 1u << b;
   uint32_t P = 0;
 #pragma unroll 1
-  for (int q = 3; q >= 0; --q) {
+  for (int q = NS / 2 - 1; q >= 0; --q) {
     int64_t x[8];
-    load8<TY, true, NT>(data, tb, lane, tb + kTileRows, q, x);
+    load8<TY, NS == kSteps, NT>(data, tb, lane, nrows, q, x);
 #pragma unroll
     for (int k = 7; k >= 0; --k) {
       const bool hit = T[in_hash(x[k], c1, b)] == x[k] || T[m + in_hash(x[k], c2, b)] == x[k];
@@ -341,77 +378,64 @@ __device__ __forceinline__ uint32_t inhash_bits(const void* data, uint64_t tb, u
 }
 
 // ---------------------------------------------------------------- leaves --
-// A scan's leaf on a whole tile.
-template <int TY, bool NT>
-__device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb, uint32_t lane, uint32_t need,
+// A scan's leaf on a whole tile, or on a small scan's quarter of one.
+template <int TY, int NS, bool NT>
+__device__ __forceinline__ uint32_t leaf_pred(const Ins& I, uint64_t tb, uint64_t nrows, uint32_t lane, uint32_t need,
                                               const StageView& sv) {
-  const void* data = I->data;
-  const int64_t lo = I->lo;
-  const uint64_t span = I->span;
+  const uint32_t op = I.op;
+  const void* data = I.data;
+  const int64_t lo = I.lo;
+  const uint64_t span = I.span;
+  const bool staged = I.lds_word < sv.words;
+  const uint32_t* copy = sv.lds + I.lds_word;
   if (op == D_INLIST) {
-    const uint32_t f = I->flags;
+    const uint32_t f = I.flags;
     if (f & F_HASHED) {
       // the cuckoo tables after the sorted list: their LDS copy if staged
       const uint32_t b = in_hash_bits(f), c1 = kInHashMul[in_hash_pair(f)][0], c2 = kInHashMul[in_hash_pair(f)][1];
-      const uint32_t* tabs = (const uint32_t*)I->aux + 2 * I->n;
-      for (uint32_t k = 0; k < sv.n; ++k)
-        if (sv.list[k].src == tabs)
-          return inhash_bits<TY, NT>(data, tb, lane, (const int64_t*)(sv.lds + sv.list[k].lds_word), b, c1, c2, need);
-      return inhash_bits<TY, NT>(data, tb, lane, gptr<int64_t>(tabs), b, c1, c2, need);
+      if (staged) return inhash_bits<TY, NS, NT>(data, tb, nrows, lane, (const int64_t*)copy, b, c1, c2, need);
+      return inhash_bits<TY, NS, NT>(data, tb, nrows, lane, gptr<int64_t>((const int64_t*)I.aux + I.n), b, c1, c2, need);
     }
-    // the list's LDS copy if the scan staged it
-    for (uint32_t k = 0; k < sv.n; ++k)
-      if (sv.list[k].src == (const uint32_t*)I->aux)
-        return inlist_bits<TY, NT>(data, tb, lane, (const int64_t*)(sv.lds + sv.list[k].lds_word), I->n, need);
-    return inlist_bits<TY, NT>(data, tb, lane, gptr<int64_t>(I->aux), I->n, need);
+    if (staged) return inlist_bits<TY, NS, NT>(data, tb, nrows, lane, (const int64_t*)copy, I.n, need);
+    return inlist_bits<TY, NS, NT>(data, tb, nrows, lane, gptr<int64_t>(I.aux), I.n, need);
   }
-  if (op == D_BITMAP && sv.n) {
-    uint32_t off = kNoLds, z = 0;
-    for (uint32_t k = 0; k < sv.n; ++k) {
-      if (sv.list[k].src == (const uint32_t*)I->aux) {
-        off = sv.list[k].lds_word;
-        z = sv.list[k].words * 32;
-        break;
-      }
-    }
-    if (off != kNoLds) {
-      // an offset outside the window, or a row the guard skips, reads the
-      // zero bit z after the copy; for narrow columns the window lies inside
-      // int32 (the host stages only such bitmaps)
-      const uint32_t* bm = sv.lds + off;
-      if constexpr (TY == T_I64) {
-        return pred_bits<TY, NT>(data, tb, lane, [=](int64_t x, int b) -> uint32_t {
-          const uint64_t d = (uint64_t)x - (uint64_t)lo;
-          const uint32_t k = ((need >> b) & 1u) && d < z ? (uint32_t)d : z;
-          return (bm[k >> 5] >> (k & 31)) & 1u;
-        });
-      } else {
-        const uint32_t lo32 = (uint32_t)lo;
-        return pred_bits<TY, NT>(data, tb, lane, [=](int32_t x, int b) -> uint32_t {
-          const uint32_t d = (uint32_t)x - lo32;
-          const uint32_t k = ((need >> b) & 1u) && d < z ? d : z;
-          return (bm[k >> 5] >> (k & 31)) & 1u;
-        });
-      }
+  if (op == D_BITMAP && staged) {
+    // an offset outside the window, or a row the guard skips, reads the
+    // zero bit z after the copy; for narrow columns the window lies inside
+    // int32 (the host stages only such bitmaps)
+    const uint32_t z = (uint32_t)((span + 31u) & ~31ull);
+    if constexpr (TY == T_I64) {
+      return pred_bits<TY, NS, NT>(data, tb, nrows, lane, [=](int64_t x, int b) -> uint32_t {
+        const uint64_t d = (uint64_t)x - (uint64_t)lo;
+        const uint32_t k = ((need >> b) & 1u) && d < z ? (uint32_t)d : z;
+        return (copy[k >> 5] >> (k & 31)) & 1u;
+      });
+    } else {
+      const uint32_t lo32 = (uint32_t)lo;
+      return pred_bits<TY, NS, NT>(data, tb, nrows, lane, [=](int32_t x, int b) -> uint32_t {
+        const uint32_t d = (uint32_t)x - lo32;
+        const uint32_t k = ((need >> b) & 1u) && d < z ? d : z;
+        return (copy[k >> 5] >> (k & 31)) & 1u;
+      });
     }
   }
   if (op == D_RANGE) {
     if constexpr (TY == T_I64) {
-      return pred_bits<TY, NT>(data, tb, lane, [=](int64_t x, int) {
+      return pred_bits<TY, NS, NT>(data, tb, nrows, lane, [=](int64_t x, int) {
         return (uint64_t)x - (uint64_t)lo <= span;
       });
     } else {
       const uint32_t lo32 = (uint32_t)lo, span32 = (uint32_t)span;
-      return pred_bits<TY, NT>(data, tb, lane, [=](int32_t x, int) {
+      return pred_bits<TY, NS, NT>(data, tb, nrows, lane, [=](int32_t x, int) {
         return (uint32_t)x - lo32 <= span32;
       });
     }
   } else if (op == D_BITMAP) {
     // rows that need no test (guard) or fall outside [lo, lo + nbits) read
     // word 0 and are masked: no branch, so all 32 lookups issue together
-    const GLOBAL uint32_t* bits = gptr<uint32_t>(I->aux);
+    const GLOBAL uint32_t* bits = gptr<uint32_t>(I.aux);
     if constexpr (TY == T_I64) {
-      return pred_bits<TY, NT>(data, tb, lane, [=](int64_t x, int b) -> uint32_t {
+      return pred_bits<TY, NS, NT>(data, tb, nrows, lane, [=](int64_t x, int b) -> uint32_t {
         const uint64_t d = (uint64_t)x - (uint64_t)lo;
         const bool ok = d < span && ((need >> b) & 1u);
         const uint32_t k = ok ? (uint32_t)d : 0u;  // nbits <= 2^32
@@ -420,7 +444,7 @@ __device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb
     } else {
       // x - lo in 64 bits: a negative key must not alias a bit when nbits
       // exceeds 2^31
-      return pred_bits<TY, NT>(data, tb, lane, [=](int32_t x, int b) -> uint32_t {
+      return pred_bits<TY, NS, NT>(data, tb, nrows, lane, [=](int32_t x, int b) -> uint32_t {
         const uint64_t d = (uint64_t)((int64_t)x - lo);
         const bool ok = d < span && ((need >> b) & 1u);
         const uint32_t k = ok ? (uint32_t)d : 0u;
@@ -432,12 +456,12 @@ __device__ __forceinline__ uint32_t leaf_pred(uint32_t op, CInstr I, uint64_t tb
   }
 }
 
-template <bool FULL, bool NT = true>
-__device__ __forceinline__ void eval_leaf(uint32_t op, CInstr I, uint64_t tb, uint32_t lane,
+template <int NS, bool PARTIAL, bool NT>
+__device__ __forceinline__ void eval_leaf(const Ins& I, uint64_t tb, uint32_t lane,
                                           uint64_t nrows, uint32_t tos_t, uint32_t tos_f,
                                           uint32_t& t, uint32_t& f, const StageView& sv) {
-  const uint32_t* valid = I->valid;
-  const uint32_t V = valid_bits<FULL>(valid, tb, lane, nrows);
+  const uint32_t op = I.op;
+  const uint32_t V = valid_bits<NS == kSteps && !PARTIAL, NS>(I.valid, tb, lane, nrows);
   if (op >= D_NN_TRUE) {
     switch (op) {
       case D_NN_TRUE: t = V; f = 0; return;
@@ -446,19 +470,19 @@ __device__ __forceinline__ void eval_leaf(uint32_t op, CInstr I, uint64_t tb, ui
       default: t = V; f = ~V; return;  // D_NOTNULL
     }
   }
-  const uint32_t flags = I->flags;
+  const uint32_t flags = I.flags;
   uint32_t need = ~0u;
   if (flags & F_GUARD_AND) need = ~tos_f;
   else if (flags & F_GUARD_OR) need = ~tos_t;
   uint32_t P;
-  if constexpr (!FULL) {
-    P = partial_leaf<true>(I, I->type, tb, lane, nrows);
+  if constexpr (PARTIAL) {
+    P = partial_leaf<true>(I, I.type, tb, lane, nrows);
   } else {
-    switch (I->type) {
-      case T_I8: P = leaf_pred<T_I8, NT>(op, I, tb, lane, need, sv); break;
-      case T_I16: P = leaf_pred<T_I16, NT>(op, I, tb, lane, need, sv); break;
-      case T_I32: P = leaf_pred<T_I32, NT>(op, I, tb, lane, need, sv); break;
-      default: P = leaf_pred<T_I64, NT>(op, I, tb, lane, need, sv); break;
+    switch (I.type) {
+      case T_I8: P = leaf_pred<T_I8, NS, NT>(I, tb, nrows, lane, need, sv); break;
+      case T_I16: P = leaf_pred<T_I16, NS, NT>(I, tb, nrows, lane, need, sv); break;
+      case T_I32: P = leaf_pred<T_I32, NS, NT>(I, tb, nrows, lane, need, sv); break;
+      default: P = leaf_pred<T_I64, NS, NT>(I, tb, nrows, lane, need, sv); break;
     }
   }
   t = P & V;
@@ -466,51 +490,70 @@ __device__ __forceinline__ void eval_leaf(uint32_t op, CInstr I, uint64_t tb, ui
 }
 
 // ---------------------------------------------------------- interpreter --
-// The stack below the top is held in registers; its index is uniform, so
-// the unrolled selects below compile to scalar branches / v_cndmask and no
-// private memory is used.
-__device__ __forceinline__ void spill(uint32_t (&st)[kMaxDepth], uint32_t (&sf)[kMaxDepth],
+// The stack below its two top values is held in registers; its index is
+// uniform, so the unrolled selects below compile to scalar branches and no
+// private memory is used.  Few programs get there: the top two have
+// registers of their own.
+constexpr int kDeep = kMaxDepth - 2;
+__device__ __forceinline__ void spill(uint32_t (&st)[kDeep], uint32_t (&sf)[kDeep],
                                       int idx, uint32_t t, uint32_t f) {
 #pragma unroll
-  for (int k = 0; k < kMaxDepth; ++k)
+  for (int k = 0; k < kDeep; ++k)
     if (k == idx) { st[k] = t; sf[k] = f; }
 }
-__device__ __forceinline__ void fill(const uint32_t (&st)[kMaxDepth], const uint32_t (&sf)[kMaxDepth],
+__device__ __forceinline__ void fill(const uint32_t (&st)[kDeep], const uint32_t (&sf)[kDeep],
                                      int idx, uint32_t& t, uint32_t& f) {
   t = 0; f = 0;
 #pragma unroll
-  for (int k = 0; k < kMaxDepth; ++k)
+  for (int k = 0; k < kDeep; ++k)
     if (k == idx) { t = st[k]; f = sf[k]; }
 }
 
-// TRUE bits of the lane's 32 rows of the tile starting at row tb.
-template <bool FULL, bool NT = true>
+// TRUE bits of the lane's rows of the NS steps from row tb (bits past them,
+// and of rows past the table, are to be dropped by the caller unless the tile
+// is whole).  The host has folded a NOT, AND or OR that follows a leaf into
+// the leaf (scan_code), so that most programs run an instruction per leaf.
+template <int NS, bool PARTIAL, bool NT>
 __device__ __forceinline__ uint32_t eval_tile(CInstr prog, uint32_t nins, uint64_t tb,
                                               uint32_t lane, uint64_t nrows, const StageView& sv) {
-  uint32_t st[kMaxDepth], sf[kMaxDepth];
-  uint32_t tt = 0, tf = 0;
-  int d = 0;  // values on the stack; the top is (tt, tf)
+  uint32_t st[kDeep], sf[kDeep];
+  uint32_t tt = 0, tf = 0, ut = 0, uf = 0;
+  int d = 0;  // values on the stack; the top is (tt, tf), below it (ut, uf)
+  // the next instruction is asked for before the current one runs
+  v16u next = *(const CONSTANT v16u*)prog;
   for (uint32_t pc = 0; pc < nins; ++pc) {
-    CInstr I = prog + pc;
-    const uint32_t op = I->op;
-    if (op < D_AND || op == D_TRUE || op == D_FALSE) {
+    v16u cur = next;
+    asm volatile("" : "+s"(cur));
+    next = *(const CONSTANT v16u*)(prog + min(pc + 1u, nins - 1u));
+    const Ins I = decode(cur);
+    const uint32_t op = I.op;
+    if (op < D_AND || op >= D_TRUE) {
       uint32_t t, f;
       if (op == D_TRUE) { t = ~0u; f = 0; }
       else if (op == D_FALSE) { t = 0; f = ~0u; }
-      else eval_leaf<FULL, NT>(op, I, tb, lane, nrows, tt, tf, t, f, sv);
-      spill(st, sf, d - 1, tt, tf);
-      tt = t; tf = f;
-      ++d;
+      else eval_leaf<NS, PARTIAL, NT>(I, tb, lane, nrows, tt, tf, t, f, sv);
+      if (I.flags & F_THEN_NOT) { const uint32_t x = t; t = f; f = x; }
+      if (I.flags & F_THEN_AND) {
+        tt &= t;
+        tf |= f;
+      } else if (I.flags & F_THEN_OR) {
+        tt |= t;
+        tf &= f;
+      } else {
+        if (d >= 2) spill(st, sf, d - 2, ut, uf);
+        ut = tt; uf = tf;
+        tt = t; tf = f;
+        ++d;
+      }
     } else if (op == D_NOT) {
       const uint32_t x = tt; tt = tf; tf = x;
     } else if (op == D_ISUNK) {
       const uint32_t k = tt | tf; tt = ~k; tf = k;
     } else {
-      uint32_t at, af;
-      fill(st, sf, d - 2, at, af);
-      if (op == D_AND) { tt &= at; tf |= af; }
-      else { tt |= at; tf &= af; }
+      if (op == D_AND) { tt &= ut; tf |= uf; }
+      else { tt |= ut; tf &= uf; }
       --d;
+      if (d >= 2) fill(st, sf, d - 2, ut, uf);
     }
   }
   return tt;
@@ -547,8 +590,11 @@ __device__ __forceinline__ void put_host(unsigned long long* p, unsigned long lo
 // takes its ticket at once (kSlotTicket): the workgroup that sees all other
 // tickets also holds the total, publishes it and resets the slot for the next
 // launch.  Separate atomics (add, wait, ticket, read back) were four memory
-// latencies at the end of every launch instead of one.  The second count
-// (rare: out-of-range keys and ids) is added before the ticket.
+// latencies at the end of every launch instead of one.  Atomics on one word
+// take 9 ns each in turn, so that a grid of 768 workgroups that end together
+// waited 7 us: the workgroups share kSlotParts words, and the last of each
+// part adds its sum to the slot's.  The second count (rare: out-of-range keys
+// and ids) is added before the ticket.
 __device__ void finish(DevSlot* slot, unsigned long long* out, unsigned long long* host, uint32_t c0, uint32_t c1,
                        bool two) {
   __shared__ unsigned long long red0[16], red1[16];
@@ -557,42 +603,99 @@ __device__ void finish(DevSlot* slot, unsigned long long* out, unsigned long lon
   const uint32_t s1 = two ? wave_sum(c1) : 0u;
   if (lane == 0) { red0[wave] = s0; red1[wave] = s1; }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long b0 = 0, b1 = 0;
-    for (uint32_t w = 0; w < (blockDim.x >> 6); ++w) { b0 += red0[w]; b1 += red1[w]; }
-    if (b1) {
-      atomicAdd(&slot->acc2, b1);
-      atomics_done();
-    }
-    const unsigned long long old = atomicAdd(&slot->acc, kSlotTicket + b0);
-    if (old / kSlotTicket == gridDim.x - 1) {
-      const unsigned long long total = old % kSlotTicket + b0;
-      const unsigned long long second = two ? atomicExch(&slot->acc2, 0ull) : 0ull;
-      if (out) {
-        out[0] = total;
-        if (two) out[1] = second;
-      }
-      if (host) {
-        if (two) put_host(host + 1, second);
-        put_host(host, total);
-      }
-      atomicExch(&slot->acc, 0ull);
-    }
+  if (threadIdx.x != 0) return;
+  unsigned long long b0 = 0, b1 = 0;
+  for (uint32_t w = 0; w < (blockDim.x >> 6); ++w) { b0 += red0[w]; b1 += red1[w]; }
+  if (b1) {
+    atomicAdd(&slot->acc2, b1);
+    atomics_done();
   }
+  const uint32_t parts = min(gridDim.x, kSlotParts), part = blockIdx.x % kSlotParts;
+  unsigned long long* p = &slot->part[part * kSlotStride];
+  const unsigned long long here = atomicAdd(p, kSlotTicket + b0);
+  if (here / kSlotTicket != (gridDim.x - 1u - part) / kSlotParts) return;
+  atomicExch(p, 0ull);
+  const unsigned long long sum = here % kSlotTicket + b0;
+  const unsigned long long old = atomicAdd(&slot->acc, kSlotTicket + sum);
+  if (old / kSlotTicket != parts - 1u) return;
+  const unsigned long long total = old % kSlotTicket + sum;
+  const unsigned long long second = two ? atomicExch(&slot->acc2, 0ull) : 0ull;
+  if (out) {
+    out[0] = total;
+    if (two) out[1] = second;
+  }
+  if (host) {
+    if (two) put_host(host + 1, second);
+    put_host(host, total);
+  }
+  atomicExch(&slot->acc, 0ull);
 }
 
-template <int MODE, bool NT>
+// Key-bitmap push-down of one wave's rows: the keys of all its steps in a few
+// wide loads (a row at a time, each TRUE row of a lane waited for its own),
+// and one atomic for a lane's neighbouring keys in one word.
+template <int TY, int NS>
+__device__ __forceinline__ uint32_t put_keys(const ScanArgs& a, uint32_t T, uint64_t tb, uint32_t lane) {
+  constexpr int G = TY == T_I64 ? group64(NS) : NS;
+  uint32_t oor = 0, word = 0, bits = 0;
+#pragma unroll
+  for (int g = 0; g < NS / G; ++g) {
+    const __amdgpu_buffer_rsrc_t rs = col_rsrc(a.key_data, type_width<TY>(), tb, a.nrows, 256u * NS);
+    v4i w[TY == T_I64 ? 2 * G : G];
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof w / sizeof w[0]); ++k) {
+      const uint32_t off = TY == T_I64 ? 32u * lane + 2048u * (uint32_t)(G * g + (k >> 1)) + 16u * (uint32_t)(k & 1)
+                                       : 16u * lane + 1024u * (uint32_t)(G * g + k);
+      w[k] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+    }
+#pragma unroll
+    for (int b = 0; b < 4 * G; ++b) {
+      if (!((T >> (4 * G * g + b)) & 1u)) continue;
+      const int j = b >> 2, i = b & 3;
+      int64_t key;
+      if constexpr (TY == T_I64) {
+        const v4i& q = w[2 * j + (i >> 1)];
+        key = (int64_t)(((uint64_t)(uint32_t)q[2 * (i & 1) + 1] << 32) | (uint32_t)q[2 * (i & 1)]);
+      } else {
+        key = (int64_t)w[j][i];
+      }
+      const uint64_t d = (uint64_t)key - (uint64_t)a.key_min;
+      if (d >= a.nbits) {
+        ++oor;
+        continue;
+      }
+      const uint32_t at = (uint32_t)(d >> 5);
+      if (at != word && bits) {
+        atomicOr(&a.bitmap[word], bits);
+        bits = 0;
+      }
+      word = at;
+      bits |= 1u << (d & 31);
+    }
+  }
+  if (bits) atomicOr(&a.bitmap[word], bits);
+  return oor;
+}
+
+// NS = kSteps: tiles, by as many waves as fill the chip.  NS = kSmallSteps:
+// quarters of tiles, for tables where that many waves would have a tile or
+// two each: latency bounds those (six leaves in turn took 13 us a tile), so
+// more and shorter waves share the table.
+template <int MODE, bool NT, int NS>
 __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_, ScanArgs a) {
+  constexpr bool SMALL = NS != kSteps;
+  constexpr uint32_t kRows = 256u * NS, kWords = 8u * NS;   // of a tile, or a quarter
   CInstr prog = (CInstr)prog_;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t nw = blockDim.x >> 6;
   const uint64_t W = (uint64_t)gridDim.x * nw;
+  const uint64_t wid = uni64((uint64_t)blockIdx.x * nw + (threadIdx.x >> 6));
   extern __shared__ __align__(16) uint32_t sbm[];
-  const StageView sv{(const CONSTANT BatchBitmap*)a.stage, a.nstage, sbm};
+  const StageView sv{sbm, a.stage_words};
   if (a.nstage) {
     // the program's small bitmaps, each followed by a zero word
     for (uint32_t k = 0; k < a.nstage; ++k) {
-      const CONSTANT BatchBitmap* B = sv.list + k;
+      const CONSTANT BatchBitmap* B = (const CONSTANT BatchBitmap*)a.stage + k;
       const uint32_t n = B->words, last = B->last_mask;
       const GLOBAL uint32_t* src = gptr<uint32_t>(B->src);
       uint32_t* dst = sbm + B->lds_word;
@@ -616,7 +719,7 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
   uint64_t words = 0, place = 0;
   if constexpr (MODE == M_MASK) place = wave_place(a.order, (uint32_t)uni((uint32_t)(blockIdx.x * nw + (threadIdx.x >> 6))));
   auto put_group = [&](uint32_t turns) {
-    if (lane < cur) a.mask[(place * kWave + (uint64_t)blocks * kWave) + lane] = hold;
+    if (lane < cur) a.mask[place * kWords + (uint64_t)blocks * kWave + lane] = hold;
     if (lane < turns) {
       a.tile_words[place + lane] = words;
       a.tile_meta[place + lane] = meta;
@@ -626,13 +729,13 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
   };
   // Each wave takes runs of tps consecutive whole tiles, W runs apart.  A
   // partial last tile goes to the last wave, which has the fewest, before its
-  // others: at the end of the scan every other wave would wait for it.
+  // others: at the end of the scan every other wave would wait for it.  (A
+  // quarter's loads are bounded: the last one is like the others.)
   const uint64_t tps = a.tiles_per_step ? a.tiles_per_step : 1;
-  const uint64_t wid = uni64((uint64_t)blockIdx.x * nw + (threadIdx.x >> 6));
-  const uint64_t nfull = a.nrows / kTileRows;
+  const uint64_t nfull = SMALL ? a.ntiles : a.nrows / kTileRows;
   uint64_t run = wid * tps;
   uint32_t k = 0;
-  bool partial = wid == W - 1 && nfull < a.ntiles;
+  bool partial = !SMALL && wid == W - 1 && nfull < a.ntiles;
   for (;;) {
     uint64_t tile = nfull;
     if (!partial) {
@@ -643,12 +746,14 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
       tile = run + k++;
       if (tile >= nfull) break;
     }
-    const uint64_t tb = tile * kTileRows;
+    const uint64_t tb = tile * kRows;
     uint32_t T;
-    if (!partial) {
-      T = eval_tile<true, NT>(prog, a.nins, tb, lane, a.nrows, sv);
+    if constexpr (SMALL) {
+      T = eval_tile<NS, false, NT>(prog, a.nins, tb, lane, a.nrows, sv) & inrange_bits<NS>(tb, lane, a.nrows);
+    } else if (!partial) {
+      T = eval_tile<NS, false, NT>(prog, a.nins, tb, lane, a.nrows, sv);
     } else {
-      T = eval_tile<false, NT>(prog, a.nins, tb, lane, a.nrows, sv) & inrange_bits(tb, lane, a.nrows);
+      T = eval_tile<NS, true, NT>(prog, a.nins, tb, lane, a.nrows, sv) & inrange_bits<NS>(tb, lane, a.nrows);
       partial = false;
     }
     cnt += __builtin_popcount(T);
@@ -674,7 +779,7 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
       const uint32_t at = blocks * kWave + cur;
       hold = lane < cur ? hold : v;
       if (cur + n >= kWave) {
-        a.mask[(place * kWave + (uint64_t)blocks * kWave) + lane] = hold;
+        a.mask[place * kWords + (uint64_t)blocks * kWave + lane] = hold;
         ++blocks;
         hold = v;
       }
@@ -689,17 +794,8 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
         turn = 0;
       }
     } else if constexpr (MODE == M_KEYBITMAP) {
-      uint32_t m = T;
-      while (m) {
-        const int b = __builtin_ctz(m);
-        m &= m - 1;
-        const uint64_t row = row_of(tb, lane, b);
-        const int64_t key = a.key_type == T_I64 ? ((const int64_t*)a.key_data)[row]
-                                                : (int64_t)((const int32_t*)a.key_data)[row];
-        const uint64_t d = (uint64_t)key - (uint64_t)a.key_min;
-        if (d < a.nbits) atomicOr(&a.bitmap[d >> 5], 1u << (d & 31));
-        else ++oor;
-      }
+      if (__ballot(T != 0u))
+        oor += a.key_type == T_I64 ? put_keys<T_I64, NS>(a, T, tb, lane) : put_keys<T_I32, NS>(a, T, tb, lane);
     }
   }
   if constexpr (MODE == M_MASK) {
@@ -823,7 +919,8 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
   const uint32_t place = tile_place(a.order, tile, turn);
   const uint64_t nz = lane < nt ? a.tile_words[place] : 0ull;
   const uint32_t meta = a.tile_meta[place];
-  const uint32_t word0 = (place - turn % kMaskGroup) * (uint32_t)kWave + (meta >> kMetaShift);   // < 2^27
+  const uint32_t word0 = (place - turn % kMaskGroup) * (a.quarters ? 8u * kSmallSteps : (uint32_t)kWave) +
+                         (meta >> kMetaShift);   // < 2^27
   // ids before the wave's first tile
   uint32_t before = 0;
   if (a.offsets) {
@@ -842,6 +939,17 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
     hi[q] = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(nz >> 32), q);
     w0[q] = (uint32_t)__builtin_amdgcn_readlane((int)word0, q);
     sum[q + 1] = sum[q] + (uint32_t)(__builtin_popcount(lo[q]) + __builtin_popcount(hi[q]));
+  }
+  if (a.quarters) {
+    // a small scan's four quarters make a tile: word r of it in lane r
+    const uint32_t mlo = lo[0] | (lo[1] << 16), mhi = lo[2] | (lo[3] << 16);
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0u));
+    const uint32_t q = lane >> 4;
+    const uint32_t from = (q == 0 ? w0[0] : q == 1 ? w0[1] - sum[1] : q == 2 ? w0[2] - sum[2] : w0[3] - sum[3]) + rank;
+    const bool set = (((lane & 32u ? mhi : mlo) >> (lane & 31u)) & 1u) != 0u;
+    const uint32_t w = set ? a.mask[from] : 0u;
+    compact_tile(w, wave_sum(before), t0 / 4u, lane, a.out);
+    return;
   }
   if (sum[4] <= (uint32_t)kWave) {
     // All the wave's words at once, lane x the x-th: the tile it belongs to,
@@ -1344,7 +1452,7 @@ __device__ __forceinline__ void entry_leaves_partial(const CONSTANT BatchTable* 
     if (vs != kNoSlot) wl[vs * kWave + lane] = valid_bits<false>(C->valid, tb, lane, nrows);
     for (uint32_t k = 0; k < ln; ++k) {
       CInstr I = leaves + lb + k;
-      const uint32_t P = partial_leaf<false>(I, C->type, tb, lane, nrows);
+      const uint32_t P = partial_leaf<false>(load_ins(I), C->type, tb, lane, nrows);
       put_leaf(wl, lane, I->slot, P);
     }
   }
@@ -1545,7 +1653,7 @@ __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
       entry_leaves_full(E, cols, leaves, tb, lane, wl, bmlds, (const CONSTANT uint32_t*)a.ops);
     } else {
       entry_leaves_partial(E, cols, leaves, tb, lane, nrows, wl, (const CONSTANT uint32_t*)a.ops);
-      inr = inrange_bits(tb, lane, nrows);
+      inr = inrange_bits<kSteps>(tb, lane, nrows);
     }
     // programs in pairs: both popcounts (at most 2048 per wave each) share
     // one wave reduction, 16 bits apart
@@ -2460,17 +2568,25 @@ int sel_launch_scan(int mode, const ScanArgs& a, uint32_t grid, uint32_t block, 
   hipStream_t s = (hipStream_t)stream;
   const uint32_t lds = a.nstage ? 4u * a.stage_words : 0u;
   const bool nt = !a.cached;
+  if (a.small && block != 256) return (int)hipErrorInvalidValue;
+#define SCAN(...) hipLaunchKernelGGL((k_scan<__VA_ARGS__>), dim3(grid), dim3(block), lds, s, a.prog, a)
   switch (mode) {
     case M_COUNT:
-      if (nt) hipLaunchKernelGGL((k_scan<M_COUNT, true>), dim3(grid), dim3(block), lds, s, a.prog, a);
-      else hipLaunchKernelGGL((k_scan<M_COUNT, false>), dim3(grid), dim3(block), lds, s, a.prog, a);
+      if (a.small) SCAN(M_COUNT, false, kSmallSteps);
+      else if (nt) SCAN(M_COUNT, true, kSteps);
+      else SCAN(M_COUNT, false, kSteps);
       break;
     case M_MASK:
-      if (nt) hipLaunchKernelGGL((k_scan<M_MASK, true>), dim3(grid), dim3(block), lds, s, a.prog, a);
-      else hipLaunchKernelGGL((k_scan<M_MASK, false>), dim3(grid), dim3(block), lds, s, a.prog, a);
+      if (a.small) SCAN(M_MASK, false, kSmallSteps);
+      else if (nt) SCAN(M_MASK, true, kSteps);
+      else SCAN(M_MASK, false, kSteps);
       break;
-    default: hipLaunchKernelGGL((k_scan<M_KEYBITMAP, true>), dim3(grid), dim3(block), lds, s, a.prog, a); break;
+    default:
+      if (a.small) SCAN(M_KEYBITMAP, false, kSmallSteps);
+      else SCAN(M_KEYBITMAP, true, kSteps);
+      break;
   }
+#undef SCAN
   return (int)hipGetLastError();
 }
 
@@ -2516,13 +2632,10 @@ int sel_launch_fill(uint32_t* p, uint64_t nwords, uint32_t value, void* stream) 
 }
 
 int sel_scan_occupancy(int mode, uint32_t block, int* blocks_per_cu) {
-  hipError_t e;
-  switch (mode) {
-    case M_COUNT: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_scan<M_COUNT, true>, block, 0); break;
-    case M_MASK: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_scan<M_MASK, true>, block, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_scan<M_KEYBITMAP, true>, block, 0); break;
-  }
-  return (int)e;
+  const void* k = mode == M_COUNT  ? (const void*)k_scan<M_COUNT, true, kSteps>
+                  : mode == M_MASK ? (const void*)k_scan<M_MASK, true, kSteps>
+                                   : (const void*)k_scan<M_KEYBITMAP, true, kSteps>;
+  return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, block, 0);
 }
 
 int sel_launch_batch(const BatchArgs& a, uint32_t grid, uint32_t block, uint32_t lds_bytes,

@@ -80,6 +80,8 @@ class Arena {
 constexpr size_t kArenaBytes = 8u << 20;
 // Resident waves per CU of an untuned scan launch.
 constexpr int kScanWavesPerCu = 12;
+// LDS words of constants that a small scan's many short workgroups stage.
+constexpr uint32_t kSmallStageWords = 2048;
 constexpr size_t kStageBytes = 1u << 20;
 }  // namespace selrt
 
@@ -95,8 +97,8 @@ struct sel_ctx {
   unsigned long long* hout = nullptr;      // pinned host, 2 values
   char* hstage = nullptr;                  // pinned host staging (kStageBytes)
   hipEvent_t stage_free = nullptr;         // recorded after each copy out of hstage
-  DevInstr* dstar = nullptr;               // device, star-count program (128)
-  sel::BatchBitmap* dstage = nullptr;      // device, its staged bitmaps (kMaxStage)
+  DevInstr* dstar = nullptr;               // device, star-count program (up to 128)
+                                           // and its staged bitmaps (kMaxStage)
   DevInstr* dtrue = nullptr;               // device, the program TRUE
   void* arena_mem = nullptr;               // device, programs
   void* batch_mem = nullptr;               // device, sel_count_batch workspace
@@ -141,6 +143,7 @@ struct sel_program {
   uint32_t nstage = 0, stage_words = 0;
   std::vector<uint32_t> stage_end;  // per staged bitmap: the LDS words up to its end
   uint32_t nins = 0;
+  uint32_t scan_nins = 0;           // of the scan's code (dcode), see scan_code
   uint32_t tune_class = 0;          // bytes-per-row and length bucket
   int depth = 0;
   double bytes_per_row = 0.0;
@@ -194,21 +197,30 @@ inline uint32_t batch_class(uint32_t nprogs) {
 }
 // The launch configuration a context uses when the caller fixed none.
 constexpr sel_launch kDefaultLaunch{256, 0, 0, 1, 0, 0};
-void scan_shape(sel_ctx* ctx, int mode, uint32_t cls, uint64_t ntiles, sel_launch& cfg, uint32_t& grid,
-                uint32_t& block);
+// Launches a scan of a.nrows rows in a configuration: fills the rest of `a`
+// (tiles, knobs, mask order) and returns a hipError_t.
+int launch_scan(sel_ctx* ctx, int mode, sel::ScanArgs& a, const sel_launch& cfg,
+                const std::vector<uint32_t>* stage_end);
 sel_status run_scan(sel_ctx* ctx, int mode, uint32_t cls, sel::ScanArgs& a, int kind,
                     bool timed = true, const std::vector<uint32_t>* stage_end = nullptr);
 
-// Byte layout of the row-id path's workspace for a table of ntiles tiles:
+// Tables of up to this many rows are scanned a quarter tile at a time unless
+// the caller or the tuner chose a launch shape.
+constexpr uint64_t kSmallScanRows = 1u << 20;
+
+// Byte layout of the row-id path's workspace for a table of nrows rows:
 // the packed mask words, tile counts and offsets in their streams, tile id
 // offsets, chunk sums, tile word maps, in that order.
 struct RowidScratch {
   size_t mask, words, chunk, maps;
-  explicit RowidScratch(uint64_t ntiles)
-      : mask((size_t)ntiles * sel::kWave * 4),
-        words(((size_t)ntiles * 4 + 255) & ~size_t(255)),
-        chunk(2 * 2048 * 4),
-        maps(((size_t)ntiles * 8 + 255) & ~size_t(255)) {}
+  explicit RowidScratch(uint64_t nrows) {
+    const size_t ntiles = (size_t)((nrows + sel::kTileRows - 1) / sel::kTileRows);
+    const size_t units = nrows <= kSmallScanRows ? ntiles * (sel::kSteps / sel::kSmallSteps) : ntiles;
+    mask = ntiles * sel::kWave * 4;
+    words = (units * 4 + 255) & ~size_t(255);
+    chunk = 2 * 2048 * 4;
+    maps = (units * 8 + 255) & ~size_t(255);
+  }
   size_t o_meta() const { return mask; }
   size_t o_offsets() const { return mask + words; }
   size_t o_chunks() const { return mask + 2 * words; }
@@ -216,7 +228,7 @@ struct RowidScratch {
   size_t total() const { return o_maps() + maps; }
 };
 // The push-down of sel_pushdown_rowids with its workspace at `sp` (at least
-// RowidScratch(ntiles).total() bytes of device memory); arguments checked.
+// RowidScratch(nrows).total() bytes of device memory); arguments checked.
 sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_program* prog,
                                 uint64_t max_rows, uint32_t* d_out, uint64_t cap,
                                 uint64_t* out_count, char* sp, bool timed);
@@ -321,9 +333,13 @@ std::vector<std::pair<size_t, size_t>> and_factors(const std::vector<sel::DevIns
 uint32_t batch_slots_alone(const sel_program* p);
 // The bitmaps of a program that a single-program scan stages in LDS: in
 // program order, distinct, windows inside int32 for narrow columns, at most
-// kScanStageWords words with one zero word after each.  Returns the words.
+// kScanStageWords words with one zero word after each.  Sets every leaf's
+// lds_word (kNoLds: not staged) and returns the words.
 constexpr uint32_t kMaxStage = 64;
-uint32_t plan_scan_stage(const std::vector<DevInstr>& code, std::vector<sel::BatchBitmap>& out);
+// The form of a program that the scan kernels run: a NOT, AND or OR right
+// after a leaf becomes a flag of the leaf.
+std::vector<DevInstr> scan_code(const std::vector<DevInstr>& code);
+uint32_t plan_scan_stage(std::vector<DevInstr>& code, std::vector<sel::BatchBitmap>& out);
 inline void set_stage(sel::ScanArgs& a, const sel_program* p) {
   a.stage = p ? p->dstage : nullptr;
   a.nstage = p ? p->nstage : 0;

@@ -18,6 +18,7 @@ constexpr int kWave = 64;
 constexpr int kRowsPerStep = 4;
 constexpr int kSteps = 8;
 constexpr int kTileRows = kWave * kRowsPerStep * kSteps;  // 2048
+constexpr int kSmallSteps = 2;                            // of a small scan's quarter tile
 constexpr int kMaxDepth = 8;
 
 // Bytes of the fixed device workspace of the push-down that allocates
@@ -48,9 +49,14 @@ enum DevFlags : uint32_t {
   F_GUARD_AND = 1,  // leaf is the right operand of the next AND: rows whose
                     // left operand is FALSE need not be evaluated
   F_GUARD_OR = 2,   // ... of the next OR: rows whose left operand is TRUE
-  F_HASHED = 4      // D_INLIST: two cuckoo tables follow the sorted list;
+  F_HASHED = 4,     // D_INLIST: two cuckoo tables follow the sorted list;
                     // bits 8..12 hold their log2 size, bits 16..18 the
                     // multiplier pair
+  // in a scan's code (scan_code), of any leaf or constant: its truth is
+  // negated, and ANDed or ORed with the value below instead of being pushed
+  F_THEN_NOT = 8,
+  F_THEN_AND = 16,
+  F_THEN_OR = 32
 };
 
 // IN lists of up to kInHashMax values also get two cuckoo tables of
@@ -82,23 +88,28 @@ struct DevInstr {          // 64 bytes, read with scalar loads
   uint64_t span;           // D_RANGE: hi - lo (unsigned) / D_BITMAP: nbits
   const void* aux;         // D_BITMAP words / D_INLIST values
   uint32_t slot;           // batched evaluation: LDS slot of the leaf's word
-  uint32_t lds_word;       // batched D_BITMAP: offset of its staged copy in
-                           // LDS (n = index of a zero bit past it), or kNoLds
+  uint32_t lds_word;       // offset of the staged copy in LDS, or kNoLds
+                           // (batched D_BITMAP: n = index of a zero bit past it)
 };
 static_assert(sizeof(DevInstr) == 64, "DevInstr layout");
 
-// Per-launch completion slot: counters that the last workgroup resets, so
+// Per-launch completion slot: counters that the last workgroups reset, so
 // that no memset is needed between launches.  A scan's workgroups add their
 // counts and take their tickets in one word: the low 40 bits hold the count
-// (at most 2^32), the high 24 the workgroups done.
+// (at most 2^32), the high 24 the workgroups done -- first in one of
+// kSlotParts words, each in a cache line of its own, whose last workgroups
+// then do the same in `acc`.
 constexpr unsigned long long kSlotTicket = 1ull << 40;
 constexpr uint32_t kSlotMaxGrid = 1u << 24;
+constexpr uint32_t kSlotParts = 16, kSlotStride = 16;
 struct DevSlot {
-  unsigned long long acc;    // running count and tickets of a scan
+  unsigned long long acc;    // running count and tickets of a scan's parts
   unsigned long long acc2;   // second counter (out-of-range keys)
   unsigned int ticket;       // a batch launch's ticket
-  unsigned int pad[3];
+  unsigned int pad[27];
+  unsigned long long part[kSlotParts * kSlotStride];   // of a scan
 };
+static_assert(sizeof(DevSlot) == 128 + 128 * kSlotParts, "DevSlot layout");
 
 enum ScanMode : int { M_COUNT = 0, M_MASK = 1, M_KEYBITMAP = 2 };
 
@@ -120,12 +131,14 @@ struct MaskOrder {
 #else
 #define SEL_HD
 #endif
-SEL_HD inline MaskOrder mask_order(uint64_t nrows, uint32_t waves, uint32_t tps) {
+// small: the tiles are quarters, of which the last is like the others.
+SEL_HD inline MaskOrder mask_order(uint64_t nrows, uint32_t waves, uint32_t tps, bool small) {
+  constexpr uint32_t quarter = 256u * kSmallSteps;
   MaskOrder o{};
   o.waves = waves;
   o.tps = tps;
-  o.nfull = (uint32_t)(nrows / kTileRows);
-  o.partial = nrows % kTileRows ? 1u : 0u;
+  o.nfull = small ? (uint32_t)((nrows + quarter - 1) / quarter) : (uint32_t)(nrows / kTileRows);
+  o.partial = !small && nrows % kTileRows ? 1u : 0u;
   const uint32_t runs = (o.nfull + tps - 1) / tps;
   o.runs_q = runs / waves;
   o.runs_r = runs % waves;
@@ -142,7 +155,7 @@ SEL_HD inline uint32_t tile_place(const MaskOrder& o, uint32_t tile, uint32_t& t
   const uint32_t run = tile / o.tps, round = run / o.waves;
   uint32_t w = run - round * o.waves;
   turn = round * o.tps + (tile - run * o.tps);
-  if (tile == o.nfull) {         // the partial tile
+  if (o.partial && tile == o.nfull) {   // the partial tile
     w = o.waves - 1;
     turn = 0;
   } else if (o.partial && w == o.waves - 1) {
@@ -166,6 +179,7 @@ struct ScanArgs {
   uint32_t nstage;             // bitmaps the workgroups copy to LDS first
   uint32_t cached;             // 1: column loads through the caches (0: nontemporal)
   uint32_t tiles_per_step;     // consecutive tiles a wave takes per step (0: 1)
+  uint32_t small;              // 1: k_scan takes quarter tiles (ntiles of them)
   uint64_t nrows;
   uint64_t ntiles;
   DevSlot* slot;
@@ -173,8 +187,8 @@ struct ScanArgs {
   unsigned long long* host;    // the same in pinned host memory, may be null
   // M_MASK, by place (MaskOrder): the result words (of 32 rows in table
   // order) that hold a TRUE row, of each group of kMaskGroup turns one packed
-  // stream in turn and row order, at the 64-word slot of the group's first
-  // place (the rest is not written); per tile the map of its words that are
+  // stream in turn and row order, at the slot (a word per 32 rows of a tile)
+  // of the group's first place (the rest is not written); per tile the map of its words that are
   // there, and its count and offset
   uint32_t* mask;
   uint64_t* tile_words;
@@ -209,6 +223,7 @@ struct CompactArgs {
   MaskOrder order;
   uint32_t ntiles;
   uint32_t tiles_per_wave;     // 1 or 4
+  uint32_t quarters;           // 1: a small scan's quarter tiles (4 a wave)
   uint32_t* out;
   // the count the mask pass published; the compaction writes nothing when
   // it is 0 or above `limit` (Algorithm 1's maxSize, or the capacity)

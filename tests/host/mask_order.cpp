@@ -9,9 +9,10 @@
 
 using namespace sel;
 
-static int check(uint64_t nrows, uint32_t waves, uint32_t tps) {
-  const MaskOrder o = mask_order(nrows, waves, tps);
-  const uint32_t ntiles = (uint32_t)((nrows + kTileRows - 1) / kTileRows), nfull = (uint32_t)(nrows / kTileRows);
+static int check(uint64_t nrows, uint32_t waves, uint32_t tps, bool small = false) {
+  const MaskOrder o = mask_order(nrows, waves, tps, small);
+  const uint32_t rows = small ? 256 * kSmallSteps : kTileRows;
+  const uint32_t ntiles = (uint32_t)((nrows + rows - 1) / rows), nfull = small ? ntiles : (uint32_t)(nrows / rows);
   std::vector<char> seen(ntiles, 0);
   for (uint32_t w = 0; w < waves; ++w) {
     uint32_t turn = 0, place = wave_place(o, w);
@@ -50,6 +51,7 @@ int main() {
       for (uint32_t tiles = 0; tiles <= 1100; tiles += tiles < 70 ? 1 : 37)
         for (uint32_t tail : {0u, 1u, 2047u}) {
           if (check((uint64_t)tiles * kTileRows + tail, waves, tps)) return 1;
+          if (tps == 1 && check((uint64_t)tiles * kTileRows + tail, waves, tps, true)) return 1;
           ++n;
         }
   if (check((1ull << 32) - 1, 3072, 1) || check((1ull << 32) - 1, 1, 4)) return 1;

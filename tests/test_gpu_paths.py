@@ -136,3 +136,43 @@ def test_row_ids_by_density(sel, ctx, tiles, most):
         np.testing.assert_array_equal(as_u32(out)[:-1], want)
         assert as_u32(out)[-1] == 0xDEADBEEF
     ctx.set_launch()
+
+
+@pytest.mark.parametrize("n", [1, 255, 511, 512, 513, 2048 * 37 + 1, (1 << 20) - 1, 1 << 20, (1 << 20) + 1])
+def test_small_scan_sizes(sel, ctx, n):
+    """Tables on both sides of the small scan's limit and of its quarter
+    tiles, by the library's own launch and by a fixed one: counts, ids and key
+    bitmaps, with a staged bitmap, a list too long for the small scan's LDS, a
+    two-sided stack and NOTs and constants that fold into the leaf before."""
+    rng = np.random.default_rng(n)
+    t = datagen.random_table(rng, n, grid=False, null_rate=0.2)
+    t.columns.append(datagen.Column("row", "i32", rng.permutation(n).astype(np.int32)))
+    t.columns.append(datagen.Column("far", "i64", rng.integers(-2 ** 40, 2 ** 40, n)))
+    t.columns.append(datagen.Column("code", "i32", rng.integers(0, 99_000, n).astype(np.int32), dict_card=99_000))
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+    half = datagen.words_from_codes(rng.choice(99_000, 40_000, replace=False), 99_000)
+    few = datagen.words_from_codes(range(0, 60, 7), 60)
+    many = tuple(int(v) for v in np.concatenate([rng.choice(t.columns[5].data, min(n, 900)),
+                                                 rng.integers(-2 ** 40, 2 ** 40, 100)]))
+    a, b, c, d = (("cmp", 0, ">", 2), ("between", 1, -9, 9), ("codeset", 6, 99_000, half), ("in", 5, many))
+    trees = [a, c, d, ("codeset", 6, 60, few), ("and", ("not", a), c), ("or", ("not", ("not", d)), ("isnull", 2)),
+             ("or", ("and", a, b), ("and", c, ("not", d))), ("and", ("true",), ("or", ("false",), b)),
+             ("not", ("and", ("or", a, c), ("or", b, ("isunknown", ("cmp", 3, "<", 0))))),
+             ("or", ("and", ("or", a, b), ("or", c, d)), ("and", ("or", b, ("notnull", 3)), ("or", ("not", a), d)))]
+    say(f"small scan: {n} rows")
+    if n > 100_000:
+        trees = trees[4:6] + trees[9:]
+    for shape in (None, dict(block=256, grid=40), dict(block=64, grid=7, cached=1)):
+        ctx.set_launch(**shape) if shape else ctx.set_launch()
+        for tree in trees:
+            check(sel, ctx, dt, orc, tree)
+            prog = ctx.program(dt, tree)
+            for lo, bits in ((0, n), (n // 3, max(1, n // 2)))[:1 if n > 100_000 else 2]:
+                bm = torch.full(((bits + 31) // 32,), -1, dtype=torch.int32, device="cuda")
+                st, cnt = ctx.pushdown_keybitmap(dt, 4, lo, prog, bm, bits)
+                ost, ocnt, words = orc.keybitmap(tree, 4, lo, bits)
+                assert (st == sel.SEL_OK) == (ost == 0) and cnt == ocnt
+                if st == sel.SEL_OK:
+                    np.testing.assert_array_equal(as_u32(bm), words)
+    ctx.set_launch()
