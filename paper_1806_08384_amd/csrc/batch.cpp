@@ -26,7 +26,7 @@ struct sel_batch {
   uint32_t* d_gtab = nullptr;
   const TableBuild* d_builds = nullptr;       // as captured
   uint32_t nbuilds = 0;
-  uint64_t table_entries = 0;
+  uint64_t table_units = 0;
   unsigned long long* d_acc = nullptr;
   DevSlot* d_slot = nullptr;
   unsigned long long* h_out = nullptr;        // pinned
@@ -217,7 +217,7 @@ sel_status rebuild(sel_batch* b) {
   const uint32_t llds = b->plan.lut.empty() ? 0u : b->plan.lut.lds_bytes();
   if (b->exec && std::memcmp(&a, &b->args, sizeof a) == 0 && grid == b->grid && block == b->block &&
       lds == b->lds && d_builds == b->d_builds && nbuilds == b->nbuilds &&
-      b->plan.table_entries == b->table_entries &&
+      b->plan.table_units == b->table_units &&
       std::memcmp(&b->plan.largs, &b->largs, sizeof b->largs) == 0 && lgrid == b->lut_grid &&
       lblock == b->lut_block && llds == b->lut_lds)
     return SEL_OK;
@@ -231,7 +231,7 @@ sel_status rebuild(sel_batch* b) {
   b->lds = lds;
   b->d_builds = d_builds;
   b->nbuilds = nbuilds;
-  b->table_entries = b->plan.table_entries;
+  b->table_units = b->plan.table_units;
   // the capture stream must see the uploads before its first replay
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
   return capture(b);

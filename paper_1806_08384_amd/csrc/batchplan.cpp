@@ -443,7 +443,7 @@ void BatchPlan::clear() {
   col_gtab.clear();
   builds.clear();
   gtab_words = 0;
-  table_entries = 0;
+  table_units = 0;
   total_tiles = 0;
   max_slots = 0;
 }
@@ -541,11 +541,11 @@ void BatchPlan::add(const sel_table* t, uint64_t row_begin, uint64_t row_end,
         tbd.leaves = (const DevInstr*)(uintptr_t)bc.leaf_begin;  // index until written
         tbd.lo = c.tab_lo;
         tbd.n = c.tab_n;
-        tbd.entry_begin = table_entries;
+        tbd.unit_begin = table_units;
         tbd.m = c.tab_count;
         builds.push_back(tbd);
         col_gtab.back() = gtab_words;
-        table_entries += (uint64_t)c.tab_n + 1;
+        table_units += ((uint64_t)c.tab_n + kTableUnit) / kTableUnit;
         const uint64_t bytes = ((uint64_t)c.tab_n + 1) * tab_entry_bytes(c.tab_count);
         gtab_words += ((bytes + 255) & ~255ull) / 4;   // 256-byte aligned tables
       }
@@ -722,7 +722,7 @@ int BatchPlan::launch(const BatchArgs& a, const TableBuild* d_builds, uint32_t g
   }
   if (!leaf) return 0;
   if (!builds.empty()) {
-    const int e = sel_launch_tables(d_builds, (uint32_t)builds.size(), table_entries, stream);
+    const int e = sel_launch_tables(d_builds, (uint32_t)builds.size(), table_units, stream);
     if (e) return e;
   }
   return sel_launch_batch(a, grid, block, lds_bytes(block), stream);

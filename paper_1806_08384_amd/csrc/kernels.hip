@@ -1714,39 +1714,84 @@ __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
   }
 }
 
-// Device-memory lookup tables of a batch (one thread per entry; the bitmap
-// words of neighbouring entries are shared, so the reads coalesce).
-__global__ void __launch_bounds__(256) k_tables(const TableBuild* __restrict__ tb, uint32_t nb,
-                                                uint64_t nentries) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nentries; e += stride) {
-    uint32_t lo = 0, hi = nb;
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (tb[mid].entry_begin <= e) lo = mid; else hi = mid;
+// Bits r (of 32) with a <= r < b.
+__device__ __forceinline__ uint32_t span_bits(int64_t a, int64_t b) {
+  const uint32_t lo = (uint32_t)(a < 0 ? 0 : a > 32 ? 32 : a), hi = (uint32_t)(b < 0 ? 0 : b > 32 ? 32 : b);
+  const uint32_t below = hi < 32u ? (1u << hi) - 1u : ~0u;
+  return lo < 32u ? below & (~0u << lo) : 0u;
+}
+
+// Device-memory lookup tables of a batch: a thread takes 32 entries, for which
+// each leaf's truth is one word (a range's bits, or two neighbouring words of
+// its bitmap), and transposes the leaves' words into entries.  A wave works on
+// one table, so the leaves are scalar loads, and all bitmap words are in
+// flight together.  (A thread per entry, testing one leaf after another, took
+// 93 us for the tables of 16 star programs over a 3.2M-key dimension.)
+__global__ void __launch_bounds__(256) k_tables(const TableBuild* __restrict__ tb_, uint32_t nb, uint64_t nunits) {
+  const CONSTANT TableBuild* tb = (const CONSTANT TableBuild*)tb_;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t unit = uni64((uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6));
+  if (unit >= nunits) return;
+  uint32_t lo = 0, hi = nb;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (tb[mid].unit_begin <= unit) lo = mid; else hi = mid;
+  }
+  const CONSTANT TableBuild* B = tb + uni(lo);
+  const uint64_t e0 = (unit - B->unit_begin) * kTableUnit + 32u * lane;   // first entry
+  const uint64_t n = B->n;
+  const uint32_t m = B->m;
+  if (e0 > n) return;
+  const int64_t x0 = B->lo + (int64_t)e0;
+  const uint32_t inside = span_bits(0, (int64_t)(n - e0));   // entry n is zero
+  CInstr leaves = (CInstr)B->leaves;
+  uint32_t a[32];
+#pragma unroll
+  for (int k = 0; k < 32; ++k) {
+    a[k] = 0;
+    if ((uint32_t)k >= m) continue;
+    CInstr I = leaves + k;
+    const int64_t at = (int64_t)((uint64_t)I->lo - (uint64_t)x0);
+    if (I->op == D_RANGE) {
+      a[k] = span_bits(at, at + (int64_t)I->span + 1) & inside;
+    } else {  // D_BITMAP
+      const GLOBAL uint32_t* bits = gptr<uint32_t>(I->aux);
+      const int64_t span = (int64_t)I->span, w = -at >> 5, words = (span + 31) >> 5;   // floor
+      const uint32_t sh = (uint32_t)-at & 31u;
+      const uint32_t w0 = w >= 0 && w < words ? bits[w] : 0u;
+      const uint32_t w1 = w + 1 >= 0 && w + 1 < words ? bits[w + 1] : 0u;
+      a[k] = (uint32_t)((((uint64_t)w1 << 32) | w0) >> sh) & span_bits(at, at + span) & inside;
     }
-    const TableBuild& B = tb[lo];
-    const uint64_t i = e - B.entry_begin;
-    uint32_t w = 0;
-    if (i < B.n) {
-      const int64_t x = B.lo + (int64_t)i;
-      for (uint32_t k = 0; k < B.m; ++k) {
-        const DevInstr& I = B.leaves[k];
-        const uint64_t d = (uint64_t)x - (uint64_t)I.lo;
-        uint32_t bit;
-        if (I.op == D_RANGE) {
-          bit = d <= I.span;
-        } else {  // D_BITMAP
-          const uint32_t* bits = (const uint32_t*)I.aux;
-          bit = d < I.span ? (bits[d >> 5] >> (d & 31)) & 1u : 0u;
-        }
-        w |= bit << k;
-      }
+  }
+  transpose32<32>(a);
+  const uint32_t eb = tab_entry_bytes(m);
+  uint8_t* dst = (uint8_t*)B->dst + e0 * eb;
+  const uint32_t cnt = n + 1 - e0 < 32u ? (uint32_t)(n + 1 - e0) : 32u;
+  if (cnt < 32u) {
+#pragma unroll
+    for (int r = 0; r < 32; ++r) {
+      if ((uint32_t)r >= cnt) continue;
+      if (eb == 1) dst[r] = (uint8_t)a[r];
+      else if (eb == 2) ((uint16_t*)dst)[r] = (uint16_t)a[r];
+      else ((uint32_t*)dst)[r] = a[r];
     }
-    const uint32_t eb = tab_entry_bytes(B.m);
-    if (eb == 1) ((uint8_t*)B.dst)[i] = (uint8_t)w;
-    else if (eb == 2) ((uint16_t*)B.dst)[i] = (uint16_t)w;
-    else B.dst[i] = w;
+  } else if (eb == 4) {
+#pragma unroll
+    for (int r = 0; r < 32; r += 4) ((v4u*)dst)[r / 4] = v4u{a[r], a[r + 1], a[r + 2], a[r + 3]};
+  } else if (eb == 2) {
+#pragma unroll
+    for (int r = 0; r < 32; r += 8)
+      ((v4u*)dst)[r / 8] = v4u{a[r] | (a[r + 1] << 16), a[r + 2] | (a[r + 3] << 16), a[r + 4] | (a[r + 5] << 16),
+                               a[r + 6] | (a[r + 7] << 16)};
+  } else {
+#pragma unroll
+    for (int r = 0; r < 32; r += 16) {
+      v4u q;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        q[c] = a[r + 4 * c] | (a[r + 4 * c + 1] << 8) | (a[r + 4 * c + 2] << 16) | (a[r + 4 * c + 3] << 24);
+      ((v4u*)dst)[r / 16] = q;
+    }
   }
 }
 
@@ -1759,9 +1804,9 @@ __global__ void __launch_bounds__(256) k_tables(const TableBuild* __restrict__ t
 // Truth of a literal (a leaf test, possibly negated) on a row: `nonnull`
 // says whether the row's value is present, `inwin` whether x lies in the
 // window of the column's value tests (outside it every value test is FALSE).
-__device__ __forceinline__ bool lit_true(const DevInstr& L, bool nonnull, bool inwin, int64_t x) {
-  const bool neg = (L.flags & kLitNeg) != 0u;
-  switch (L.op) {
+__device__ __forceinline__ bool lit_true(CInstr L, bool nonnull, bool inwin, int64_t x) {
+  const bool neg = (L->flags & kLitNeg) != 0u;
+  switch (L->op) {
     case D_NN_TRUE: return nonnull && !neg;
     case D_NN_FALSE: return nonnull && neg;
     case D_ISNULL: return nonnull ? neg : !neg;
@@ -1771,14 +1816,14 @@ __device__ __forceinline__ bool lit_true(const DevInstr& L, bool nonnull, bool i
   if (!nonnull) return false;   // a value test on NULL is UNKNOWN, negated or not
   bool v = false;
   if (inwin) {
-    const uint64_t d = (uint64_t)x - (uint64_t)L.lo;
-    if (L.op == D_RANGE) {
-      v = d <= L.span;
-    } else if (L.op == D_BITMAP) {
-      v = d < L.span && ((((const uint32_t*)L.aux)[d >> 5] >> (d & 31)) & 1u);
+    const uint64_t d = (uint64_t)x - (uint64_t)L->lo;
+    if (L->op == D_RANGE) {
+      v = d <= L->span;
+    } else if (L->op == D_BITMAP) {
+      v = d < L->span && ((gptr<uint32_t>(L->aux)[d >> 5] >> (d & 31)) & 1u);
     } else {  // D_INLIST: lower bound in the sorted list
-      const int64_t* list = (const int64_t*)L.aux;
-      uint32_t base = 0, len = L.n;
+      const GLOBAL int64_t* list = gptr<int64_t>(L->aux);
+      uint32_t base = 0, len = L->n;
       while (len > 1) {
         const uint32_t half = len >> 1;
         base = list[base + half] <= x ? base + half : base;
@@ -1790,63 +1835,57 @@ __device__ __forceinline__ bool lit_true(const DevInstr& L, bool nonnull, bool i
   return v != neg;
 }
 
-// The bits the atoms [ab, ab + an) set for one row (dwords w0 .. w3).
-__device__ __forceinline__ void atoms_eval(const LutAtom* atoms, const DevInstr* lits, uint32_t ab,
-                                           uint32_t an, bool nonnull, bool inwin, int64_t x,
-                                           uint32_t& w0, uint32_t& w1, uint32_t& w2, uint32_t& w3) {
-  for (uint32_t k = 0; k < an; ++k) {
-    const LutAtom A = atoms[ab + k];
-    bool any = false;
-    for (uint32_t l = 0; l < A.lit_count && !any; ++l) any = lit_true(lits[A.lit_begin + l], nonnull, inwin, x);
-    if (any != (A.kind == LA_SAT)) continue;
-    const uint32_t m = 1u << (A.bit & 31);
-    switch (A.bit >> 5) {
-      case 0: w0 |= m; break;
-      case 1: w1 |= m; break;
-      case 2: w2 |= m; break;
-      default: w3 |= m; break;
-    }
+// Lookup tables of a launch, in device memory.  A workgroup takes 64 entries
+// of one column, an entry per lane, and its waves share the column's atoms,
+// whose literals are then scalar loads; their bits meet in LDS.  (A thread per
+// entry, one atom after another by vector loads, was a chain of some sixty
+// memory latencies: 31 us before every batch.)
+constexpr uint32_t kLutWaves = 8;
+__global__ void __launch_bounds__(kLutWaves * 64) k_luts(LutArgs a) {
+  __shared__ uint32_t out[4 * 64];
+  const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
+  const CONSTANT LutBuild* builds = (const CONSTANT LutBuild*)a.builds;
+  uint32_t lo = 0, hi = a.nbuilds;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (builds[mid].unit_begin <= blockIdx.x) lo = mid; else hi = mid;
   }
-}
-
-// Lookup tables of a launch, in device memory (one thread per entry).
-__global__ void __launch_bounds__(256) k_luts(LutArgs a) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < a.nentries; e += stride) {
-    uint32_t lo = 0, hi = a.nbuilds;
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (a.builds[mid].entry_begin <= e) lo = mid; else hi = mid;
-    }
-    const LutBuild& B = a.builds[lo];
-    const LutCol& C = a.cols[B.col];
-    const uint32_t i = (uint32_t)(e - B.entry_begin);
-    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-    bool zero = false, nonnull = true, inwin = true;
-    int64_t x = 0;
-    if (C.kind == LK_DIRECT) {
-      // 0: below the window, 1..n: values lo.., n+1: above, n+2: NULL, n+3: zero
-      if (i == 0 || i == C.n + 1) inwin = false;
-      else if (i == C.n + 2) nonnull = false;
-      else if (i == C.n + 3) zero = true;
-      else x = C.lo + (int64_t)(i - 1);
-    } else if (C.kind == LK_RANK) {
-      // 0..n: by rank, n+1: NULL, n+2: zero
-      if (i == C.n + 1) nonnull = false;
-      else if (i == C.n + 2) zero = true;
-      else x = a.reps[B.reps + i];
-    } else {  // LK_VALID: 0 non-NULL, 1 NULL
-      nonnull = i == 0;
-      inwin = false;
-    }
-    if (!zero) atoms_eval(a.atoms, a.lits, C.atom_begin, C.atom_count, nonnull, inwin, x, w0, w1, w2, w3);
-    uint32_t* dst = B.dst + (uint64_t)i * B.dwords;
-    dst[0] = w0;
-    if (B.dwords > 1) dst[1] = w1;
-    if (B.dwords > 2) {
-      dst[2] = w2;
-      dst[3] = w3;
-    }
+  const CONSTANT LutBuild* B = builds + uni(lo);
+  const CONSTANT LutCol* C = (const CONSTANT LutCol*)a.cols + B->col;
+  const uint32_t i = (blockIdx.x - (uint32_t)B->unit_begin) * kLutUnit + lane;
+  const uint32_t kind = C->kind, n = C->n, ents = B->nentries;
+  bool zero = i >= ents, nonnull = true, inwin = true;
+  int64_t x = 0;
+  if (kind == LK_DIRECT) {
+    // 0: below the window, 1..n: values lo.., n+1: above, n+2: NULL, n+3: zero
+    if (i == 0 || i == n + 1) inwin = false;
+    else if (i == n + 2) nonnull = false;
+    else if (i == n + 3) zero = true;
+    else x = C->lo + (int64_t)(i - 1);
+  } else if (kind == LK_RANK) {
+    // 0..n: by rank, n+1: NULL, n+2: zero
+    if (i == n + 1) nonnull = false;
+    else if (i == n + 2) zero = true;
+    else if (!zero) x = a.reps[B->reps + i];
+  } else {  // LK_VALID: 0 non-NULL, 1 NULL
+    nonnull = i == 0;
+    inwin = false;
+  }
+  for (uint32_t k = threadIdx.x; k < 4 * 64; k += blockDim.x) out[k] = 0;
+  __syncthreads();
+  const CONSTANT LutAtom* atoms = (const CONSTANT LutAtom*)a.atoms + C->atom_begin;
+  const uint32_t an = C->atom_count;
+  for (uint32_t k = wave; k < an; k += kLutWaves) {
+    const uint32_t lb = atoms[k].lit_begin, ln = atoms[k].lit_count, bit = atoms[k].bit;
+    bool any = false;
+    for (uint32_t l = 0; l < ln; ++l) any |= lit_true((CInstr)a.lits + lb + l, nonnull, inwin && !zero, x);
+    if (!zero && any == (atoms[k].kind == LA_SAT)) atomicOr(&out[(bit >> 5) * 64 + lane], 1u << (bit & 31));
+  }
+  __syncthreads();
+  const uint32_t D = B->dwords;
+  for (uint32_t k = threadIdx.x; k < 64 * D; k += blockDim.x) {
+    const uint32_t e = (blockIdx.x - (uint32_t)B->unit_begin) * kLutUnit + k / D;
+    if (e < ents) B->dst[(uint64_t)e * D + k % D] = out[(k % D) * 64 + k / D];
   }
 }
 
@@ -2614,12 +2653,11 @@ int sel_launch_gather(const GatherArgs& a, uint32_t grid, uint32_t block, void* 
   return (int)hipGetLastError();
 }
 
-int sel_launch_tables(const TableBuild* d_builds, uint32_t nbuilds, uint64_t nentries, void* stream) {
-  if (nbuilds == 0 || nentries == 0) return 0;
-  uint64_t blocks = (nentries + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_tables, dim3((uint32_t)blocks), dim3(256), 0, (hipStream_t)stream, d_builds,
-                     nbuilds, nentries);
+int sel_launch_tables(const TableBuild* d_builds, uint32_t nbuilds, uint64_t nunits, void* stream) {
+  if (nbuilds == 0 || nunits == 0) return 0;
+  const uint64_t blocks = (nunits + 3) / 4;
+  if (blocks >= 1ull << 31) return (int)hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_tables, dim3((uint32_t)blocks), dim3(256), 0, (hipStream_t)stream, d_builds, nbuilds, nunits);
   return (int)hipGetLastError();
 }
 
@@ -2649,10 +2687,9 @@ int sel_batch_occupancy(uint32_t block, uint32_t lds_bytes, int* blocks_per_cu) 
 }
 
 int sel_launch_luts(const LutArgs& a, void* stream) {
-  if (a.nbuilds == 0 || a.nentries == 0) return 0;
-  uint64_t blocks = (a.nentries + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_luts, dim3((uint32_t)blocks), dim3(256), 0, (hipStream_t)stream, a);
+  if (a.nbuilds == 0 || a.nunits == 0) return 0;
+  if (a.nunits >= 1ull << 31) return (int)hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_luts, dim3((uint32_t)a.nunits), dim3(kLutWaves * 64), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
 

@@ -258,7 +258,7 @@ void LutPlan::clear() {
   acc_index.clear();
   builds.clear();
   gtab_words = 0;
-  nentries = 0;
+  nunits = 0;
   total_tiles = 0;
   max_lds_words = 0;
 }
@@ -547,14 +547,14 @@ std::vector<uint32_t> LutPlan::add(const sel_table* t, uint64_t row_begin, uint6
       }
       LutBuild b{};
       b.dst = (uint32_t*)(uintptr_t)gtab_words;   // offset until written
-      b.entry_begin = nentries;
+      b.unit_begin = nunits;
       b.col = (uint32_t)cols.size();
       b.nentries = (uint32_t)c->entries;
       b.dwords = D;
       b.reps = (uint32_t)reps.size();
       builds.push_back(b);
       lc.gtab = (const uint32_t*)(uintptr_t)gtab_words;
-      nentries += c->entries;
+      nunits += (c->entries + kLutUnit - 1) / kLutUnit;
       gtab_words += ((c->entries * D * 4 + 255) & ~255ull) / 4;
       bounds.insert(bounds.end(), c->bounds.begin(), c->bounds.end());
       // whole blocks of eight for the kernel's block loads
@@ -656,7 +656,7 @@ void LutPlan::write(uint8_t* host, char* dev, uint32_t* gtab_dev, LutArgs& a) co
   a.nprogs = (uint32_t)acc_index.size();
   a.nbuilds = (uint32_t)builds.size();
   a.acc_words = acc_words();
-  a.nentries = nentries;
+  a.nunits = nunits;
   a.total_tiles = total_tiles;
 }
 

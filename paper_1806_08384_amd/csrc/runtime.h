@@ -244,7 +244,7 @@ struct LutPlan {
   std::vector<uint32_t> acc_index;     // per program: its accumulator line
   std::vector<sel::LutBuild> builds;   // dst holds a word offset until written
   uint64_t gtab_words = 0;             // tables in device memory, in words
-  uint64_t nentries = 0;
+  uint64_t nunits = 0;                 // of table entries, for k_luts
   uint64_t total_tiles = 0;
   uint32_t max_lds_words = 0;
   void clear();
@@ -284,7 +284,7 @@ struct BatchPlan {
   std::vector<uint64_t> col_gtab;        // per column: word offset of its device table, or ~0
   std::vector<sel::TableBuild> builds;   // dst / leaves hold offsets until written
   uint64_t gtab_words = 0;               // device-memory tables of k_batch, in words
-  uint64_t table_entries = 0;            // entries k_tables writes
+  uint64_t table_units = 0;              // units of entries k_tables builds
   uint64_t total_tiles = 0;
   uint32_t max_slots = 0;
   void clear();

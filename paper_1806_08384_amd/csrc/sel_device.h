@@ -381,12 +381,14 @@ struct BatchCol {              // 64 bytes: a column one entry reads
 // launch: entry i (i < n) holds bit k = leaf k's test of value lo + i, for
 // the m leaves at `leaves`; entry n is zero.  Entries are
 // tab_entry_bytes(m) wide.
+// A wave builds kTableUnit entries of one table.
+constexpr uint32_t kTableUnit = 2048;
 struct TableBuild {            // 48 bytes
   uint32_t* dst;
   const DevInstr* leaves;
   int64_t lo;
   uint64_t n;
-  uint64_t entry_begin;        // first entry of this table in the launch's flat range
+  uint64_t unit_begin;         // first of its units in the launch's flat range
   uint32_t m;
   uint32_t pad;
 };
@@ -499,10 +501,12 @@ struct LutPass {             // 112 bytes: one pass over a table or a chunk of i
 };
 static_assert(sizeof(LutPass) == 112, "LutPass layout");
 
-// Table build: entry e of column `col` (e < nentries) at dst + e * dwords.
+// Table build: entry e of column `col` (e < nentries) at dst + e * dwords; a
+// workgroup builds kLutUnit entries of one column.
+constexpr uint32_t kLutUnit = 64;
 struct LutBuild {            // 40 bytes
   uint32_t* dst;
-  uint64_t entry_begin;      // in the launch's flat entry range
+  uint64_t unit_begin;       // in the launch's flat range of units
   uint32_t col;              // into the LutCol array
   uint32_t nentries;
   uint32_t dwords;
@@ -531,7 +535,7 @@ struct LutArgs {
   uint32_t nprogs;
   uint32_t nbuilds;
   uint32_t acc_words;        // LDS counters: min(nprogs, kBatchMaxProgs)
-  uint64_t nentries;         // table entries k_luts writes
+  uint64_t nunits;           // units of table entries k_luts builds
   uint64_t total_tiles;      // a multiple of kLutTileAlign
   unsigned long long* acc;   // accumulator lines (kBatchAccStride u64 each)
   const uint32_t* done;      // as BatchArgs
@@ -554,7 +558,7 @@ int sel_launch_scan_tiles(const sel::MaskOrder& order, const uint32_t* tile_meta
 int sel_launch_compact(const sel::CompactArgs& a, void* stream);
 int sel_launch_gather(const sel::GatherArgs& a, uint32_t grid, uint32_t block, void* stream);
 int sel_launch_fill(uint32_t* p, uint64_t nwords, uint32_t value, void* stream);
-int sel_launch_tables(const sel::TableBuild* d_builds, uint32_t nbuilds, uint64_t nentries,
+int sel_launch_tables(const sel::TableBuild* d_builds, uint32_t nbuilds, uint64_t nunits,
                       void* stream);
 int sel_scan_occupancy(int mode, uint32_t block, int* blocks_per_cu);
 int sel_launch_batch(const sel::BatchArgs& a, uint32_t grid, uint32_t block, uint32_t lds_bytes,

@@ -176,3 +176,35 @@ def test_small_scan_sizes(sel, ctx, n):
                 if st == sel.SEL_OK:
                     np.testing.assert_array_equal(as_u32(bm), words)
     ctx.set_launch()
+
+
+@pytest.mark.parametrize("lo", [-37, 0, 5, 1000])
+@pytest.mark.parametrize("width", [1, 31, 32, 33, 2046, 2047, 2048, 2049, 70_001])
+@pytest.mark.parametrize("nprog", [3, 9, 20])
+def test_batch_table_builds(sel, ctx, width, lo, nprog):
+    """Lookup tables of both batch kernels at the edges of the builds' units
+    (32 entries a thread, 64 or 2048 a unit) and entry widths: ranges, bitmaps
+    of lists from any first value, NULLs, programs in conjunctive form and
+    (IS UNKNOWN) not."""
+    rng = np.random.default_rng(width + 3 * nprog + abs(lo))
+    n = 6000
+    data = rng.integers(lo - 3, lo + width + 3, n).astype(np.int32)
+    t = datagen.Table("tab", n)
+    t.columns.append(datagen.Column("x", "i32", data))
+    valid = datagen.words_from_codes([i for i in range(n) if i % 7], n)
+    t.columns.append(datagen.Column("y", "i32", data[::-1].copy(), valid))
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+
+    def leaf(col):
+        a, b = sorted(int(v) for v in rng.integers(lo, lo + width, 2))
+        if rng.random() < 0.4:
+            return ("between", col, a, b)
+        vals = set(int(v) for v in rng.integers(lo, lo + width, max(2, min(300, width // 3))))
+        return ("in", col, tuple(vals | {a}))
+
+    plain = [("and", leaf(0), ("or", leaf(1), leaf(0))) for _ in range(nprog)]
+    other = [("and", leaf(0), leaf(0), leaf(0), ("not", ("isunknown", leaf(1)))) for _ in range(nprog)]
+    for trees in (plain, other, plain + other):
+        got = ctx.count_batch([(dt, ctx.program(dt, tree)) for tree in trees])
+        assert got == [orc.count(tree) for tree in trees]
