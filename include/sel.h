@@ -548,9 +548,9 @@ typedef struct sel_launch {
   uint32_t stage_words;    /* scans: most LDS words of the program's bitmaps
                               and IN lists copied to LDS first (0 = all that
                               fit 32 KB; 1 = none)                            */
-  uint32_t rows_per_lane;  /* lookup-table batch kernel: rows per lane per
-                              segment, 4 or 8 (0 = 8; four-dword passes
-                              always take 4)                                  */
+  uint32_t rows_per_lane;  /* lookup-table batch kernel: 8 = sixteen rows per
+                              lane at a time, 4 = eight (0 = 8; four-dword
+                              passes always take eight)                       */
 } sel_launch;
 
 /* Override (or with NULL, restore) the launch configuration used by the

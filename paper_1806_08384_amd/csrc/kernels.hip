@@ -98,6 +98,8 @@ template <int NS> struct Raw<T_I32, NS> { v4i w[NS]; };
 constexpr int group64(int ns) { return ns < 4 ? ns : 4; }
 template <int NS> struct Raw<T_I64, NS> { v4i w[2 * group64(NS)]; };
 
+constexpr int kNt = 2;   // buffer-load cache policy: nontemporal (streamed once)
+
 // A streamed load: nontemporal (NT, the default) or through the caches as
 // usual; which one is faster is left to the tuner.
 template <bool NT, class T>
@@ -1889,56 +1891,76 @@ __global__ void __launch_bounds__(kLutWaves * 64) k_luts(LutArgs a) {
   }
 }
 
-// Values of one lane's rows of one column in a segment: 4 S rows (S steps
-// of the tile's row mapping) held from vector w[0]: step s of a narrow
-// column in w[s] (its leading components); of an int64 column, rows 0 and 1
-// of step s in w[s] and rows 2 and 3 in w[S + s] (the next slot).
-template <int TY, int S>
-__device__ __forceinline__ auto lget(const v4i* w, int s, int i) {
+// A pass column in scalar registers, from one 64-byte scalar load.
+struct ColD {
+  const void* data;
+  const uint32_t* valid;
+  uint32_t type, kind;
+  int64_t lo;
+  uint32_t n, lds_word;
+  const uint32_t* gtab;
+  uint32_t first, guard;
+};
+__device__ __forceinline__ ColD decode_col(v16u w) {
+  return ColD{(const void*)pair64(w, 0), (const uint32_t*)pair64(w, 2), w[4], w[5], (int64_t)pair64(w, 6),
+              w[8], w[9], (const uint32_t*)pair64(w, 10), w[12], w[15]};
+}
+
+// One column's loads for S steps of the tile: per step one 16-byte load at the
+// lane's first row, whatever the column's width, so that the registers do not
+// depend on a branch (which would make the compiler wait for the loads in
+// flight).  A narrow column reads its neighbours' rows too (the same cache
+// lines); an int64 column's rows 2 and 3 of each step are four more loads.
+// Bounded to the table's rows: past them the loads return zero without
+// touching memory.
+template <int S, bool WIDE>
+struct Stage {
+  v4i w[WIDE ? 2 * S : S];
+  uint32_t vr[WIDE ? S : 1];   // validity words of the lane's rows
+};
+
+template <int S, bool WIDE>
+__device__ __forceinline__ void lut_issue(Stage<S, WIDE>& g, const ColD& c, uint64_t tb, uint64_t nrows, uint32_t lane, int j0,
+                                          bool on = true) {
+  const uint32_t width = c.type == T_I8 ? 1u : c.type == T_I16 ? 2u : c.type == T_I32 ? 4u : 8u;
+  const __amdgpu_buffer_rsrc_t rs = col_rsrc(c.data, width, tb, nrows, on ? (uint32_t)kTileRows : 0u);
+  const uint32_t at = width * (4u * lane + 256u * (uint32_t)j0), step = width * 256u;
+#pragma unroll
+  for (int s = 0; s < S; ++s) g.w[s] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)(at + step * (uint32_t)s), 0, kNt);
+  if (WIDE && c.type == T_I64) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      g.w[(WIDE ? S : 0) + s] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)(at + 16u + step * (uint32_t)s), 0, kNt);
+  }
+  if (WIDE && c.valid) {
+    const uint32_t rows = nrows - tb < (uint64_t)kTileRows ? (uint32_t)(nrows - tb) : (uint32_t)kTileRows;
+    const __amdgpu_buffer_rsrc_t vs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(c.valid + tb / 32), (short)0, (int)uni((rows + 31u) / 32u * 4u), 0x00020000);
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      g.vr[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(vs, (int)(4u * ((lane >> 3) + 8u * (uint32_t)(j0 + s))), 0, 0);
+  }
+}
+
+// value of row r (step r / 4) of a stage
+template <int TY, int S, bool WIDE>
+__device__ __forceinline__ auto sget(const Stage<S, WIDE>& g, int r) {
+  const int s = r >> 2, i = r & 3;
   if constexpr (TY == T_I8) {
-    return (int32_t)(int8_t)((uint32_t)w[s][0] >> (8 * i));
+    return (int32_t)(int8_t)((uint32_t)g.w[s][0] >> (8 * i));
   } else if constexpr (TY == T_I16) {
-    return (int32_t)(int16_t)((uint32_t)w[s][i >> 1] >> (16 * (i & 1)));
+    return (int32_t)(int16_t)((uint32_t)g.w[s][i >> 1] >> (16 * (i & 1)));
   } else if constexpr (TY == T_I32) {
-    return (int32_t)w[s][i];
+    return (int32_t)g.w[s][i];
   } else {
-    const v4i& q = w[S * (i >> 1) + s];   // rows 2, 3 in the next slot
+    const v4i& q = g.w[S * (i >> 1) + s];
     const int k = 2 * (i & 1);
     return (int64_t)(((uint64_t)(uint32_t)q[k + 1] << 32) | (uint32_t)q[k]);
   }
 }
 
-// Buffer resource over rows [tb, min(tb + 2048, nrows)) of a column of
-// `width`-byte values: 32-bit offsets from the tile's start, and a read past
-// the table's last row returns zero without touching memory.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* data, uint64_t tb, uint64_t nrows,
-                                                            uint32_t width) {
-  const uint64_t rows = nrows - tb < (uint64_t)kTileRows ? nrows - tb : (uint64_t)kTileRows;
-  return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)data + tb * width), (short)0,
-                                           (int)(rows * width), 0x00020000);
-}
-
-constexpr int kNt = 2;   // buffer-load cache policy: nontemporal (streamed once)
-
-// One register slot's loads for steps j0 .. j0 + S - 1: one 16-byte load
-// per step at the lane's first row, whatever the column's width, so that
-// every slot has the same shape and no slot's registers depend on a branch
-// (a branch would make the compiler wait for loads in flight).  A column
-// narrower than 4 bytes reads its neighbours' rows too (the same cache
-// lines); an int64 column takes two slots, the second one 16 bytes further.
-// The resource bounds the reads: past the table, or for an unused slot (no
-// bytes), they return zero without touching memory.
-template <int S>
-__device__ __forceinline__ void slot_issue(v4i* w, __amdgpu_buffer_rsrc_t rs, uint32_t width, int j0,
-                                           uint32_t lane) {
-#pragma unroll
-  for (int s = 0; s < S; ++s)
-    w[s] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)(width * (4u * lane + 256u * (uint32_t)(j0 + s))), 0,
-                                                      kNt);
-}
-
-// Validity of the segment's rows: bit 4 s + i = row (step j0 + s, i) is not
-// NULL (0 past nrows).
+// Validity of R rows of the lane from step j0: bit b = row b is not NULL (0
+// past the table).
 template <int R>
 __device__ __forceinline__ uint32_t lseg_valid(const uint32_t* valid, uint64_t tb, int j0, uint32_t lane,
                                                uint64_t nrows, bool full) {
@@ -1950,23 +1972,6 @@ __device__ __forceinline__ uint32_t lseg_valid(const uint32_t* valid, uint64_t t
   for (int s = 0; s < S; ++s)
     if (full || tb + 256u * (uint32_t)(j0 + s) + 4u * lane < nrows) V |= ((vw[8 * s] >> sh) & 0xFu) << (4 * s);
   return V;
-}
-
-
-
-template <int D>
-__device__ __forceinline__ void ent_or(const uint32_t* tab, uint32_t idx, uint32_t (&acc)[D]) {
-  if constexpr (D == 1) {
-    acc[0] |= tab[idx];
-  } else if constexpr (D == 2) {
-    const v2u e = ((const v2u*)tab)[idx];
-    acc[0] |= e[0];
-    acc[1] |= e[1];
-  } else {
-    const v4u e = ((const v4u*)tab)[idx];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) acc[d] |= e[d];
-  }
 }
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
@@ -2011,70 +2016,21 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t table_rsrc(const uint32_t* tab
   return __builtin_amdgcn_make_buffer_rsrc((void*)tab, (short)0, (int)(entries * dwords * 4u), 0x00020000);
 }
 
-// A register slot's column as its lookups need it, decoded once per tile.
-struct SlotD {
-  uint32_t info;          // kSd* flags, type in bits 0..3, kind in bits 4..5
-  uint32_t n;             // DIRECT: window size; RANK: bounds
-  int64_t lo;             // DIRECT: value of entry 1
-  uint32_t tab;           // table: LDS word offset, or kNoLds
-  uint32_t first;         // RANK: first bound
-  const uint32_t* gtab;   // table in device memory
-  const char* data;       // the slot's bytes of the tile's first row
-  const uint32_t* valid;  // validity word of the tile's first row
-  uint32_t bytes, vbytes; // readable bytes from there (0: none)
-};
-constexpr uint32_t kSdNullable = 1u << 8, kSdGuard = 1u << 10, kSdData = 1u << 11;
-
-__device__ __forceinline__ SlotD slot_decode(const CONSTANT LutPass* P, const CONSTANT LutCol* cb, int k,
-                                             uint64_t tb, uint64_t rows) {
-  SlotD d{};
-  const uint32_t code = (P->slot_col[k / 4] >> (8 * (k % 4))) & 0xFFu;
-  if (code == kNoSlotCol) {
-    d.info = T_I32;
-    d.data = (const char*)P;
-    d.valid = (const uint32_t*)P;
-  } else {
-    const CONSTANT LutCol* C = cb + (code & kSlotColMask);
-    const uint32_t ty = C->type;
-    const uint32_t width = ty == T_I8 ? 1u : ty == T_I16 ? 2u : ty == T_I32 ? 4u : 8u;
-    const uint32_t half = code & kSlotHigh ? 16u : 0u;
-    d.info = ty | (C->kind << 4) | (C->valid ? kSdNullable : 0u) | (C->guard ? kSdGuard : 0u) |
-             (half ? 0u : kSdData);
-    d.n = C->n;
-    d.lo = C->lo;
-    d.tab = C->lds_word;
-    d.first = C->first;
-    d.gtab = C->gtab;
-    d.data = (const char*)C->data + tb * width + half;
-    // whole dwords: a raw buffer load zeroes a dword that crosses the
-    // bound, and the bytes up to the next 4-byte boundary share the last
-    // element's 16-byte-aligned block (the same memory page)
-    const uint32_t span = ((uint32_t)(rows * width) + 3u) & ~3u;
-    // made scalar: the compiler turns this into a saturating subtract that
-    // only the vector unit has, and a buffer resource built from a vector
-    // register is wrapped in a readfirstlane loop at every load
-    d.bytes = uni(span > half ? span - half : 0u);
-    const bool hv = !half && C->valid;
-    d.valid = hv ? C->valid + tb / 32 : (const uint32_t*)P;
-    d.vbytes = hv ? (uint32_t)(((rows + 31) / 32) * 4) : 0u;
-  }
-  return d;
-}
-
-// Table indices of an item's rows to entries, ORed into the accumulators of
-// segment rows OFF .. OFF + NR - 1: from LDS, or from device memory where a
-// guarded table is read only on rows some program of the pass can still
-// count (the others read the zero entry).
-template <int D, int R, int NR, int OFF>
-__device__ __forceinline__ void lookup_or(const SlotD& sd, const uint32_t* lds, uint32_t (&idx)[NR],
-                                          uint32_t zero, const CONSTANT LutPass* P, uint32_t (&acc)[R][D]) {
-  if (sd.tab != kNoLds) {
-    const uint32_t* tab = lds + sd.tab;
+// Table indices of eight rows to entries, ORed into the accumulators of rows
+// off .. off + 7: from LDS, or from device memory where a guarded table is
+// read only on rows some program of the pass can still count (the others read
+// the zero entry).
+template <int D, int R>
+__device__ __forceinline__ void lookup_or(const ColD& c, const uint32_t* lds, uint32_t (&idx)[8], uint32_t zero,
+                                          const CONSTANT LutPass* P, uint32_t (&acc)[R][D], int off) {
+  if (c.lds_word != kNoLds) {
+    const LDS_PTR(char) l3 = (LDS_PTR(char))lds;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) ent_or<D>(tab, idx[r], acc[OFF + r]);
+    for (int r = 0; r < 8; ++r)
+      ent_or_lds<D>((LDS_PTR(const char))(l3 + (c.lds_word * 4u + idx[r] * (4u * D))), acc[off + r]);
   } else {
-    const __amdgpu_buffer_rsrc_t tab = table_rsrc(sd.gtab, zero + 1, D);
-    if (sd.info & kSdGuard) {
+    const __amdgpu_buffer_rsrc_t tab = table_rsrc(c.gtab, zero + 1, D);
+    if (c.guard) {
       // a row some program can still count: a failure bit (word 0 of a
       // dword) still clear
       uint32_t am[D];
@@ -2084,91 +2040,92 @@ __device__ __forceinline__ void lookup_or(const SlotD& sd, const uint32_t* lds, 
         am[d] = g >= 32 ? ~0u : (1u << g) - 1u;
       }
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
+      for (int r = 0; r < 8; ++r) {
         uint32_t alive = 0;
 #pragma unroll
-        for (int d = 0; d < D; ++d) alive |= ~acc[OFF + r][d] & am[d];
+        for (int d = 0; d < D; ++d) alive |= ~acc[off + r][d] & am[d];
         idx[r] = alive ? idx[r] : zero;
       }
     }
 #pragma unroll
-    for (int r = 0; r < NR; ++r) gent_or<D>(tab, idx[r], acc[OFF + r]);
+    for (int r = 0; r < 8; ++r) gent_or<D>(tab, idx[r], acc[off + r]);
   }
 }
 
-// One column on one segment: every row's entry ORed into its accumulator.
-// V holds the validity of the segment's R rows.
-template <int D, int R, int TY, int NR, int OFF>
-__device__ __forceinline__ void lut_col(const v4i* seg, const SlotD& sd, const LutArgs& a, uint32_t V,
-                                        const uint32_t* lds, const CONSTANT LutPass* P, uint32_t (&acc)[R][D]) {
-  constexpr int S = NR / 4;
-  const uint32_t kind = (sd.info >> 4) & 3u, n = sd.n;
-  const bool nullable = (sd.info & kSdNullable) != 0;
-  uint32_t idx[NR];
-  if (kind == LK_DIRECT) {
-    const int64_t lo = sd.lo;
+// One column on the segment's rows of the lane: every row's
+// entry ORed into its accumulator.
+// Eight rows at a time (a scheduling barrier between them): more entries in
+// flight would spill the accumulators.
+template <int D, int R, int TY, bool WIDE>
+__device__ __forceinline__ void lut_col(const Stage<R / 4, WIDE>& raw, const ColD& c, const LutArgs& a, uint32_t lane, const uint32_t* lds,
+                                        const CONSTANT LutPass* P, uint32_t (&acc)[R][D]) {
+  const uint32_t n = c.n;
+  const int64_t lo = c.lo;
+  const bool nullable = WIDE && c.valid != nullptr;
+  uint32_t V = 0;   // the rows' validity
+  if (nullable) {
+#pragma unroll
+    for (int s = 0; s < R / 4; ++s) V |= ((raw.vr[WIDE ? s : 0] >> (4u * (lane & 7u))) & 0xFu) << (4 * s);
+  }
+  if (c.kind == LK_DIRECT) {
+    constexpr int64_t tmin = TY == T_I8 ? INT8_MIN : TY == T_I16 ? INT16_MIN : INT32_MIN;
+    constexpr int64_t tmax = TY == T_I8 ? INT8_MAX : TY == T_I16 ? INT16_MAX : INT32_MAX;
+    const int32_t cl = (int32_t)(lo - 1 < tmin ? tmin : lo - 1);
+    const int32_t ch = (int32_t)(lo + (int64_t)n > tmax ? tmax : lo + (int64_t)n);
     if constexpr (TY != T_I64) {
-      if (sd.tab != kNoLds && !nullable) {
+      if (c.lds_word != kNoLds && !nullable) {
         // clamped value straight to the entry's LDS byte address: the
         // table's address less (lo - 1) entries, plus the value's entries
-        constexpr int64_t tmin = TY == T_I8 ? INT8_MIN : TY == T_I16 ? INT16_MIN : INT32_MIN;
-        constexpr int64_t tmax = TY == T_I8 ? INT8_MAX : TY == T_I16 ? INT16_MAX : INT32_MAX;
-        const int32_t cl = (int32_t)(lo - 1 < tmin ? tmin : lo - 1);
-        const int32_t ch = (int32_t)(lo + (int64_t)n > tmax ? tmax : lo + (int64_t)n);
-        // byte offsets within LDS, through an LDS-space pointer (32-bit)
-        const LDS_PTR(const char) l3 = (LDS_PTR(const char))lds;
-        const uint32_t abase = sd.tab * 4u - (uint32_t)(lo - 1) * (4u * D);
+        const LDS_PTR(char) l3 = (LDS_PTR(char))lds;
+        const uint32_t abase = c.lds_word * 4u - (uint32_t)(lo - 1) * (4u * D);
         int32_t chv = ch;   // in a vector register once: one scalar operand per VALU op
         asm volatile("v_mov_b32 %0, %1" : "=v"(chv) : "s"(ch));
 #pragma unroll
-        for (int s = 0; s < S; ++s)
+        for (int g = 0; g < R; g += 8) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int32_t x = lget<TY, S>(seg, s, i);
+          for (int r = g; r < g + 8; ++r) {
+            const int32_t x = sget<TY>(raw, r);
             int32_t m;
             asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(x), "s"(cl), "v"(chv));
-            ent_or_lds<D>(l3 + (abase + (uint32_t)m * (4u * D)), acc[OFF + 4 * s + i]);
+            ent_or_lds<D>((LDS_PTR(const char))(l3 + (abase + (uint32_t)m * (4u * D))), acc[r]);
           }
+          __builtin_amdgcn_sched_barrier(0);
+        }
         return;
       }
-      // clamp to [lo - 1, lo + n] (inside the type), then offset: entry 0
-      // below the window, n + 1 above it
-      constexpr int64_t tmin = TY == T_I8 ? INT8_MIN : TY == T_I16 ? INT16_MIN : INT32_MIN;
-      constexpr int64_t tmax = TY == T_I8 ? INT8_MAX : TY == T_I16 ? INT16_MAX : INT32_MAX;
-      const int32_t cl = (int32_t)(lo - 1 < tmin ? tmin : lo - 1);
-      const int32_t ch = (int32_t)(lo + (int64_t)n > tmax ? tmax : lo + (int64_t)n);
-      const uint32_t base = (uint32_t)(lo - 1);
-#pragma unroll
-      for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int32_t x = lget<TY, S>(seg, s, i);
-          idx[4 * s + i] = (uint32_t)min(max(x, cl), ch) - base;
-        }
-    } else {
-      const int64_t cl = lo == INT64_MIN ? lo : lo - 1;
-      const int64_t ch = lo + (int64_t)n;   // the planned window ends below INT64_MAX
-      const uint64_t base = (uint64_t)lo - 1u;
-#pragma unroll
-      for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t x = lget<TY, S>(seg, s, i);
-          const int64_t m = x < cl ? cl : x > ch ? ch : x;
-          idx[4 * s + i] = (uint32_t)((uint64_t)m - base);
-        }
     }
-    if (nullable) {
 #pragma unroll
-      for (int r = 0; r < NR; ++r) idx[r] = (V >> (OFF + r)) & 1u ? idx[r] : n + 2;
+    for (int g = 0; g < R; g += 8) {
+      uint32_t idx[8];
+      if constexpr (TY != T_I64) {
+        // clamp to [lo - 1, lo + n] (inside the type), then offset: entry 0
+        // below the window, n + 1 above it
+        const uint32_t base = (uint32_t)(lo - 1);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) idx[r] = (uint32_t)min(max((int32_t)sget<TY>(raw, g + r), cl), ch) - base;
+      } else {
+        const int64_t cl8 = lo == INT64_MIN ? lo : lo - 1;
+        const int64_t ch8 = lo + (int64_t)n;   // the planned window ends below INT64_MAX
+        const uint64_t base = (uint64_t)lo - 1u;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const int64_t x = sget<TY>(raw, g + r);
+          const int64_t m = x < cl8 ? cl8 : x > ch8 ? ch8 : x;
+          idx[r] = (uint32_t)((uint64_t)m - base);
+        }
+      }
+      if (nullable) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) idx[r] = (V >> (g + r)) & 1u ? idx[r] : n + 2;
+      }
+      lookup_or<D, R>(c, lds, idx, n + 3, P, acc, g);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    lookup_or<D, R, NR, OFF>(sd, lds, idx, n + 3, P, acc);
   } else {  // LK_RANK: the number of bounds at or below the value
     // bounds in blocks of eight (the list is padded to whole blocks), one
     // scalar load per block
-    const CONSTANT int64_t* b = (const CONSTANT int64_t*)a.bounds + sd.first;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) idx[r] = 0;
+    const CONSTANT int64_t* b = (const CONSTANT int64_t*)a.bounds + c.first;
+    uint32_t idx[R / 8][8] = {};
     for (uint32_t k0 = 0; k0 < n; k0 += 8) {
       int64_t bb[8];
 #pragma unroll
@@ -2177,19 +2134,21 @@ __device__ __forceinline__ void lut_col(const v4i* seg, const SlotD& sd, const L
       for (int j = 0; j < 8; ++j) {
         if (k0 + j >= n) break;
 #pragma unroll
-        for (int s = 0; s < S; ++s)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if constexpr (TY != T_I64) idx[4 * s + i] += lget<TY, S>(seg, s, i) >= (int32_t)bb[j] ? 1u : 0u;
-            else idx[4 * s + i] += lget<TY, S>(seg, s, i) >= bb[j] ? 1u : 0u;
-          }
+        for (int r = 0; r < R; ++r) {
+          if constexpr (TY != T_I64) idx[r >> 3][r & 7] += (int32_t)sget<TY>(raw, r) >= (int32_t)bb[j] ? 1u : 0u;
+          else idx[r >> 3][r & 7] += sget<TY>(raw, r) >= bb[j] ? 1u : 0u;
+        }
       }
     }
-    if (nullable) {
 #pragma unroll
-      for (int r = 0; r < NR; ++r) idx[r] = (V >> (OFF + r)) & 1u ? idx[r] : n + 1;
+    for (int g = 0; g < R / 8; ++g) {
+      if (nullable) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) idx[g][r] = (V >> (8 * g + r)) & 1u ? idx[g][r] : n + 1;
+      }
+      lookup_or<D, R>(c, lds, idx[g], n + 2, P, acc, 8 * g);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    lookup_or<D, R, NR, OFF>(sd, lds, idx, n + 2, P, acc);
   }
 }
 
@@ -2204,7 +2163,7 @@ struct Hs {
 
 __device__ __forceinline__ void csa(uint32_t& carry, uint32_t& sum, uint32_t a, uint32_t b, uint32_t c) {
   const uint32_t u = a ^ b;
-  carry = (a & b) | (u & c);
+  carry = (u & c) | (~u & a);   // one bit-field insert
   sum = u ^ c;
 }
 
@@ -2270,9 +2229,10 @@ __device__ __forceinline__ void hs_add(Hs& s, const uint32_t* w) {
   }
 }
 
-// Rows' accumulators to their T words (bit p: program p counts the row),
-// packed 32 / B rows to a word, into the counters.  Within dword d, word 0
-// is inverted and the b_d-bit words are ANDed together by folding.
+// Rows' accumulators to their T words (bit p: program p counts the row), eight
+// rows at a time, packed 32 / B rows to a word, into the counters.  Within
+// dword d, word 0 is inverted and the b_d-bit words are ANDed together by
+// folding.
 template <int D, int R>
 __device__ __forceinline__ void lut_count(uint32_t (&acc)[R][D], const CONSTANT LutPass* P, uint32_t inr,
                                           Hs& hs) {
@@ -2287,27 +2247,21 @@ __device__ __forceinline__ void lut_count(uint32_t (&acc)[R][D], const CONSTANT 
     nm[d] = bw[d] >= 32 ? ~0u : (1u << bw[d]) - 1u;
     gm[d] = g >= 32 ? ~0u : (1u << g) - 1u;
   }
-  uint32_t T[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) T[r] = 0;
+  // each dword folded in place; its width is a uniform branch around all rows
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    // the dword's width, a uniform branch around all rows
     if (bw[d] >= 32) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) T[r] |= ((acc[r][d] ^ nm[d]) & gm[d]) << ps[d];
+      for (int r = 0; r < R; ++r) acc[r][d] = ~acc[r][d];
     } else if (bw[d] == 16) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const uint32_t t = acc[r][d] ^ nm[d];
-        T[r] |= ((t & (t >> 16)) & gm[d]) << ps[d];
-      }
+      for (int r = 0; r < R; ++r) acc[r][d] = (acc[r][d] >> 16) & ~acc[r][d];
     } else if (bw[d] == 8) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         uint32_t t = acc[r][d] ^ nm[d];
         t &= t >> 16;
-        T[r] |= ((t & (t >> 8)) & gm[d]) << ps[d];
+        acc[r][d] = t & (t >> 8);
       }
     } else {
 #pragma unroll
@@ -2315,26 +2269,38 @@ __device__ __forceinline__ void lut_count(uint32_t (&acc)[R][D], const CONSTANT 
         uint32_t t = acc[r][d] ^ nm[d];
         t &= t >> 16;
         t &= t >> 8;
-        T[r] |= ((t & (t >> 4)) & gm[d]) << ps[d];
+        acc[r][d] = t & (t >> 4);
       }
     }
   }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    acc[r][0] = (acc[r][0] & gm[0]) << ps[0];
+#pragma unroll
+    for (int d = 1; d < D; ++d) acc[r][0] |= (acc[r][d] & gm[d]) << ps[d];
+  }
   if (inr != ~0u) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) T[r] = (inr >> r) & 1u ? T[r] : 0u;
+    for (int r = 0; r < R; ++r) acc[r][0] = (inr >> r) & 1u ? acc[r][0] : 0u;
   }
   if (B == 32) {
-    hs_add<R>(hs, T);
+#pragma unroll
+    for (int g = 0; g < R; g += 8) {
+      uint32_t w[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) w[k] = acc[g + k][0];
+      hs_add<8>(hs, w);
+    }
   } else if (B == 16) {
     uint32_t w[R / 2];
 #pragma unroll
-    for (int k = 0; k < R / 2; ++k) w[k] = T[2 * k] | (T[2 * k + 1] << 16);
+    for (int k = 0; k < R / 2; ++k) w[k] = acc[2 * k][0] | (acc[2 * k + 1][0] << 16);
     hs_add<R / 2>(hs, w);
   } else {
     uint32_t w[R / 4];
 #pragma unroll
     for (int k = 0; k < R / 4; ++k)
-      w[k] = T[4 * k] | (T[4 * k + 1] << 8) | (T[4 * k + 2] << 16) | (T[4 * k + 3] << 24);
+      w[k] = acc[4 * k][0] | (acc[4 * k + 1][0] << 8) | (acc[4 * k + 2][0] << 16) | (acc[4 * k + 3][0] << 24);
     hs_add<R / 4>(hs, w);
   }
 }
@@ -2366,118 +2332,81 @@ __device__ __forceinline__ void hs_flush(Hs& s, const CONSTANT LutPass* P, unsig
   s = Hs{};
 }
 
-// Start of a segment: accumulators to the pass's initial value, the rows in
-// range (partial tile), and the columns that only null tests read (no
-// data), which come last in the pass.
-template <int D, int R>
-__device__ __forceinline__ void lut_start(const CONSTANT LutPass* P, const CONSTANT LutCol* cols,
-                                          uint64_t tb, bool full, int seg, uint32_t lane,
-                                          uint32_t (&acc)[R][D], uint32_t& inr) {
-  constexpr int S = R / 4;
-  const uint64_t nrows = P->nrows;
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    const uint32_t v = P->init[d];
-#pragma unroll
-    for (int r = 0; r < R; ++r) acc[r][d] = v;
-  }
-  inr = ~0u;
-  if (!full) {
-    inr = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      inr |= (uint32_t)(tb + 256u * (uint32_t)(seg * S + (r >> 2)) + 4u * lane + (uint32_t)(r & 3) < nrows) << r;
-  }
-  const uint32_t cb = P->col_begin, cn = P->col_count;
-  for (uint32_t c = P->ndata; c < cn; ++c) {
-    const CONSTANT LutCol* C = cols + cb + c;
-    const uint32_t V = lseg_valid<R>(C->valid, tb, seg * S, lane, nrows, full);
-    const CONSTANT uint32_t* e = (const CONSTANT uint32_t*)C->gtab;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const uint32_t e0 = e[d], e1 = e[D + d];
-#pragma unroll
-      for (int r = 0; r < R; ++r) acc[r][d] |= (V >> r) & 1u ? e0 : e1;
-    }
-  }
-}
-
-// Calls f(integral_constant<int, k>) for k = 0 .. N-1, unrolled whatever
-// the size of f's body (slot indexes must stay compile-time constants for
-// the slots to live in registers).
-template <class F, int... K>
-__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, K...>) {
-  (f(std::integral_constant<int, K>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_seq(f, std::make_integer_sequence<int, N>{});
-}
-
-// Every column of a pass on one tile, in segments of R = 4 S rows per lane
-// (S steps): the loads of all the segment's data columns and of their
-// validity words are issued together, unconditionally, into register slots
-// of S vectors (an int64 column takes two slots), so that a wave keeps
-// every column of its segment in flight; other waves hide the latency while
-// it waits.  Rows past the table read zeros or neighbouring values and are
-// not counted.
+// Every column of a pass on one tile, R rows of the lane at a time (half of
+// the tile, or a quarter): the loads of a column and, if it is narrow and has
+// no NULLs, of the one after it, then every row's lookups.  The rows'
+// accumulators stay in registers, and a column's description is read once for
+// all of them.  With every column of eight rows loaded together, the
+// descriptions of eight columns did not fit the scalar registers: a third of
+// the vector instructions moved them to vector lanes and back (124 a row, now
+// 79), and 64 programs over four tables took 1.87 ms, now 1.38.  Vector issue
+// and memory latency share the time: one column at a time took 1.57 ms, three
+// 1.51 (spills), whole tiles (32 rows a lane) 2.1 (spills), the next column
+// loaded or touched ahead 1.7 to 2.4.  The second column's loads are issued
+// whether or not there is one (with no bytes in bounds), so that the compiler
+// knows how many are in flight and waits for the first column's alone.  Rows
+// past the table read zeros and are not counted.
 template <int D, int R>
 __device__ __forceinline__ void lut_tile(const CONSTANT LutPass* P, const CONSTANT LutCol* cols,
                                          const LutArgs& a, uint64_t tb, uint32_t lane,
                                          const uint32_t* lds, Hs& hs) {
-  static_assert(R == 4 || R == 8, "segments of one or two steps");
-  constexpr int S = R / 4, NSEG = kSteps / S;
-  const bool full = tb + kTileRows <= P->nrows;
+  static_assert(R == 8 || R == 16, "a quarter tile or half of one");
+  constexpr int S = R / 4;
   const uint64_t nrows = P->nrows;
-  const uint64_t rows = nrows - tb < (uint64_t)kTileRows ? nrows - tb : (uint64_t)kTileRows;
+  const bool full = tb + kTileRows <= nrows;
   const CONSTANT LutCol* cb = cols + P->col_begin;
+  const uint32_t nd = P->ndata, cn = P->col_count;
   uint32_t acc[R][D];
-  uint32_t inr;
-  v4i buf[S * kLutSlots];
-  uint32_t vr[kLutSlots][S];
-  // decoded once per tile (what does not fit in scalar registers moves to
-  // lanes of vector registers, cheaper than reloading it per segment)
-  SlotD sd[kLutSlots];
-  static_for<kLutSlots>([&](auto kc) {
-    constexpr int k = decltype(kc)::value;
-    sd[k] = slot_decode(P, cb, k, tb, rows);
-  });
-  for (int seg = 0; seg < NSEG; ++seg) {
-    const int j0 = seg * S;
-    static_for<kLutSlots>([&](auto kc) {
-      constexpr int k = decltype(kc)::value;
-      const uint32_t ty = sd[k].info & 15u;
-      const uint32_t width = ty == T_I8 ? 1u : ty == T_I16 ? 2u : ty == T_I32 ? 4u : 8u;
-      slot_issue<S>(buf + S * k,
-                    __builtin_amdgcn_make_buffer_rsrc((void*)sd[k].data, (short)0, (int)sd[k].bytes, 0x00020000),
-                    width, j0, lane);
-      const __amdgpu_buffer_rsrc_t vrs =
-          __builtin_amdgcn_make_buffer_rsrc((void*)sd[k].valid, (short)0, (int)sd[k].vbytes, 0x00020000);
+  auto start = [&](int j0) {
 #pragma unroll
-      for (int st = 0; st < S; ++st)
-        vr[k][st] = __builtin_amdgcn_raw_buffer_load_b32(vrs, (int)(4u * ((lane >> 3) + 8u * (uint32_t)(j0 + st))), 0, 0);
-    });
-    lut_start<D, R>(P, cols, tb, full, seg, lane, acc, inr);
-    static_for<kLutSlots>([&](auto kc) {
-      constexpr int k = decltype(kc)::value;
-      const SlotD& d = sd[k];
-      if (!(d.info & kSdData)) return;
-      uint32_t V = 0xFFu;
-      if (d.info & kSdNullable) {
-        V = 0;
+    for (int d = 0; d < D; ++d) {
+      const uint32_t v = P->init[d];
 #pragma unroll
-        for (int st = 0; st < S; ++st) V |= ((vr[k][st] >> (4 * (lane & 7))) & 0xFu) << (4 * st);
+      for (int r = 0; r < R; ++r) acc[r][d] = v;
+    }
+    // columns that only null tests read (no data) come last in the pass
+    for (uint32_t c = nd; c < cn; ++c) {
+      const CONSTANT LutCol* C = cb + c;
+      const uint32_t V = lseg_valid<R>(C->valid, tb, j0, lane, nrows, full);
+      const CONSTANT uint32_t* e = (const CONSTANT uint32_t*)C->gtab;
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const uint32_t e0 = e[d], e1 = e[D + d];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r][d] |= (V >> r) & 1u ? e0 : e1;
       }
-      switch (d.info & 15u) {
-        case T_I8: lut_col<D, R, T_I8, R, 0>(buf + S * k, d, a, V, lds, P, acc); break;
-        case T_I16: lut_col<D, R, T_I16, R, 0>(buf + S * k, d, a, V, lds, P, acc); break;
-        case T_I32: lut_col<D, R, T_I32, R, 0>(buf + S * k, d, a, V, lds, P, acc); break;
-        default:
-          if constexpr (k + 1 < (int)kLutSlots) lut_col<D, R, T_I64, R, 0>(buf + S * k, d, a, V, lds, P, acc);
-          break;
-      }
-    });
-    lut_count<D, R>(acc, P, inr, hs);
+    }
+  };
+  auto count = [&](int j0) {
+    lut_count<D, R>(acc, P, full ? ~0u : inrange_bits<kSteps>(tb, lane, nrows) >> (4 * j0), hs);
+  };
+  auto use = [&](auto& g, const ColD& c) {
+    constexpr bool WIDE = sizeof g.w / sizeof g.w[0] == 2 * S;
+    if (WIDE && c.type == T_I64) {
+      if constexpr (WIDE) lut_col<D, R, T_I64, WIDE>(g, c, a, lane, lds, P, acc);
+    } else if (c.type == T_I32) {
+      lut_col<D, R, T_I32, WIDE>(g, c, a, lane, lds, P, acc);
+    } else if (c.type == T_I8) {
+      lut_col<D, R, T_I8, WIDE>(g, c, a, lane, lds, P, acc);
+    } else {
+      lut_col<D, R, T_I16, WIDE>(g, c, a, lane, lds, P, acc);
+    }
+  };
+  for (int j0 = 0; j0 < kSteps; j0 += S) {
+    start(j0);
+    for (uint32_t c = 0; c < nd;) {
+      const ColD ca = decode_col(*(const CONSTANT v16u*)(cb + c));
+      const ColD cc = decode_col(*(const CONSTANT v16u*)(cb + min(c + 1, nd - 1)));
+      const bool two = c + 1 < nd && cc.type != T_I64 && !cc.valid;
+      Stage<S, true> A;
+      Stage<S, false> B;
+      lut_issue<S, true>(A, ca, tb, nrows, lane, j0);
+      lut_issue<S, false>(B, cc, tb, nrows, lane, j0, two);
+      use(A, ca);
+      if (two) use(B, cc);
+      c += two ? 2 : 1;
+    }
+    count(j0);
   }
 }
 
@@ -2487,14 +2416,14 @@ __device__ __forceinline__ void lut_tile(const CONSTANT LutPass* P, const CONSTA
 // (pass ranges are padded to kLutTileAlign), and copies a pass's LDS tables
 // from device memory when it moves to that pass.
 // Workgroup of the lookup-table kernel (one per CU, whose LDS it takes):
-// twelve waves, three per SIMD (168 vector registers each); with four
-// accumulator dwords the segments hold four rows per lane instead of eight,
-// which fits 128 registers and so sixteen waves, four per SIMD.
-template <int D>
-constexpr uint32_t lbatch_threads() { return D == 4 ? 1024u : 768u; }
+// twelve waves, three per SIMD (168 vector registers each); sixteen waves of
+// eight rows a lane (the tuner's other choice) fit 128 registers where the
+// rows have one or two accumulator dwords (1.44 ms for the 64 programs,
+// against 1.38).
+constexpr uint32_t lbatch_threads(uint32_t dwords, uint32_t rows) { return rows == 8 && dwords < 4 ? 1024u : 768u; }
 
 template <int D, int R>
-__global__ void __launch_bounds__(lbatch_threads<D>()) k_lbatch(LutArgs a) {
+__global__ void __launch_bounds__((lbatch_threads(D, R))) k_lbatch(LutArgs a) {
   extern __shared__ __align__(16) uint32_t dyn[];
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t nw = blockDim.x >> 6;
@@ -2693,30 +2622,29 @@ int sel_launch_luts(const LutArgs& a, void* stream) {
   return (int)hipGetLastError();
 }
 
-// The lookup-table kernel for passes of `dwords` accumulator dwords per row,
-// with `rows` rows per lane per segment (the larger choice, or half of it).
+// The lookup-table kernel for passes of `dwords` accumulator dwords per row.
+// `rows` is the launch configuration's: 8 for sixteen rows per lane at a time,
+// 4 for eight.
 namespace {
 const void* lbatch_kernel(uint32_t dwords, uint32_t rows) {
   switch (dwords) {
-    case 1: return rows == 4 ? (const void*)k_lbatch<1, 4> : (const void*)k_lbatch<1, 8>;
-    case 2: return rows == 4 ? (const void*)k_lbatch<2, 4> : (const void*)k_lbatch<2, 8>;
-    default: return (const void*)k_lbatch<4, 4>;   // four rows per lane: sixteen waves fit
+    case 1: return rows == 4 ? (const void*)k_lbatch<1, 8> : (const void*)k_lbatch<1, 16>;
+    case 2: return rows == 4 ? (const void*)k_lbatch<2, 8> : (const void*)k_lbatch<2, 16>;
+    default: return (const void*)k_lbatch<4, 8>;   // sixteen rows' accumulators would not fit
   }
 }
 }  // namespace
 
 int sel_launch_lbatch(const LutArgs& a, uint32_t dwords, uint32_t rows, uint32_t grid, uint32_t block,
                       uint32_t lds_bytes, void* stream) {
-  if (block == 0 || block > sel_lbatch_block(dwords) || block % kWave) return (int)hipErrorInvalidValue;
+  if (block == 0 || block > sel_lbatch_block(dwords, rows) || block % kWave) return (int)hipErrorInvalidValue;
   LutArgs args = a;
   void* kargs[] = {&args};
   return (int)hipLaunchKernel(lbatch_kernel(dwords, rows), dim3(grid), dim3(block), kargs, lds_bytes,
                               (hipStream_t)stream);
 }
 
-uint32_t sel_lbatch_block(uint32_t dwords) {
-  return dwords == 1 ? lbatch_threads<1>() : dwords == 2 ? lbatch_threads<2>() : lbatch_threads<4>();
-}
+uint32_t sel_lbatch_block(uint32_t dwords, uint32_t rows) { return lbatch_threads(dwords, rows == 4 || dwords == 4 ? 8 : 16); }
 
 int sel_lbatch_occupancy(uint32_t dwords, uint32_t rows, uint32_t block, uint32_t lds_bytes, int* blocks_per_cu) {
   return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, lbatch_kernel(dwords, rows), block,

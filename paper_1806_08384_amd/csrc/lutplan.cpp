@@ -142,7 +142,6 @@ uint32_t dwords_for(const std::vector<uint32_t>& Ws) {
 struct Form {
   std::vector<Clause> clauses;
   std::vector<std::vector<uintptr_t>> cols;   // per clause: its columns (distinct)
-  std::map<uintptr_t, uint32_t> slots;        // per column: register slots of its data
   uint32_t ncross = 0;                        // clauses over several columns
   bool always_false = false;
   const sel_program* prog = nullptr;
@@ -179,8 +178,6 @@ bool make_form(const sel_program* p, Form& f) {
     for (const Lit& L : c) {
       const uintptr_t k = lit_col(L, c);
       if (std::find(cs.begin(), cs.end(), k) == cs.end()) cs.push_back(k);
-      if (is_value(L.ins.op)) f.slots[k] = L.ins.type == T_I64 ? 2u : 1u;
-      else f.slots.emplace(k, 0u);
     }
     if (cs.size() > 1) ++f.ncross;
     f.cols.push_back(std::move(cs));
@@ -369,14 +366,6 @@ std::vector<uint32_t> LutPlan::add(const sel_table* t, uint64_t row_begin, uint6
         if (std::find(key[i].begin(), key[i].end(), k) == key[i].end()) key[i].push_back(k);
     std::sort(key[i].begin(), key[i].end());
   }
-  std::map<uintptr_t, uint32_t> slots;
-  for (const FormRef& r : forms)
-    for (const auto& kv : r.f->slots) slots[kv.first] = std::max(slots[kv.first], kv.second);
-  auto slots_of = [&](const std::set<uintptr_t>& cs) {
-    uint32_t n = 0;
-    for (uintptr_t k : cs) n += slots[k];
-    return n;
-  };
   std::vector<size_t> order(forms.size());
   for (size_t i = 0; i < order.size(); ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return key[x] < key[y]; });
@@ -464,6 +453,20 @@ std::vector<uint32_t> LutPlan::add(const sel_table* t, uint64_t row_begin, uint6
       const int rb = b->kind == LK_VALID ? 2 : b->lds ? 0 : 1;
       return ra < rb;
     });
+    // the kernel loads a narrow column without NULLs together with the one
+    // before it: such a column after each of the others while there are any
+    {
+      std::vector<PassCol*> wide, narrow, out;
+      for (PassCol* c : order_c)
+        if (c->lds && c->kind != LK_VALID) (c->type == T_I64 || c->valid ? wide : narrow).push_back(c);
+      size_t k = 0;
+      for (PassCol* c : wide) {
+        out.push_back(c);
+        if (k < narrow.size()) out.push_back(narrow[k++]);
+      }
+      out.insert(out.end(), narrow.begin() + k, narrow.end());
+      std::copy(out.begin(), out.end(), order_c.begin());
+    }
     LutPass e{};
     e.nrows = t->nrows;
     e.tile_begin = total_tiles;
@@ -496,23 +499,6 @@ std::vector<uint32_t> LutPlan::add(const sel_table* t, uint64_t row_begin, uint6
         }
         e.init[d] = init;
       }
-    }
-    // register slots: int64 columns first (two each, aligned), then the
-    // narrower ones
-    e.slot_col[0] = e.slot_col[1] = ~0u;
-    {
-      uint32_t k = 0;
-      for (int wide = 1; wide >= 0; --wide)
-        for (uint32_t ci = 0; ci < order_c.size(); ++ci) {
-          const PassCol* c = order_c[ci];
-          if (c->kind == LK_VALID || (c->type == T_I64) != (wide == 1)) continue;
-          const uint32_t need = c->type == T_I64 ? 2u : 1u;
-          if (k + need > kLutSlots) return false;
-          for (uint32_t h = 0; h < need; ++h, ++k) {
-            e.slot_col[k / 4] &= ~(0xFFu << (8 * (k % 4)));
-            e.slot_col[k / 4] |= (ci | (h ? kSlotHigh : 0u)) << (8 * (k % 4));
-          }
-        }
     }
     uint32_t lw = 0;
     for (PassCol* c : order_c) {
@@ -590,8 +576,7 @@ std::vector<uint32_t> LutPlan::add(const sel_table* t, uint64_t row_begin, uint6
     std::vector<uint32_t> Ws;
     for (const FormRef* g : cur) Ws.push_back(1 + g->f->ncross);
     Ws.push_back(1 + f.ncross);
-    if (!cur.empty() && (P > kMaxPassProgs || dwords_for(Ws) == 0 || cs.size() > kMaxPassCols ||
-                         slots_of(cs) > kLutSlots)) {
+    if (!cur.empty() && (P > kMaxPassProgs || dwords_for(Ws) == 0 || cs.size() > kMaxPassCols)) {
       flush();
       cs.clear();
       for (const auto& c : f.cols) cs.insert(c.begin(), c.end());

@@ -274,7 +274,7 @@ struct BatchPlan {
   mutable sel::LutArgs largs{};          // as written
   uint32_t num_cus = 256;
   uint32_t lut_block = 0, lut_grid = 0;  // 0: the defaults
-  mutable uint32_t lut_rows = 8;         // rows per lane per segment (four-dword passes: 4)
+  mutable uint32_t lut_rows = 8;         // launch configuration: 8 (sixteen rows per lane at a time) or 4 (eight)
   std::vector<sel::BatchTable> entries;
   std::vector<sel::BatchCol> cols;
   std::vector<DevInstr> leaves;

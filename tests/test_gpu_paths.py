@@ -208,3 +208,42 @@ def test_batch_table_builds(sel, ctx, width, lo, nprog):
     for trees in (plain, other, plain + other):
         got = ctx.count_batch([(dt, ctx.program(dt, tree)) for tree in trees])
         assert got == [orc.count(tree) for tree in trees]
+
+
+@pytest.mark.parametrize("rows", [4, 8])
+@pytest.mark.parametrize("n", [1, 1023, 1025, 2048 * 25, 2048 * 49 + 1500])
+def test_lookup_batch_columns(sel, ctx, n, rows):
+    """The lookup-table kernel over passes of 1 to 16 columns of every type,
+    with NULLs and without, windows and ranks, columns that only null tests
+    read, and one-, two- and four-dword accumulators; both numbers of rows per
+    lane, at the edges of quarter and half tiles and of the counters' reads."""
+    rng = np.random.default_rng(n)
+    t = datagen.random_table(rng, n, types=("i8", "i16", "i32", "i64") * 4, grid=False, null_rate=0.25)
+    for k in (3, 7):       # wide values: ranks
+        t.columns[k].data = rng.integers(-2 ** 61, 2 ** 61, n)
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+
+    def leaf(k):
+        if k in (3, 7):
+            return ("cmp", k, str(rng.choice(["<", ">="])), int(rng.integers(-2 ** 61, 2 ** 61)))
+        r = rng.random()
+        if r < 0.2:
+            return ("isnull", k) if r < 0.1 else ("notnull", k)
+        return ("between", k, int(rng.integers(-21, 5)), int(rng.integers(-4, 21)))
+
+    def tree(cols, cross):
+        parts = [leaf(int(c)) for c in cols]
+        for _ in range(cross):
+            a, b = (int(c) for c in rng.choice(cols, 2, replace=len(cols) < 2))
+            parts.append(("or", leaf(a), ("not", leaf(b))))
+        return parts[0] if len(parts) == 1 else ("and", *parts)
+
+    ctx.set_launch(256, 0, rows_per_lane=rows)
+    for ncols, nprog, cross in ((1, 2, 0), (2, 8, 1), (7, 16, 1), (9, 12, 2), (12, 9, 4), (16, 30, 1)):
+        cols = rng.choice(16, ncols, replace=False)
+        trees = [tree(rng.choice(cols, min(ncols, 1 + k % 4), replace=False), cross if ncols > 1 else 0)
+                 for k in range(nprog)]
+        got = ctx.count_batch([(dt, ctx.program(dt, x)) for x in trees])
+        assert got == [orc.count(x) for x in trees], (ncols, nprog, cross)
+    ctx.set_launch()
