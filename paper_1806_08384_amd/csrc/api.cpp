@@ -139,7 +139,19 @@ int launch_scan(sel_ctx* ctx, int mode, ScanArgs& a, const sel_launch& cfg, cons
       int occ = 0;
       if (block == 256) occ = ctx->occ[mode];
       else if (sel_scan_occupancy(mode, block, &occ) != 0) occ = 1;
-      g = (uint64_t)std::min(std::max(occ, 1), (int)(kScanWavesPerCu / wpb)) * ctx->num_cus;
+      const int per_cu = std::min(std::max(occ, 1), (int)(kScanWavesPerCu / wpb));
+      g = (uint64_t)per_cu * ctx->num_cus;
+      // A table of a few tiles per wave: a fourth workgroup per CU where it
+      // saves enough turns.  A turn of sixteen waves per CU takes 1.25 times
+      // one of twelve; six leaves over 8M rows (2 turns or 1) 42.9 -> 38.6 us,
+      // 16M (3 or 2) 73.4 -> 67.6, but 12M (2 or 2) 53.2 -> 55.6, and from
+      // seven turns on the unequal last one no longer counts (45M: 171.6 ->
+      // 174.9).  The staged constants must leave room for it.
+      if (per_cu == 3 && occ >= 4 && 4ull * (4ull * a.stage_words + 512) <= kLdsPerCu) {
+        const uint64_t t3 = (a.ntiles + g * wpb - 1) / (g * wpb), g4 = 4ull * ctx->num_cus;
+        const uint64_t t4 = (a.ntiles + g4 * wpb - 1) / (g4 * wpb);
+        if (t3 <= 6 && 5 * t4 < 4 * t3) g = g4;
+      }
     }
   }
   const uint64_t need = std::max<uint64_t>((a.ntiles + wpb - 1) / wpb, 1);
