@@ -258,15 +258,16 @@ sel_status check_columns(sel_ctx* ctx, uint64_t nrows, uint32_t ncols, const sel
   return SEL_OK;
 }
 
-// The row-id push-down over the workspace at sp (the context's grow-only
+// Enqueues the row-id push-down over the workspace at sp (the context's grow-only
 // scratch, or the fixed array of the call that allocates nothing).  Every
 // word the kernels read there is written earlier in the same call: the mask
 // pass writes each tile's count, offset and word map and the mask words those
 // maps name, the tile scan writes every offset and chunk value the compaction
-// reads.  So nothing needs clearing between calls.
-sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_program* prog,
-                                uint64_t max_rows, uint32_t* d_out, uint64_t cap,
-                                uint64_t* out_count, char* sp, bool timed) {
+// reads.  So nothing needs clearing between calls, and the push-downs that
+// follow one another on the stream share it.  The count goes to `host`
+// (pinned).
+sel_status enqueue_pushdown(sel_ctx* ctx, const sel_table* table, const sel_program* prog, uint64_t max_rows,
+                            uint32_t* d_out, uint64_t cap, unsigned long long* host, char* sp, bool timed) {
   const RowidScratch L(table->nrows);
   ScanArgs a{};
   a.prog = prog->dcode;
@@ -274,7 +275,7 @@ sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_
   set_stage(a, prog);
   a.nrows = table->nrows;
   a.out = ctx->dout;
-  a.host = ctx->hout;
+  a.host = host;
   a.mask = (uint32_t*)sp;
   a.tile_meta = (uint32_t*)(sp + L.o_meta());
   a.tile_words = (uint64_t*)(sp + L.o_maps());
@@ -318,13 +319,25 @@ sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_
     tl.done();
     if (e) return hip_err(ctx, (hipError_t)e, "compaction launch");
   }
+  return SEL_OK;
+}
+
+sel_status pushdown_outcome(uint64_t count, uint64_t max_rows, uint64_t cap) {
+  if (count > max_rows) return SEL_OVER_LIMIT;   // Algorithm 1: throw, revert
+  return count > cap ? SEL_E_CAPACITY : SEL_OK;
+}
+
+// One push-down, waited for.
+static sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_program* prog,
+                                       uint64_t max_rows, uint32_t* d_out, uint64_t cap, uint64_t* out_count,
+                                       char* sp, bool timed) {
+  sel_status st = enqueue_pushdown(ctx, table, prog, max_rows, d_out, cap, ctx->hout, sp, timed);
+  if (st != SEL_OK) return st;
   uint64_t count = 0;
   st = read_out(ctx, &count, nullptr);   // waits for the compaction too
   if (st != SEL_OK) return st;
   *out_count = count;
-  if (count > max_rows) return SEL_OVER_LIMIT;   // Algorithm 1: throw, revert
-  if (count > cap) return SEL_E_CAPACITY;
-  return SEL_OK;
+  return pushdown_outcome(count, max_rows, cap);
 }
 
 }  // namespace selrt

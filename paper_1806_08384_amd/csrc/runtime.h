@@ -228,10 +228,12 @@ struct RowidScratch {
   size_t total() const { return o_maps() + maps; }
 };
 // The push-down of sel_pushdown_rowids with its workspace at `sp` (at least
-// RowidScratch(nrows).total() bytes of device memory); arguments checked.
-sel_status pushdown_rowids_with(sel_ctx* ctx, const sel_table* table, const sel_program* prog,
-                                uint64_t max_rows, uint32_t* d_out, uint64_t cap,
-                                uint64_t* out_count, char* sp, bool timed);
+// RowidScratch(nrows).total() bytes of device memory) and its count in `host`
+// (pinned), enqueued; arguments checked.  Its outcome, once the stream has
+// run, follows from the count.
+sel_status enqueue_pushdown(sel_ctx* ctx, const sel_table* table, const sel_program* prog, uint64_t max_rows,
+                            uint32_t* d_out, uint64_t cap, unsigned long long* host, char* sp, bool timed);
+sel_status pushdown_outcome(uint64_t count, uint64_t max_rows, uint64_t cap);
 
 // Descriptors of the batched count over per-column lookup tables of program
 // bits (k_luts, k_lbatch): passes of up to 32 programs in conjunctive form.
