@@ -499,6 +499,15 @@ void BatchPlan::add(const sel_table* t, uint64_t row_begin, uint64_t row_end,
   const uint32_t n = (uint32_t)prg_v.size();
   if (n == 0) return;
   const uint64_t tiles = (row_end - row_begin + kTileRows - 1) / kTileRows;
+  // lists that the kernel reads kSlotGroup words at a time
+  auto group_begin = [&] {
+    ops.resize((ops.size() + kSlotGroup - 1) / kSlotGroup * kSlotGroup);
+    return (uint32_t)ops.size();
+  };
+  auto group = [&](const std::vector<uint32_t>& list) {
+    ops.insert(ops.end(), list.begin(), list.end());
+    if (!list.empty()) ops.resize((ops.size() + kSlotGroup - 1) / kSlotGroup * kSlotGroup, list.back());
+  };
   auto flush = [&](Pass& ps) {
     if (ps.progs.empty()) return;
     ps.finalize();
@@ -511,11 +520,11 @@ void BatchPlan::add(const sel_table* t, uint64_t row_begin, uint64_t row_end,
     e.col_begin = (uint32_t)cols.size();
     e.col_count = (uint32_t)ps.cols.size();
     e.ntiles = tiles;
-    e.init_begin = (uint32_t)ops.size();
+    e.init_begin = group_begin();
     e.init_count = (uint32_t)ps.inits.size();
     e.bm_words = ps.bm_words;
     e.slot_words = ps.slots * (uint32_t)kWave;
-    ops.insert(ops.end(), ps.inits.begin(), ps.inits.end());
+    group(ps.inits);
     e.bm_begin = (uint32_t)bms.size();
     e.bm_count = (uint32_t)ps.bms.size();
     bms.insert(bms.end(), ps.bms.begin(), ps.bms.end());
@@ -531,7 +540,19 @@ void BatchPlan::add(const sel_table* t, uint64_t row_begin, uint64_t row_end,
       bc.tab_count = c.tab_count;
       bc.tab_lo = c.tab_lo;
       bc.tab_n = c.tab_n;
-      bc.tab_guarded = c.tab_guarded ? 1u : 0u;
+      if (c.tab_count) {
+        std::vector<uint32_t> slots;
+        bool factors = true;
+        for (uint32_t k = 0; k < c.tab_count; ++k) {
+          const uint32_t s = c.leaves[k].slot;
+          slots.push_back(s);
+          factors &= (s & kAccTarget) && !(s & kAccOr) && (s >> 24) == (slots[0] >> 24);
+        }
+        bc.tab_flags = (c.tab_guarded ? kTabGuarded : 0u) | (factors ? kTabFactors : 0u);
+        bc.tab_slots = group_begin();
+        slots.resize(tab_entry_bytes(c.tab_count) * 8, slots.back());
+        group(slots);
+      }
       col_gtab.push_back(~0ull);
       // every lookup table is built once per launch in device memory by
       // k_tables; an LDS table is then copied into each workgroup's LDS
@@ -553,6 +574,7 @@ void BatchPlan::add(const sel_table* t, uint64_t row_begin, uint64_t row_end,
       leaves.insert(leaves.end(), c.leaves.begin(), c.leaves.end());
       cols.push_back(bc);
     }
+    std::vector<uint32_t> words;   // of programs that are one TRUE word
     for (auto& pr : ps.progs) {
       BatchProg bp{};
       bp.ops = (const uint32_t*)(uintptr_t)ops.size();
@@ -572,12 +594,18 @@ void BatchPlan::add(const sel_table* t, uint64_t row_begin, uint64_t row_end,
       }
       if (and_list) {
         bp.nops = (uint32_t)pr.first.size() | kAndList;
+        if (pr.first.size() == 1) words.push_back(((pr.first[0] >> 8) & 0xFFFu) * (uint32_t)kWave);
         for (uint32_t w : pr.first) ops.push_back(((w >> 8) & 0xFFFu) * (uint32_t)kWave);
       } else {
         ops.insert(ops.end(), pr.first.begin(), pr.first.end());
       }
       bp.acc_index = pr.second;
       progs.push_back(bp);
+    }
+    e.words_begin = kNoLds;
+    if (words.size() == ps.progs.size()) {
+      e.words_begin = group_begin();
+      group(words);
     }
     entries.push_back(e);
     max_slots = std::max(max_slots, ps.slots);

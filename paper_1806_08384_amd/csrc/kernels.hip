@@ -74,6 +74,7 @@ struct Ins {
   const void* aux;
   uint32_t lds_word;
 };
+typedef uint32_t v8u __attribute__((ext_vector_type(8)));
 typedef uint32_t v16u __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ uint64_t pair64(v16u w, int k) { return ((uint64_t)w[k + 1] << 32) | w[k]; }
 __device__ __forceinline__ Ins decode(v16u w) {
@@ -1136,6 +1137,15 @@ __device__ __forceinline__ uint32_t leaf_valid(uint32_t sl, const uint32_t* wl, 
   return vs == kAccNoValid ? ~0u : wl[vs * kWave + lane];
 }
 
+// *w &= x and *w |= x on the lane's own LDS word, by the LDS itself: nothing
+// is read back and waited for.
+__device__ __forceinline__ void lds_and(uint32_t* w, uint32_t x) {
+  __hip_atomic_fetch_and(w, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void lds_or(uint32_t* w, uint32_t x) {
+  __hip_atomic_fetch_or(w, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 // Stores a leaf's TRUE word (its test on non-NULL rows): into its slot, or
 // for a direct factor of a conjunction ANDed into its program's accumulator,
 // or for a leaf of an OR factor of narrow tests ORed into that factor's word.
@@ -1143,17 +1153,19 @@ __device__ __forceinline__ void put_leaf(uint32_t* wl, uint32_t lane, uint32_t s
   const uint32_t T = P & leaf_valid(sl, wl, lane);
   uint32_t* w = wl + (sl & 0xFFFu) * kWave + lane;
   if (!(sl & kAccTarget)) *w = T;
-  else if (sl & kAccOr) *w |= T;
-  else *w &= T;
+  else if (sl & kAccOr) lds_or(w, T);
+  else lds_and(w, T);
 }
 
 // Resets the accumulators of an entry's programs for a new tile.
 __device__ __forceinline__ void reset_acc(const CONSTANT BatchTable* E, const CONSTANT uint32_t* ops,
                                           uint32_t* wl, uint32_t lane) {
   const uint32_t ib = E->init_begin, in = E->init_count;
-  for (uint32_t k = 0; k < in; ++k) {
-    const uint32_t w = ops[ib + k];
-    wl[(w & 0xFFFu) * kWave + lane] = (w & kInitTrue) ? ~0u : 0u;
+  for (uint32_t k = 0; k < in; k += kSlotGroup) {
+    const v8u w = *(const CONSTANT v8u*)(ops + ib + k);
+#pragma unroll
+    for (uint32_t q = 0; q < kSlotGroup; ++q)
+      wl[(w[q] & 0xFFFu) * kWave + lane] = (w[q] & kInitTrue) ? ~0u : 0u;
   }
 }
 
@@ -1275,9 +1287,17 @@ __device__ __forceinline__ void transpose32(uint32_t (&a)[32]) {
 // (entries of E: one bit per leaf, NOUT >= the leaf count) serves them all;
 // transposed, word i holds leaf i's truth bits.
 template <class E, int NOUT, int TY>
-__device__ __forceinline__ void tab_leaves(const Seg& r, const CONSTANT BatchCol* C, CInstr tl,
+__device__ __forceinline__ void tab_leaves(const Seg& r, const CONSTANT BatchCol* C,
+                                           const CONSTANT uint32_t* ops,
                                            const uint32_t* bmlds, uint32_t* wl, uint32_t lane) {
   const uint32_t L32 = (uint32_t)C->tab_lo, n = C->tab_n, m = C->tab_count;
+  uint32_t sl[NOUT];   // uniform
+#pragma unroll
+  for (int i = 0; i < NOUT; i += (int)kSlotGroup) {
+    const v8u s = *(const CONSTANT v8u*)(ops + C->tab_slots + i);
+#pragma unroll
+    for (int q = 0; q < (int)kSlotGroup; ++q) sl[i + q] = s[q];
+  }
   uint32_t T[32];
   if (C->tab_word != kNoLds) {
     const E* tab = (const E*)(bmlds + C->tab_word);
@@ -1290,12 +1310,13 @@ __device__ __forceinline__ void tab_leaves(const Seg& r, const CONSTANT BatchCol
     // 32-bit byte offsets from the table's uniform base (device tables
     // are at most 32 MB)
     const GLOBAL char* tab = gptr<char>(C->gtab);
-    if (C->tab_guarded) {
+    if (C->tab_flags & kTabGuarded) {
       // rows no table leaf needs (the complement of the union of the
       // leaves' guards) read the zero entry n: with g all ones on such a
       // row, min(d | g, n) is n, and on the others it is min(d, n)
       uint32_t need = 0;
-      for (uint32_t i = 0; i < m; ++i) need |= acc_need(tl[i].slot, wl, lane);
+#pragma unroll
+      for (int i = 0; i < NOUT; ++i) need |= acc_need(sl[i], wl, lane);
       const uint32_t skip = ~need;
 #pragma unroll
       for (int b = 0; b < 32; ++b) {
@@ -1316,9 +1337,16 @@ __device__ __forceinline__ void tab_leaves(const Seg& r, const CONSTANT BatchCol
   // row b's entry holds leaf i in bit i; transposed, T[i] holds leaf i's
   // word (bit b = row b)
   transpose32<NOUT>(T);
+  if (C->tab_flags & kTabFactors) {
+    const uint32_t V = leaf_valid(sl[0], wl, lane);
 #pragma unroll
-  for (int i = 0; i < NOUT; ++i)
-    if ((uint32_t)i < m) put_leaf(wl, lane, tl[i].slot, T[i]);
+    for (int i = 0; i < NOUT; ++i)
+      if ((uint32_t)i < m) lds_and(wl + (sl[i] & 0xFFFu) * kWave + lane, T[i] & V);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NOUT; ++i)
+      if ((uint32_t)i < m) put_leaf(wl, lane, sl[i], T[i]);
+  }
 }
 
 // A sparse IN-list leaf of the batched kernel: rows one at a time (its
@@ -1354,7 +1382,8 @@ __device__ __noinline__ uint32_t inlist_rows(CInstr I, uint64_t tb, uint32_t lan
 // segment of their column.
 template <int TY>
 __device__ __forceinline__ void seg_leaves(const Seg& r, const CONSTANT BatchCol* C, int h,
-                                           CInstr leaves, uint64_t tb, uint32_t lane,
+                                           CInstr leaves, const CONSTANT uint32_t* ops,
+                                           uint64_t tb, uint32_t lane,
                                            uint32_t* wl, const uint32_t* bmlds) {
   const uint32_t lb = C->leaf_begin, ln = C->leaf_count;
   const uint32_t tw = TY != T_I64 ? C->tab_word : kNoLds;
@@ -1380,9 +1409,9 @@ __device__ __forceinline__ void seg_leaves(const Seg& r, const CONSTANT BatchCol
   if constexpr (TY != T_I64) {
     if (tw != kNoLds || C->gtab != nullptr) {
       const uint32_t m = C->tab_count;
-      if (m <= 8) tab_leaves<uint8_t, 8, TY>(r, C, leaves + lb, bmlds, wl, lane);
-      else if (m <= 16) tab_leaves<uint16_t, 16, TY>(r, C, leaves + lb, bmlds, wl, lane);
-      else tab_leaves<uint32_t, 32, TY>(r, C, leaves + lb, bmlds, wl, lane);
+      if (m <= 8) tab_leaves<uint8_t, 8, TY>(r, C, ops, bmlds, wl, lane);
+      else if (m <= 16) tab_leaves<uint16_t, 16, TY>(r, C, ops, bmlds, wl, lane);
+      else tab_leaves<uint32_t, 32, TY>(r, C, ops, bmlds, wl, lane);
     }
   }
 }
@@ -1426,10 +1455,10 @@ __device__ __forceinline__ void entry_leaves_full(const CONSTANT BatchTable* E,
     if (more) seg_issue(nxt, nxtV, cols + cb + nc, nh, tb, lane);
     if (h == 0 && C->vslot != kNoSlot) wl[C->vslot * kWave + lane] = curV;
     switch (ty) {
-      case T_I8: seg_leaves<T_I8>(cur, C, h, leaves, tb, lane, wl, bmlds); break;
-      case T_I16: seg_leaves<T_I16>(cur, C, h, leaves, tb, lane, wl, bmlds); break;
-      case T_I32: seg_leaves<T_I32>(cur, C, h, leaves, tb, lane, wl, bmlds); break;
-      default: seg_leaves<T_I64>(cur, C, h, leaves, tb, lane, wl, bmlds); break;
+      case T_I8: seg_leaves<T_I8>(cur, C, h, leaves, ops, tb, lane, wl, bmlds); break;
+      case T_I16: seg_leaves<T_I16>(cur, C, h, leaves, ops, tb, lane, wl, bmlds); break;
+      case T_I32: seg_leaves<T_I32>(cur, C, h, leaves, ops, tb, lane, wl, bmlds); break;
+      default: seg_leaves<T_I64>(cur, C, h, leaves, ops, tb, lane, wl, bmlds); break;
     }
     if (!more) break;
     cur = nxt;
@@ -1576,6 +1605,16 @@ __device__ __forceinline__ uint32_t run_ops2(const CONSTANT uint32_t* ops, uint3
   return tt;
 }
 
+// Star programs (one lookup per dimension and row serves 16 of them) over 160M
+// rows: 230 us with the two dimensions whose tables fit LDS, at the rate of the
+// columns' bytes; a third of 200,000 keys (400 KB) adds 460 us, all of them
+// lines of 128 bytes that L2 sends the CU for two bytes each (0.42 lines a
+// cycle and CU with no row skipped, of 0.5 that 64 bytes a cycle allow), and a
+// fourth of 3.2M keys 250 us.  What a tile does besides is kept off that path:
+// slots are read eight at a time by one scalar load, words combine in the LDS,
+// and programs of one word are counted sixteen at a time (1690 scalar
+// instructions and 219 scalar loads a tile became 800 and 75; 985 -> 943 us).
+//
 // Per workgroup, per-program counts accumulate in LDS; at the end each
 // workgroup adds them to per-program accumulator lines (128 bytes each, so
 // atomics on different programs do not contend), and the last workgroup by
@@ -1604,6 +1643,7 @@ __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
   // workgroup
   const uint64_t ngroups = a.total_tiles / nw;
   uint32_t staged = 0xFFFFFFFFu;
+  uint32_t word0 = 0;   // LDS offset of the TRUE word of the pass's program lane / 4
   for (uint64_t g = blockIdx.x; g < ngroups; g += gridDim.x) {
     const uint64_t flat = g * nw + wave;
     // entry holding this tile: last e with tile_begin <= flat (uniform search)
@@ -1619,6 +1659,8 @@ __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
       // wave must be done with the previous one's first
       __syncthreads();
       wl = bmlds + E->bm_words + wave * E->slot_words;
+      if (E->words_begin != kNoLds)
+        word0 = gptr<uint32_t>(a.ops)[E->words_begin + min(lane >> 2, E->prog_count - 1)];
       if (E->bm_count || E->ntab) {
         // lookup tables: copies of the ones k_tables built in device memory
         for (uint32_t c = 0; c < E->col_count; ++c) {
@@ -1656,6 +1698,28 @@ __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
     } else {
       entry_leaves_partial(E, cols, leaves, tb, lane, nrows, wl, (const CONSTANT uint32_t*)a.ops);
       inr = inrange_bits<kSteps>(tb, lane, nrows);
+    }
+    if (full && E->words_begin != kNoLds) {
+      // every program is one TRUE word: sixteen at a time, a lane counts 16
+      // of the 64 lanes' words of its program, each lane of a program from
+      // another word on (64 banks)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      for (uint32_t k0 = 0; k0 < pn; k0 += 16) {
+        const uint32_t j = lane >> 2, k = k0 + j;
+        const uint32_t off = k0 ? gptr<uint32_t>(a.ops)[E->words_begin + min(k, pn - 1)] : word0;
+        const uint32_t* w = wl + off + (lane & 3u) * 16u;
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i) c += __builtin_popcount(w[(i + j) & 15u]);
+        c += __builtin_amdgcn_update_dpp(0u, c, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+        c += __builtin_amdgcn_update_dpp(0u, c, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+        if ((lane & 3u) == 0 && k < pn && c) {
+          if (pb + k < nacc) atomicAdd(&acc[pb + k], c);
+          else atomicAdd(&a.acc[(uint64_t)progs[pb + k].acc_index * kBatchAccStride], (unsigned long long)c);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      continue;
     }
     // programs in pairs: both popcounts (at most 2048 per wave each) share
     // one wave reduction, 16 bits apart

@@ -320,8 +320,11 @@ constexpr uint32_t kAccNoValid = 0x7Fu;
 // accumulator still holds TRUE.
 constexpr uint32_t kAccGuard = 0xFFFFFFFEu;
 // Accumulator reset list entries: slot | kInitTrue (reset to ~0) or slot
-// (reset to 0), once per tile before the first column.
+// (reset to 0), once per tile before the first column.  Like the lists of
+// slots below, it is read kSlotGroup words at a time: it starts at a multiple
+// of that in the ops array and is padded with its last word.
 constexpr uint32_t kInitTrue = 0x80000000u;
+constexpr uint32_t kSlotGroup = 8;
 inline constexpr uint32_t batch_op(uint32_t op, uint32_t p, uint32_t v) {
   return op | (p << 8) | (v << 20);
 }
@@ -343,7 +346,8 @@ struct BatchTable {            // 80 bytes: one pass over a table or a chunk
   uint32_t init_count;
   uint32_t bm_words;           // LDS layout of this pass: words of its tables
   uint32_t slot_words;         // and staged bitmaps; each wave's slots (slots * 64)
-  uint32_t pad;
+  uint32_t words_begin;        // every program is one TRUE word: the list of their LDS
+                               // offsets, in the ops array; else kNoLds
 };
 
 struct BatchBitmap {           // 24 bytes: a bitmap staged in LDS (batch or scan)
@@ -353,6 +357,13 @@ struct BatchBitmap {           // 24 bytes: a bitmap staged in LDS (batch or sca
   uint32_t lds_word;           // offset in the workgroup's bitmap area
   uint32_t pad;
 };
+
+// Every leaf of a column's lookup table has a guard: rows outside all guards
+// read entry tab_n.
+constexpr uint32_t kTabGuarded = 1u;
+// Every one is a direct factor (kAccTarget without kAccOr), with one validity
+// word for all.
+constexpr uint32_t kTabFactors = 2u;
 
 struct BatchCol {              // 64 bytes: a column one entry reads
   const void* data;
@@ -372,9 +383,8 @@ struct BatchCol {              // 64 bytes: a column one entry reads
   int32_t tab_lo;
   uint32_t tab_n;
   const uint32_t* gtab;
-  uint32_t tab_guarded;        // every table leaf has a guard: rows outside
-                               // all guards read entry tab_n
-  uint32_t pad;
+  uint32_t tab_flags;          // kTabGuarded, kTabFactors
+  uint32_t tab_slots;          // its table leaves' slot fields, in the ops array
 };
 
 // A lookup table in device memory, built by k_tables before the batch

@@ -247,3 +247,30 @@ def test_lookup_batch_columns(sel, ctx, n, rows):
         got = ctx.count_batch([(dt, ctx.program(dt, x)) for x in trees])
         assert got == [orc.count(x) for x in trees], (ncols, nprog, cross)
     ctx.set_launch()
+
+
+@pytest.mark.parametrize("nprog", [1, 8, 9, 15, 16, 17, 33])
+def test_leaf_batch_words(sel, ctx, monkeypatch, nprog):
+    """The leaf kernel over passes whose programs are all one TRUE word (read
+    sixteen at a time) and passes where some are not, with each width of a
+    lookup table's entries, leaves of conjunctions and of OR factors in one
+    table, several leaves of one program in it, and a nullable column."""
+    monkeypatch.setenv("SEL_BATCH_KERNEL", "leaf")
+    rng = np.random.default_rng(nprog)
+    n = 2048 * 27 + 700
+    t = datagen.random_table(rng, n, types=("i8", "i16", "i32", "i32"), grid=False, null_rate=0.0)
+    valid = datagen.words_from_codes([i for i in range(n) if i % 5], n)
+    t.columns[1].valid = valid
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+
+    def leaf(k):
+        if rng.random() < 0.5:
+            return ("in", k, tuple(int(v) for v in rng.choice(np.arange(-20, 21), 9, replace=False)))
+        return ("between", k, int(rng.integers(-21, 0)), int(rng.integers(0, 21)))
+
+    one = [("and", *(leaf(k) for k in rng.permutation(4)), leaf(1), leaf(1)) for _ in range(nprog)]
+    mixed = [("and", leaf(0), ("or", leaf(1), leaf(2)), leaf(1)) for _ in range(nprog)]
+    for trees in (one, mixed, one + mixed + [("or", leaf(0), ("isunknown", leaf(1)))]):
+        got = ctx.count_batch([(dt, ctx.program(dt, tree)) for tree in trees])
+        assert got == [orc.count(tree) for tree in trees]
