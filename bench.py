@@ -248,7 +248,7 @@ def bench_batch(ctx, fact_dt, threads, log):
             "frac": batch_bytes / graph_kernel_ms / 1e6 / HBM_PEAK_GBS,
             # the graph's lookup-table launches (one per accumulator width)
             # and table builds, from the committed profile of this batch
-            "traffic": measured_traffic(["k_lbatch<2, 8>", "k_lbatch<4, 4>", "k_luts"],
+            "traffic": measured_traffic(["k_lbatch<2, 16>", "k_lbatch<4, 8>", "k_luts"],
                                         "batch_64programs_4tables.md"),
         },
     }
@@ -891,7 +891,7 @@ def main():
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": measured_traffic("k_scan<1, true>"),
+            "traffic": measured_traffic("k_scan<1, true, 8>"),
             "avg_kernel_ms": mask_avg_s * 1e3,
             "algorithmic_bytes_per_launch": mask_kernel_bytes,
             "mask_words_written": mask_words,

