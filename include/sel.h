@@ -591,7 +591,8 @@ uint32_t sel_tune_entries(const sel_ctx* ctx);
 
 /* Kernel timing: when enabled, the library brackets each scan-kernel launch
  * with HIP events on the context's stream and accumulates the elapsed time
- * per kernel kind.  Reading the totals synchronises the stream. */
+ * per kernel kind.  Reading the totals synchronises the stream and waits for
+ * every launch counted, a captured batch's on its own stream too. */
 typedef enum sel_kernel_kind {
   SEL_K_COUNT = 0,       /* fused evaluate + count                      */
   SEL_K_MASK = 1,        /* evaluate + count + packed result mask,

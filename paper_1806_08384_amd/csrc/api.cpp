@@ -470,15 +470,26 @@ sel_status sel_ctx_read_timing(sel_ctx* ctx, sel_timing* out, int reset) {
   if (!ctx || !out) return set_err(ctx, SEL_E_INVALID, "NULL argument");
   DeviceGuard g(ctx->device);
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+  // a captured batch's events lie on its own stream, and its run returns when
+  // the counts are there, which may be before the stop event: each is waited
+  // for, so that no finished launch is missed
+  hipError_t failed = hipSuccess;
   for (auto& p : ctx->pending) {
     float ms = 0.f;
-    if (hipEventElapsedTime(&ms, p.second.a, p.second.b) == hipSuccess) {
+    hipError_t e = hipEventSynchronize(p.second.b);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, p.second.a, p.second.b);
+    if (e == hipSuccess) {
       ctx->ms[p.first] += ms;
       ctx->launches[p.first] += 1;
+    } else {
+      (void)hipGetLastError();
+      // (events recorded into a stream capture have no time: not an error)
+      if (e != hipErrorInvalidHandle && e != hipErrorCapturedEvent) failed = e;
     }
     ctx->free_events.push_back(p.second);
   }
   ctx->pending.clear();
+  if (failed != hipSuccess) return hip_err(ctx, failed, "kernel timing events");
   for (int k = 0; k < SEL_K_NKINDS; ++k) {
     out->ms[k] = ctx->ms[k];
     out->launches[k] = ctx->launches[k];

@@ -274,3 +274,24 @@ def test_leaf_batch_words(sel, ctx, monkeypatch, nprog):
     for trees in (one, mixed, one + mixed + [("or", leaf(0), ("isunknown", leaf(1)))]):
         got = ctx.count_batch([(dt, ctx.program(dt, tree)) for tree in trees])
         assert got == [orc.count(tree) for tree in trees]
+
+
+def test_timing_counts_every_batch_run(sel, ctx):
+    """A batch run returns when its counts are there; read right after it, the
+    timing holds that run: one launch, with a time."""
+    n = 2048 * 40 + 9
+    t = datagen.Table("timed", n)
+    t.columns.append(datagen.Column("row", "i32", np.arange(n, dtype=np.int32)))
+    dt = sel.device_table(ctx, t)
+    pairs = [(dt, ctx.program(dt, ("cmp", 0, "<", k))) for k in (5, 700, n)]
+    batch = ctx.batch(pairs)
+    ctx.enable_timing(True)
+    try:
+        ctx.read_timing(reset=True)
+        for k in range(60):
+            assert batch.run() == [5, 700, n]
+            ms, launches = ctx.read_timing(reset=True)
+            assert launches[sel.K_BATCH] == 1 and ms[sel.K_BATCH] > 0, k
+    finally:
+        ctx.enable_timing(False)
+        batch.destroy()
