@@ -295,13 +295,14 @@ sel_status enqueue_pushdown(sel_ctx* ctx, const sel_table* table, const sel_prog
   c.total = ctx->dout;
   c.limit = std::min(max_rows, cap);
   // A table of which each scan wave takes one tile: tiles are placed by their
-  // numbers, a wave's first id is at most a few KB of counts away, and a
+  // numbers, a wave's first id is at most kSumTiles counts (16 KB) away, and a
   // wave per tile keeps the short launch wide (16 tiles a workgroup
   // and two launches for the counts: 23 us for 1M rows, against 5 us).
-  // Larger ones take the counts' scan, and four tiles a wave.
+  // Larger ones, also where a caller's grid gives each tile a wave, take the
+  // counts' scan, and four tiles a wave.
   // (A quarter tile counts as a tile there, and four of them as one here.)
   c.tiles_per_wave = 4;
-  if (a.ntiles <= a.order.waves && a.order.tps == 1) {
+  if (a.ntiles <= kSumTiles && a.ntiles <= a.order.waves && a.order.tps == 1) {
     if (!a.small) c.tiles_per_wave = 1;
   } else {
     uint32_t* offsets = (uint32_t*)(sp + L.o_offsets());

@@ -295,3 +295,34 @@ def test_timing_counts_every_batch_run(sel, ctx):
     finally:
         ctx.enable_timing(False)
         batch.destroy()
+
+
+@pytest.mark.parametrize("tiles", [4095, 4096, 4097, 9000])
+def test_row_ids_of_a_large_grid(sel, ctx, tiles):
+    """Row ids where the caller's grid gives every tile a scan wave of its own,
+    with few tiles and many: beyond 4096 tiles the counts go through their scan
+    (each compaction wave adding up all counts before its own reads a number of
+    them that grows with the square of the tiles)."""
+    n = 2048 * tiles - 77
+    rng = np.random.default_rng(tiles)
+    hit = (rng.random(n) < 0.02).astype(np.int8)
+    table = datagen.Table("grid", n)
+    table.columns.append(datagen.Column("hit", "i8", hit))
+    dt = sel.device_table(ctx, table)
+    prog = ctx.program(dt, ("cmp", 0, "=", 1))
+    want = np.flatnonzero(hit).astype(np.uint32)
+    ctx.set_launch(block=256, grid=1 << 14)
+    ctx.enable_timing(True)
+    try:
+        ctx.read_timing(reset=True)
+        out = ids_tensor(len(want) + 1, torch)
+        assert ctx.pushdown_rowids(dt, prog, UINT64_MAX, out) == (sel.SEL_OK, len(want))
+        np.testing.assert_array_equal(as_u32(out)[:-1], want)
+        assert as_u32(out)[-1] == 0xDEADBEEF
+        _, launches = ctx.read_timing(reset=True)
+        assert launches[sel.K_MASK] == 1 and launches[sel.K_COMPACT] == 1
+        if tiles > 4096:
+            assert launches[sel.K_SCAN] == 1
+    finally:
+        ctx.enable_timing(False)
+        ctx.set_launch()
