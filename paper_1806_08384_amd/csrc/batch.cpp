@@ -21,14 +21,14 @@ struct sel_batch {
   std::vector<const sel_table*> tabs;         // per caller index
   std::vector<const sel_program*> slot_prog;  // per caller index
   BatchPlan plan;
-  void* dev = nullptr;                        // descriptors | acc | slot | tables
+  void* dev = nullptr;                        // descriptors | acc | ticket | tables
   size_t desc_cap = 0, gtab_cap = 0;
   uint32_t* d_gtab = nullptr;
   const TableBuild* d_builds = nullptr;       // as captured
   uint32_t nbuilds = 0;
   uint64_t table_units = 0;
   unsigned long long* d_acc = nullptr;
-  DevSlot* d_slot = nullptr;
+  BatchTicket* d_slot = nullptr;
   unsigned long long* h_out = nullptr;        // pinned
   hipStream_t stream = nullptr;
   hipEvent_t ready = nullptr;
@@ -118,13 +118,10 @@ void batch_shape(sel_ctx* ctx, uint32_t nprogs, const BatchPlan& bp, uint32_t& g
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Workspace after the descriptors: accumulator lines, slot.
-size_t tail_bytes(uint32_t n) { return up256((size_t)n * kBatchAccStride * 8) + 256; }
-
-void place_tail(char* base, size_t desc_cap, uint32_t n, unsigned long long*& acc, DevSlot*& slot) {
-  acc = (unsigned long long*)(base + desc_cap);
-  slot = (DevSlot*)(base + desc_cap + up256((size_t)n * kBatchAccStride * 8));
-}
+// Workspace after the descriptors: accumulator lines, and for a captured batch
+// its ticket (an eager one takes the context's).
+size_t acc_bytes(uint32_t n) { return up256((size_t)n * kBatchAccStride * 8); }
+size_t tail_bytes(uint32_t n) { return acc_bytes(n) + up256(sizeof(BatchTicket)); }
 
 // Writes the plan's descriptors to `dev` in stream order and fills `a`.
 sel_status upload_plan(sel_ctx* ctx, const BatchPlan& bp, char* dev, uint32_t* gtab, BatchArgs& a,
@@ -188,7 +185,8 @@ sel_status rebuild(sel_batch* b) {
     HIP_TRY(ctx, hipMemsetAsync(b->dev, 0, total, ctx->stream), "hipMemsetAsync(batch)");
     b->desc_cap = cap;
     b->gtab_cap = gcap;
-    place_tail((char*)b->dev, cap, b->n, b->d_acc, b->d_slot);
+    b->d_acc = (unsigned long long*)((char*)b->dev + cap);
+    b->d_slot = (BatchTicket*)((char*)b->dev + cap + acc_bytes(b->n));
     b->d_gtab = (uint32_t*)((char*)b->dev + cap + tail_bytes(b->n));
   }
   BatchArgs a{};
@@ -248,10 +246,10 @@ sel_status sel_count_batch(sel_ctx* ctx, uint32_t n, const sel_table* const* tab
   sel_status st = plan_batch(ctx, n, tables, progs, bp);
   if (st != SEL_OK) return st;
   DeviceGuard g(ctx->device);
-  // workspace in the context's batch area: descriptors, then accumulators,
-  // counts and the slot
+  // workspace in the context's batch area: descriptors, then accumulators and
+  // lookup tables
   const size_t desc = up256(bp.bytes());
-  const size_t bytes = desc + tail_bytes(n) + up256(bp.gtab_total() * 4);
+  const size_t bytes = desc + acc_bytes(n) + up256(bp.gtab_total() * 4);
   if (bytes > ctx->batch_bytes) {
     if (ctx->batch_mem) {
       (void)hipStreamSynchronize(ctx->stream);
@@ -265,21 +263,19 @@ sel_status sel_count_batch(sel_ctx* ctx, uint32_t n, const sel_table* const* tab
   }
   char* base = (char*)ctx->batch_mem;
   BatchArgs a{};
-  unsigned long long* acc;
-  DevSlot* slot;
-  place_tail(base, desc, n, acc, slot);
+  unsigned long long* acc = (unsigned long long*)(base + desc);
   // the accumulators move with the descriptor size: clear this call's lines
   int e = sel_launch_fill((uint32_t*)acc, (size_t)n * kBatchAccStride * 2, 0u, ctx->stream);
   if (e) return hip_err(ctx, (hipError_t)e, "accumulator clear");
   const TableBuild* d_builds = nullptr;
-  st = upload_plan(ctx, bp, base, (uint32_t*)(base + desc + tail_bytes(n)), a, &d_builds);
+  st = upload_plan(ctx, bp, base, (uint32_t*)(base + desc + acc_bytes(n)), a, &d_builds);
   if (st != SEL_OK) return st;
   a.acc = acc;
   a.done = nullptr;
   a.ndone = n;
   a.out = ctx->hbatch;
   for (uint32_t i = 0; i < n; ++i) ctx->hbatch[i] = kPending;
-  a.slot = ctx->slot;
+  a.slot = &ctx->slot->batch;
   uint32_t grid, block;
   batch_shape(ctx, n, bp, grid, block);
   {

@@ -93,8 +93,8 @@ struct DevInstr {          // 64 bytes, read with scalar loads
 };
 static_assert(sizeof(DevInstr) == 64, "DevInstr layout");
 
-// Per-launch completion slot: counters that the last workgroups reset, so
-// that no memset is needed between launches.  A scan's workgroups add their
+// Completion slot of a context's launches: counters that the last workgroups
+// reset, so that no memset is needed between launches.  A scan's workgroups add their
 // counts and take their tickets in one word: the low 40 bits hold the count
 // (at most 2^32), the high 24 the workgroups done -- first in one of
 // kSlotParts words, each in a cache line of its own, whose last workgroups
@@ -102,14 +102,19 @@ static_assert(sizeof(DevInstr) == 64, "DevInstr layout");
 constexpr unsigned long long kSlotTicket = 1ull << 40;
 constexpr uint32_t kSlotMaxGrid = 1u << 24;
 constexpr uint32_t kSlotParts = 16, kSlotStride = 16;
+// A batch launch's completion ticket, in a cache line of its own.
+struct BatchTicket {
+  unsigned int ticket;
+  unsigned int pad[31];
+};
 struct DevSlot {
   unsigned long long acc;    // running count and tickets of a scan's parts
   unsigned long long acc2;   // second counter (out-of-range keys)
-  unsigned int ticket;       // a batch launch's ticket
-  unsigned int pad[27];
+  unsigned int pad[28];
   unsigned long long part[kSlotParts * kSlotStride];   // of a scan
+  BatchTicket batch;         // of an eager batch
 };
-static_assert(sizeof(DevSlot) == 128 + 128 * kSlotParts, "DevSlot layout");
+static_assert(sizeof(DevSlot) == 256 + 128 * kSlotParts, "DevSlot layout");
 
 enum ScanMode : int { M_COUNT = 0, M_MASK = 1, M_KEYBITMAP = 2 };
 
@@ -436,7 +441,7 @@ struct BatchArgs {
   uint32_t ndone;
   uint32_t acc_words;          // LDS counters: min(nprogs, kBatchMaxProgs)
   unsigned long long* out;
-  DevSlot* slot;
+  BatchTicket* slot;
 };
 
 // ---- batched count over per-column lookup tables of program bits ---------
@@ -544,7 +549,7 @@ struct LutArgs {
   uint32_t ndone;
   uint32_t pad;
   unsigned long long* out;
-  DevSlot* slot;
+  BatchTicket* slot;
 };
 
 }  // namespace sel

@@ -82,7 +82,7 @@ struct RoundSlot {                          // per in-flight round
   selrt::BatchPlan plan;                    // this round's descriptors
   unsigned long long* h_out = nullptr;      // pinned, finished counts
   hipEvent_t start_ev = nullptr, done_ev = nullptr;   // the round's device time
-  DevSlot* slot = nullptr;                  // ticket of this slot's launches
+  BatchTicket* slot = nullptr;              // ticket of this slot's launches
   std::vector<Member> members;              // programs this round counts for
   uint32_t ngroups = 0;                     // distinct programs (lines) in it
   bool busy = false;
@@ -499,11 +499,11 @@ sel_status sel_server_create(sel_ctx* ctx, const sel_server_config* cfg, sel_ser
   do {
     if ((e = hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking)) != hipSuccess) { where = "hipStreamCreate"; break; }
     const size_t acc_bytes = (size_t)kMaxLines * kBatchAccStride * 8;
-    const size_t slot_bytes = 256 * s->slots.size();
+    const size_t slot_bytes = sizeof(BatchTicket) * s->slots.size();
     if ((e = hipMalloc((void**)&s->d_acc, acc_bytes + slot_bytes)) != hipSuccess) { where = "hipMalloc(server)"; break; }
     if ((e = hipMemset(s->d_acc, 0, acc_bytes + slot_bytes)) != hipSuccess) { where = "hipMemset(server)"; break; }
     for (size_t k = 0; k < s->slots.size(); ++k) {
-      s->slots[k].slot = (DevSlot*)((char*)s->d_acc + acc_bytes + 256 * k);
+      s->slots[k].slot = (BatchTicket*)((char*)s->d_acc + acc_bytes) + k;
       if ((e = hipEventCreate(&s->slots[k].done_ev)) != hipSuccess ||
           (e = hipEventCreate(&s->slots[k].start_ev)) != hipSuccess) { where = "hipEventCreate"; break; }
     }
