@@ -214,24 +214,42 @@ constexpr uint64_t kSmallScanRows = 1u << 20;
 // 31.7 and 29.3.
 constexpr uint64_t kSumTiles = 4096;
 
-// Byte layout of the row-id path's workspace for a table of nrows rows:
-// the packed mask words, tile counts and offsets in their streams, tile id
-// offsets, chunk sums, tile word maps, in that order.
-struct RowidScratch {
-  size_t mask, words, chunk, maps;
+// Byte layout of the row-id path's workspace for a table of nrows rows: the
+// packed mask words, tile counts and offsets in their streams, tile id
+// offsets, chunk sums, tile word maps, in that order.  A table that is scanned
+// by quarter tiles has four maps and four counts a tile but no id offsets or
+// chunk sums; a caller's shape may scan it by whole tiles all the same, whose
+// offsets and sums then lie behind their fewer maps.  So no table takes more
+// than N/8 + 16 bytes per 2048 rows + 16 KB (the chunk sums use half of that
+// room; it bounds which tables fit the fixed workspace).
+class RowidScratch {
+  size_t meta_, offsets_, chunks_, maps_, total_;
+
+ public:
   explicit RowidScratch(uint64_t nrows) {
+    auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t ntiles = (size_t)((nrows + sel::kTileRows - 1) / sel::kTileRows);
-    const size_t units = nrows <= kSmallScanRows ? ntiles * (sel::kSteps / sel::kSmallSteps) : ntiles;
-    mask = ntiles * sel::kWave * 4;
-    words = (units * 4 + 255) & ~size_t(255);
-    chunk = 2 * 2048 * 4;
-    maps = (units * 8 + 255) & ~size_t(255);
+    const size_t mask = ntiles * sel::kWave * 4;
+    if (nrows <= kSmallScanRows) {
+      const size_t quarters = ntiles * (sel::kSteps / sel::kSmallSteps);
+      maps_ = mask;
+      offsets_ = maps_ + up(ntiles * 8);
+      chunks_ = offsets_ + up(ntiles * 4);
+      meta_ = std::max(maps_ + up(quarters * 8), chunks_ + up(4));
+      total_ = meta_ + up(quarters * 4);
+    } else {
+      meta_ = mask;
+      offsets_ = meta_ + up(ntiles * 4);
+      chunks_ = offsets_ + up(ntiles * 4);
+      maps_ = chunks_ + 2 * 2048 * 4;
+      total_ = maps_ + up(ntiles * 8);
+    }
   }
-  size_t o_meta() const { return mask; }
-  size_t o_offsets() const { return mask + words; }
-  size_t o_chunks() const { return mask + 2 * words; }
-  size_t o_maps() const { return mask + 2 * words + chunk; }
-  size_t total() const { return o_maps() + maps; }
+  size_t o_meta() const { return meta_; }
+  size_t o_offsets() const { return offsets_; }
+  size_t o_chunks() const { return chunks_; }
+  size_t o_maps() const { return maps_; }
+  size_t total() const { return total_; }
 };
 // The push-down of sel_pushdown_rowids with its workspace at `sp` (at least
 // RowidScratch(nrows).total() bytes of device memory) and its count in `host`

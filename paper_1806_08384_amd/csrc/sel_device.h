@@ -22,8 +22,7 @@ constexpr int kSmallSteps = 2;                            // of a small scan's q
 constexpr int kMaxDepth = 8;
 
 // Bytes of the fixed device workspace of the push-down that allocates
-// nothing (mask words, tile counts and offsets, chunk sums and offsets,
-// tile word maps): 64 MiB, enough for tables of about 505 M rows.
+// nothing (mask words, tile counts and offsets, chunk sums, tile word maps): 64 MiB, enough for tables of about 505 M rows.
 constexpr unsigned long long kNoAllocScratchBytes = 64ull << 20;
 
 enum DevType : uint32_t { T_I8 = 1, T_I16 = 2, T_I32 = 3, T_I64 = 4 };

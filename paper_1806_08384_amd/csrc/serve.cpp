@@ -144,7 +144,8 @@ uint64_t footprint_of(const sel_server* s, const Request& r) {
   for (const sel_program* p : r.progs) f += p->nins * sizeof(DevInstr);
   if (r.has_pd) {
     const uint64_t nt = ntiles_of(r.pd_table->nrows);
-    // mask, tile word maps, tile counts, offsets, ids
+    // mask, tile word maps, tile counts, offsets, ids (RowidScratch's fixed
+    // part, at most 16 KB, is the push-down context's, whatever it serves)
     f += nt * kWave * 4 + nt * 8 + 2 * nt * 4 + r.pd_cap * 4;
   }
   return f;

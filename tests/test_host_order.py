@@ -18,3 +18,12 @@ def test_batch_ticket_fits_its_place(tmp_path):
                     f"{ROOT}/tests/host/batch_ticket.cpp", "-o", str(exe)], check=True)
     done = subprocess.run([str(exe)], capture_output=True, text=True)
     assert done.returncode == 0, done.stdout
+
+
+def test_rowid_workspace(tmp_path):
+    exe = tmp_path / "rowid_scratch"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    f"-I{ROOT}/include", f"-I{ROOT}/paper_1806_08384_amd/csrc",
+                    f"{ROOT}/tests/host/rowid_scratch.cpp", "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert done.returncode == 0, done.stdout
