@@ -273,6 +273,40 @@ __device__ __forceinline__ void load8(const void* data, uint64_t tb, uint32_t la
   }
 }
 
+// Bitmap, hashed-list or sorted-list test of eight values, appended to P: the
+// constants at `words`, which are 64-bit `values` to the lists, in LDS or in
+// device memory.
+template <bool HASHED, class Words, class Values>
+__device__ __forceinline__ uint32_t const_bits8(uint32_t P, const Ins& I, const int64_t (&x)[8], Words words, Values values) {
+  if (I.op == D_BITMAP) {
+#pragma unroll
+    for (int k = 7; k >= 0; --k) {
+      const uint64_t d = (uint64_t)x[k] - (uint64_t)I.lo;
+      const uint32_t at = d < I.span ? (uint32_t)d : 0u;   // nbits <= 2^32
+      P = (P << 1) + ((uint32_t)(d < I.span) & ((words[at >> 5] >> (at & 31)) & 1u));
+    }
+  } else if (HASHED && (I.flags & F_HASHED)) {
+    const uint32_t f = I.flags, b = in_hash_bits(f);
+    const uint32_t c1 = kInHashMul[in_hash_pair(f)][0], c2 = kInHashMul[in_hash_pair(f)][1];
+#pragma unroll
+    for (int k = 7; k >= 0; --k) {
+      const int64_t h1 = values[in_hash(x[k], c1, b)], h2 = values[(1u << b) + in_hash(x[k], c2, b)];
+      P = (P << 1) + ((uint32_t)(h1 == x[k]) | (uint32_t)(h2 == x[k]));
+    }
+  } else {  // D_INLIST: lower bound in the sorted list
+    uint32_t base[8] = {};
+    for (uint32_t len = I.n; len > 1;) {
+      const uint32_t half = len >> 1;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) base[k] = values[base[k] + half] <= x[k] ? base[k] + half : base[k];
+      len -= half;
+    }
+#pragma unroll
+    for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)(values[base[k]] == x[k]);
+  }
+  return P;
+}
+
 // One leaf on the partial last tile of its table, eight rows of a lane at a
 // time (rows past the table test a zero and are not counted).  The values are
 // widened to int64, so that one short body serves every type and test: the
@@ -280,14 +314,16 @@ __device__ __forceinline__ void load8(const void* data, uint64_t tb, uint32_t la
 // Four loads in turn per leaf; element loads, one row of a lane after
 // another, were 32 (six leaves over 10 007 rows: 37 us, with these 19, and
 // 9 with the quarter tiles of small tables).
-// SCAN: a scan's leaf, whose flags are DevFlags (a batch's copies of the
-// leaves reuse that word, and read an IN list through its sorted values).
+// Staged constants are read from LDS here too: a sorted list's searches are
+// 4 log2(n) dependent reads, which in device memory made this one tile outlast
+// the rest of the scan (60M int64 rows against 1500 values: 214 us).
+// SCAN: a scan's leaf, whose flags are DevFlags and whose constants may be
+// staged (a batch's copies of the leaves reuse these words, and read an IN
+// list through its sorted values in device memory).
 template <bool SCAN>
-__device__ __forceinline__ uint32_t partial_leaf(const Ins& I, uint32_t ty, uint64_t tb, uint32_t lane, uint64_t nrows) {
-  const uint32_t op = I.op;
+__device__ __forceinline__ uint32_t partial_leaf(const Ins& I, uint32_t ty, uint64_t tb, uint32_t lane, uint64_t nrows,
+                                                 const StageView& sv) {
   const void* data = I.data;
-  const int64_t lo = I.lo;
-  const uint64_t span = I.span;
   uint32_t P = 0;
 #pragma unroll 1
   for (int q = 3; q >= 0; --q) {
@@ -298,37 +334,15 @@ __device__ __forceinline__ uint32_t partial_leaf(const Ins& I, uint32_t ty, uint
       case T_I32: load8<T_I32, false, true>(data, tb, lane, nrows, q, x); break;
       default: load8<T_I64, false, true>(data, tb, lane, nrows, q, x); break;
     }
-    if (op == D_RANGE) {
+    if (I.op == D_RANGE) {
 #pragma unroll
-      for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)((uint64_t)x[k] - (uint64_t)lo <= span);
-    } else if (op == D_BITMAP) {
-      const GLOBAL uint32_t* bits = gptr<uint32_t>(I.aux);
-#pragma unroll
-      for (int k = 7; k >= 0; --k) {
-        const uint64_t d = (uint64_t)x[k] - (uint64_t)lo;
-        const uint32_t at = d < span ? (uint32_t)d : 0u;   // nbits <= 2^32
-        P = (P << 1) + ((uint32_t)(d < span) & ((bits[at >> 5] >> (at & 31)) & 1u));
-      }
-    } else if (SCAN && (I.flags & F_HASHED)) {
-      const uint32_t f = I.flags, b = in_hash_bits(f);
-      const uint32_t c1 = kInHashMul[in_hash_pair(f)][0], c2 = kInHashMul[in_hash_pair(f)][1];
-      const GLOBAL int64_t* T = gptr<int64_t>(I.aux) + I.n;
-#pragma unroll
-      for (int k = 7; k >= 0; --k) {
-        const int64_t h1 = T[in_hash(x[k], c1, b)], h2 = T[(1u << b) + in_hash(x[k], c2, b)];
-        P = (P << 1) + ((uint32_t)(h1 == x[k]) | (uint32_t)(h2 == x[k]));
-      }
-    } else {  // D_INLIST: lower bound in the sorted list
-      const GLOBAL int64_t* list = gptr<int64_t>(I.aux);
-      uint32_t base[8] = {};
-      for (uint32_t len = I.n; len > 1;) {
-        const uint32_t half = len >> 1;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) base[k] = list[base[k] + half] <= x[k] ? base[k] + half : base[k];
-        len -= half;
-      }
-#pragma unroll
-      for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)(list[base[k]] == x[k]);
+      for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)((uint64_t)x[k] - (uint64_t)I.lo <= I.span);
+    } else if (SCAN && I.lds_word < sv.words) {
+      const uint32_t* copy = sv.lds + I.lds_word;
+      P = const_bits8<SCAN>(P, I, x, copy, (const int64_t*)copy);
+    } else {
+      const bool tables = SCAN && I.op == D_INLIST && (I.flags & F_HASHED);   // they follow the list
+      P = const_bits8<SCAN>(P, I, x, gptr<uint32_t>(I.aux), gptr<int64_t>(I.aux) + (tables ? I.n : 0u));
     }
   }
   return P;
@@ -483,7 +497,7 @@ __device__ __forceinline__ void eval_leaf(const Ins& I, uint64_t tb, uint32_t la
   else if (flags & F_GUARD_OR) need = ~tos_t;
   uint32_t P;
   if constexpr (PARTIAL) {
-    P = partial_leaf<true>(I, I.type, tb, lane, nrows);
+    P = partial_leaf<true>(I, I.type, tb, lane, nrows, sv);
   } else {
     switch (I.type) {
       case T_I8: P = leaf_pred<T_I8, NS, NT>(I, tb, nrows, lane, need, sv); break;
@@ -1488,7 +1502,7 @@ __device__ __forceinline__ void entry_leaves_partial(const CONSTANT BatchTable* 
     if (vs != kNoSlot) wl[vs * kWave + lane] = valid_bits<false>(C->valid, tb, lane, nrows);
     for (uint32_t k = 0; k < ln; ++k) {
       CInstr I = leaves + lb + k;
-      const uint32_t P = partial_leaf<false>(load_ins(I), C->type, tb, lane, nrows);
+      const uint32_t P = partial_leaf<false>(load_ins(I), C->type, tb, lane, nrows, StageView{});
       put_leaf(wl, lane, I->slot, P);
     }
   }

@@ -326,3 +326,65 @@ def test_row_ids_of_a_large_grid(sel, ctx, tiles):
     finally:
         ctx.enable_timing(False)
         ctx.set_launch()
+
+
+@pytest.mark.parametrize("stage", [0, 1])
+@pytest.mark.parametrize("tail", [1, 63, 700, 2047])
+def test_partial_tile_constants(sel, ctx, tail, stage):
+    """A whole-tile scan's partial last tile with its constants staged in LDS
+    and not: sorted lists short and long, hashed lists and bitmaps, on every
+    column type, two of one list among them."""
+    n = 2048 * 9 + tail
+    rng = np.random.default_rng(tail)
+    t = datagen.random_table(rng, n, grid=False, null_rate=0.2)
+    t.columns.append(datagen.Column("far", "i64", rng.integers(-2 ** 62, 2 ** 62, n)))
+    t.columns.append(datagen.Column("wide", "i32", rng.integers(-2 ** 31, 2 ** 31, n).astype(np.int32)))
+    t.columns.append(datagen.Column("code", "i32", rng.integers(0, 9000, n).astype(np.int32), dict_card=9000))
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+
+    def some(k, m):
+        x = t.columns[k].data
+        lim = 2 ** 62 if k == 4 else 2 ** 31
+        return tuple(int(v) for v in np.concatenate([x[-40:], rng.choice(x, 200), rng.integers(-lim, lim, m)]))
+
+    codes = datagen.words_from_codes(rng.choice(9000, 3000, replace=False), 9000)
+    trees = []
+    for k in (4, 5):
+        long, short = some(k, 1400), some(k, 30)
+        trees += [("in", k, long), ("in", k, short), ("in", k, some(k, 7000)),
+                  ("and", ("not", ("in", k, short)), ("in", k, long)), ("or", ("in", k, long), ("isnull", 1))]
+    trees += [("codeset", 6, 9000, codes), ("and", ("codeset", 6, 9000, codes), ("in", 4, some(4, 1200)), ("cmp", 0, "<", 5))]
+    trees += [("codeset", k, 20, datagen.words_from_codes(range(0, 20, 3), 20)) for k in range(4)]
+    ctx.set_launch(block=256, grid=2, stage_words=stage)
+    try:
+        for tree in trees:
+            check(sel, ctx, dt, orc, tree)
+    finally:
+        ctx.set_launch()
+
+
+def test_partial_tile_is_no_slower(sel, ctx):
+    """The partial last tile of a table does not hold up the scan: with a
+    sorted list staged in LDS, rows short of a whole last tile cost no more
+    than a quarter of the scan on top."""
+    n = 2048 * 1500
+    x = torch.randint(-2 ** 40, 2 ** 40, (n,), device="cuda", dtype=torch.int64)
+    torch.cuda.synchronize()
+    values = tuple(int(v) for v in np.random.default_rng(7).integers(-2 ** 40, 2 ** 40, 1500))
+    best = []
+    ctx.enable_timing(True)
+    try:
+        for rows in (n, n - 900):
+            dt = ctx.table(rows, [("i64", 0, x.data_ptr(), None)], [x])
+            prog = ctx.program(dt, ("in", 0, values))
+            ms = []
+            for _ in range(25):
+                ctx.read_timing(reset=True)
+                ctx.count(dt, prog)
+                ms.append(ctx.read_timing(reset=True)[0][sel.K_COUNT])
+            best.append(min(ms))
+    finally:
+        ctx.enable_timing(False)
+    say("whole tiles", best[0], "partial last tile", best[1])
+    assert best[1] < 1.25 * best[0]
