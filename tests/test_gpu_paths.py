@@ -388,3 +388,35 @@ def test_partial_tile_is_no_slower(sel, ctx):
         ctx.enable_timing(False)
     say("whole tiles", best[0], "partial last tile", best[1])
     assert best[1] < 1.25 * best[0]
+
+
+@pytest.mark.parametrize("n", [1, 511, 2048 * 5 + 1501, (1 << 20) - 3, (1 << 20) + 2047, (1 << 21) + 1])
+@pytest.mark.parametrize("key", ["i32", "i64"])
+def test_key_bitmaps(sel, ctx, key, n):
+    """Key bitmaps from both key types on both sides of the small scan's limit,
+    at selections from one row of a tile to all, with keys in order and not,
+    negative and (i64) beyond 32 bits, all in range and some out of it."""
+    rng = np.random.default_rng(n)
+    base = -(n // 2) if key == "i32" else int(rng.choice([-2 ** 40, 2 ** 33 + 5, -3]))
+    t = datagen.Table("keys", n)
+    dtype = np.int32 if key == "i32" else np.int64
+    t.columns.append(datagen.Column("seq", key, (base + np.arange(n)).astype(dtype)))
+    t.columns.append(datagen.Column("perm", key, (base + rng.permutation(n)).astype(dtype)))
+    t.columns.append(datagen.Column("x", "i32", rng.integers(0, 10_000, n).astype(np.int32)))
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+    say(f"key bitmaps: {key} {n} rows")
+    for shape in (None, dict(block=64, grid=11)):
+        ctx.set_launch(**shape) if shape else ctx.set_launch()
+        for below in (5, 300, 3000, 10_000):
+            tree = ("cmp", 2, "<", below)
+            prog = ctx.program(dt, tree)
+            for col in (0, 1):
+                for lo, bits in ((base, n), (base - 70, n + 100), (base + n // 3, max(1, n // 2))):
+                    bm = torch.full(((bits + 31) // 32,), -1, dtype=torch.int32, device="cuda")
+                    st, cnt = ctx.pushdown_keybitmap(dt, col, lo, prog, bm, bits)
+                    ost, ocnt, words = orc.keybitmap(tree, col, lo, bits)
+                    assert (st == sel.SEL_OK) == (ost == 0) and cnt == ocnt, (below, col, lo, bits)
+                    if ost == 0:
+                        np.testing.assert_array_equal(as_u32(bm), words)
+    ctx.set_launch()
