@@ -420,3 +420,30 @@ def test_key_bitmaps(sel, ctx, key, n):
                     if ost == 0:
                         np.testing.assert_array_equal(as_u32(bm), words)
     ctx.set_launch()
+
+
+def test_selective_key_bitmap_reads_few_keys(sel, ctx):
+    """A key bitmap of 0.5 % of a table's rows costs little more than their
+    count: it does not read every key."""
+    n = 100_000_000
+    keys = torch.arange(n, device="cuda", dtype=torch.int64)
+    x = torch.randint(0, 10_000, (n,), device="cuda", dtype=torch.int32)
+    bits = torch.zeros((n + 31) // 32, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    dt = ctx.table(n, [("i64", 0, keys.data_ptr(), None), ("i32", 0, x.data_ptr(), None)], [keys, x])
+    prog = ctx.program(dt, ("cmp", 1, "<", 50))
+    ctx.enable_timing(True)
+    try:
+        best = {}
+        for kind, call in ((sel.K_COUNT, lambda: ctx.count(dt, prog)),
+                           (sel.K_KEYBITMAP, lambda: ctx.pushdown_keybitmap(dt, 0, 0, prog, bits, n))):
+            ms = []
+            for _ in range(15):
+                ctx.read_timing(reset=True)
+                call()
+                ms.append(ctx.read_timing(reset=True)[0][kind])
+            best[kind] = min(ms)
+    finally:
+        ctx.enable_timing(False)
+    say("count", best[sel.K_COUNT], "key bitmap", best[sel.K_KEYBITMAP])
+    assert best[sel.K_KEYBITMAP] < 1.8 * best[sel.K_COUNT]
