@@ -663,10 +663,10 @@ __device__ void finish(DevSlot* slot, unsigned long long* out, unsigned long lon
 // their keys alone, four at a time; else the keys of all steps in a few wide
 // loads, those without a TRUE row of the lane sent out of bounds.  100M rows,
 // int64 keys in order: a row at a time, each waited for by itself, took 105 us
-// for 0.5 % of them and 3.76 ms for all; every key by wide loads and every bit
-// tested 227 us and 1.07 ms; now 96 us and 1.07 ms.  The line lies at a
-// quarter of a lane's rows: up to an eighth 5 % of the rows take 211 us against
-// 176, up to half 13 % take 294 against 290.
+// for 0.5 % of them and 1210 us for half; every key by wide loads and every bit
+// tested 227 and 624 us; now 96 and 618.  The line lies at a quarter of a
+// lane's rows: at an eighth 5 % of the rows take 211 us against 176, at a half
+// 13 % take 294 against 290.
 constexpr uint32_t kKeysAtOnce = 4;
 template <int TY, int NS>
 __device__ __forceinline__ uint32_t put_keys(const ScanArgs& a, uint32_t T, uint64_t tb, uint32_t lane) {
