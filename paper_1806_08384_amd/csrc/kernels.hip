@@ -938,6 +938,21 @@ __device__ __forceinline__ void put_bits(uint32_t w, uint32_t pos, uint32_t firs
   }
 }
 
+// The same for the words of lanes 0 .. n - 1 (the other lanes' are zero), two
+// words at once, so that every store fills consecutive ids: from out[base].
+__device__ __forceinline__ void put_words(uint32_t w, uint32_t first, uint32_t n, uint32_t base, uint32_t lane,
+                                          uint32_t* __restrict__ out) {
+  for (uint32_t k = 0; k < n; k += 2) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)w, (int)k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)w, (int)k + 1);
+    const uint32_t f0 = (uint32_t)__builtin_amdgcn_readlane((int)first, (int)k);
+    const uint32_t f1 = (uint32_t)__builtin_amdgcn_readlane((int)first, (int)k + 1);
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    if (((lane & 32u ? hi : lo) >> (lane & 31u)) & 1u) out[base + rank] = (lane & 32u ? f1 : f0) + (lane & 31u);
+    base += (uint32_t)(__builtin_popcount(lo) + __builtin_popcount(hi));
+  }
+}
+
 // One tile: word r of 32 rows in lane r.  With many TRUE rows the wave goes
 // through them 64 rows at a time, two words at once, so that every store
 // fills consecutive ids; with few, each lane walks its own word.  (Every lane
@@ -1030,10 +1045,19 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
       const uint32_t to = (set ? sum[k] + rank : sum[k + 1] + lane - rank) & 63u;
       number |= (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)(set ? lane : 0u));
     }
-    const uint32_t c = __builtin_popcount(w);
+    const uint32_t c = __builtin_popcount(w), first = (t0 + q) * (uint32_t)kTileRows + 32u * number;
+    // a lane's word at a time takes as many stores as the fullest word has
+    // rows, each to as many lines as there are full words; two words at a time
+    // half as many stores as words, each to one or two lines.  12 % of 200M
+    // rows in runs of 700: 192 us word by word, 110 in pairs; 3 % in runs of 8
+    // 103 and 107.
+    if (__ballot(2u * c > sum[4])) {
+      put_words(w, first, sum[4], base, lane, a.out);
+      return;
+    }
     uint32_t run;
     const uint32_t pos = wave_incl_sum(c, lane, run) - c;
-    put_bits(w, base + pos, (t0 + q) * (uint32_t)kTileRows + 32u * number, a.out);
+    put_bits(w, base + pos, first, a.out);
     return;
   }
   uint32_t base = wave_sum(before);

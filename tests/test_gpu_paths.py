@@ -447,3 +447,57 @@ def test_selective_key_bitmap_reads_few_keys(sel, ctx):
         ctx.enable_timing(False)
     say("count", best[sel.K_COUNT], "key bitmap", best[sel.K_KEYBITMAP])
     assert best[sel.K_KEYBITMAP] < 1.8 * best[sel.K_COUNT]
+
+
+@pytest.mark.parametrize("tiles", [6, 4100])
+@pytest.mark.parametrize("run", [2, 17, 32, 64, 700])
+def test_row_ids_of_clustered_rows(sel, ctx, tiles, run):
+    """Row ids where TRUE rows come in runs: words full and partly full, odd
+    and even numbers of them in a compaction wave's tiles."""
+    n = 2048 * tiles + 333
+    rng = np.random.default_rng(run + tiles)
+    for share in (0.01, 0.06, 0.12, 0.4):
+        starts = np.flatnonzero(rng.random(n) < share / run)
+        step = np.zeros(n + run + 1, dtype=np.int32)
+        np.add.at(step, starts, 1)
+        np.add.at(step, starts + run, -1)
+        hit = (np.cumsum(step)[:n] > 0).astype(np.int8)
+        table = datagen.Table("runs", n)
+        table.columns.append(datagen.Column("hit", "i8", hit))
+        dt = sel.device_table(ctx, table)
+        want = np.flatnonzero(hit).astype(np.uint32)
+        prog = ctx.program(dt, ("cmp", 0, "=", 1))
+        for shape in (None, dict(block=64, grid=3)):
+            ctx.set_launch(**shape) if shape else ctx.set_launch()
+            out = ids_tensor(len(want) + 1, torch)
+            assert ctx.pushdown_rowids(dt, prog, UINT64_MAX, out) == (sel.SEL_OK, len(want))
+            np.testing.assert_array_equal(as_u32(out)[:-1], want)
+            assert as_u32(out)[-1] == 0xDEADBEEF
+    ctx.set_launch()
+
+
+def test_short_runs_compact_like_long_ones(sel, ctx):
+    """The same number of ids takes the compaction about the same time whether
+    the rows come in runs of 700 or of 5000."""
+    n = 200_000_000
+    row = torch.arange(n, device="cuda")
+    out = torch.empty(n // 8, dtype=torch.int32, device="cuda")
+    best = {}
+    ctx.enable_timing(True)
+    try:
+        for run in (5000, 700):
+            hit = ((row // run) * 7919 % 1000 < 120).to(torch.int8)
+            torch.cuda.synchronize()
+            dt = ctx.table(n, [("i8", 0, hit.data_ptr(), None)], [hit])
+            prog = ctx.program(dt, ("cmp", 0, "=", 1))
+            ms = []
+            for _ in range(15):
+                ctx.read_timing(reset=True)
+                st, cnt = ctx.pushdown_rowids(dt, prog, UINT64_MAX, out)
+                assert st == sel.SEL_OK and abs(cnt - 0.12 * n) < 1e-3 * n
+                ms.append(ctx.read_timing(reset=True)[0][sel.K_COMPACT])
+            best[run] = min(ms)
+    finally:
+        ctx.enable_timing(False)
+    say("compaction of runs", best)
+    assert best[700] < 1.5 * best[5000]
