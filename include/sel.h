@@ -542,15 +542,20 @@ typedef struct sel_launch {
   uint32_t block;          /* threads per workgroup: 64, 128 or 256 (scans)   */
   uint32_t grid;           /* workgroups; 0 = library default                  */
   uint32_t cached;         /* scans: 1 = column loads through the caches,
-                              0 = nontemporal loads (the default)             */
+                              0 = nontemporal loads (the default; a table of
+                              up to 2^20 rows in the default shape, which is
+                              scanned by quarter tiles, goes through the
+                              caches)                                         */
   uint32_t tiles_per_step; /* scans: consecutive 2048-row tiles a wave takes
                               per step, 1, 2 or 4 (0 = 1)                     */
   uint32_t stage_words;    /* scans: most LDS words of the program's bitmaps
                               and IN lists copied to LDS first (0 = all that
-                              fit 32 KB; 1 = none)                            */
-  uint32_t rows_per_lane;  /* lookup-table batch kernel: 8 = sixteen rows per
-                              lane at a time, 4 = eight (0 = 8; four-dword
-                              passes always take eight)                       */
+                              fit 48 KB, in quarter-tile scans 8 KB; 1 = none) */
+  uint32_t rows_per_lane;  /* lookup-table batch kernel, a code: 8 = the larger
+                              number of rows per lane at a time (sixteen), 4 =
+                              the smaller (eight), as saved configurations
+                              have it (0 = 8; four-dword passes always take
+                              the smaller)                                    */
 } sel_launch;
 
 /* Override (or with NULL, restore) the launch configuration used by the
@@ -563,7 +568,7 @@ sel_status sel_ctx_set_launch(sel_ctx* ctx, const sel_launch* launch);
 /* Time the count scan (with_mask = 0) or the count + mask scan
  * (with_mask != 0) of `prog` on `table`, `reps` times each (0 = 5): first
  * every launch shape (workgroups of 64/128/256 threads, 4..32 resident
- * waves per CU), then, with the fastest shape, cached against nontemporal
+ * waves per CU, and up to 2^20 rows the default one of quarter tiles), then, with the fastest shape, cached against nontemporal
  * loads, then 1, 2 or 4 tiles per step, then the LDS staging limit (all,
  * 2048 words, none) -- one knob at a time, each kept at its fastest
  * (median).  The result is recorded for this program class (bytes per row,
@@ -574,7 +579,7 @@ sel_status sel_autotune(sel_ctx* ctx, const sel_table* table, const sel_program*
 
 /* Same for the batched count of these n pairs (see sel_count_batch): the
  * leaf-major kernel's workgroups of 64 to 768 threads whose LDS fits the
- * batch's plan, then the lookup-table kernel's rows per lane (4 or 8). */
+ * batch's plan, then the lookup-table kernel's rows_per_lane (4 or 8). */
 sel_status sel_autotune_batch(sel_ctx* ctx, uint32_t n, const sel_table* const* tables,
                               const sel_program* const* progs, uint32_t reps,
                               sel_launch* best, double* best_ms);
@@ -596,8 +601,9 @@ uint32_t sel_tune_entries(const sel_ctx* ctx);
 typedef enum sel_kernel_kind {
   SEL_K_COUNT = 0,       /* fused evaluate + count                      */
   SEL_K_MASK = 1,        /* evaluate + count + packed result mask,
-                            tile lane maps and tile counts              */
-  SEL_K_SCAN = 2,        /* exclusive scan of tile counts               */
+                            tile word maps and tile counts              */
+  SEL_K_SCAN = 2,        /* exclusive scan of tile counts (not launched
+                            for small tables)                           */
   SEL_K_COMPACT = 3,     /* mask -> ascending row ids                   */
   SEL_K_KEYBITMAP = 4,   /* dimension key bitmap build                  */
   SEL_K_STAR = 5,        /* star semi-join probe count                  */

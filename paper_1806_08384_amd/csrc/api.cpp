@@ -207,9 +207,9 @@ sel_status read_out(sel_ctx* ctx, uint64_t* v0, uint64_t* v1) {
 // Wait until the kernel enqueued on `stream` has replaced all of w[0 .. n)
 // (pinned, set to kPending before the launch) by its results.  The words are
 // polled: on a ten-microsecond count the stream wait's wake-up cost half as
-// much again (11.6 us against 6.1 for an empty kernel).  A poll that lasts
-// past the longest scans falls back to the stream wait, which also reports a
-// failed launch.
+// much again (11.6 us against 6.1 for an empty kernel).  After 20 ms of
+// polling (a large batch, or work queued before the launch) the stream is
+// waited for instead, which also reports a failed launch.
 sel_status wait_words(sel_ctx* ctx, const unsigned long long* w, uint32_t n, hipStream_t stream) {
   const auto give_up = std::chrono::steady_clock::now() + std::chrono::milliseconds(20);
   uint32_t k = 0;

@@ -2321,20 +2321,10 @@ __device__ __forceinline__ void hs_sixteens(Hs& s, uint32_t c) {
   }
 }
 
-// Add NW words (NW = 1, 2, 4 or a multiple of 8), each bit position counting 0 or 1.
+// Add NW words (NW = 2, 4 or a multiple of 8), each bit position counting 0 or 1.
 template <int NW>
 __device__ __forceinline__ void hs_add(Hs& s, const uint32_t* w) {
-  if constexpr (NW == 1) {
-    const uint32_t t = s.ones & w[0];
-    s.ones ^= w[0];
-    const uint32_t f = s.twos & t;
-    s.twos ^= t;
-    const uint32_t e = s.fours & f;
-    s.fours ^= f;
-    const uint32_t c = s.eights & e;
-    s.eights ^= e;
-    hs_sixteens(s, c);
-  } else if constexpr (NW > 8) {
+  if constexpr (NW > 8) {
     static_assert(NW % 8 == 0, "blocks of eight words");
 #pragma unroll
     for (int k = 0; k < NW; k += 8) hs_add<8>(s, w + k);
@@ -2361,7 +2351,7 @@ __device__ __forceinline__ void hs_add(Hs& s, const uint32_t* w) {
     s.eights ^= e;
     hs_sixteens(s, c);
   } else {
-    static_assert(NW == 2, "one, two, four or a multiple of eight words");
+    static_assert(NW == 2, "two, four or a multiple of eight words");
     uint32_t t;
     csa(t, s.ones, s.ones, w[0], w[1]);
     const uint32_t f = s.twos & t;
