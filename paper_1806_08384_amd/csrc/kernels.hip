@@ -1705,7 +1705,10 @@ __device__ __forceinline__ uint32_t run_ops2(const CONSTANT uint32_t* ops, uint3
 __global__ void __launch_bounds__(768) k_batch(BatchArgs a) {
   // LDS: per-program counters, tables and staged bitmaps, each wave's slots
   extern __shared__ __align__(16) uint32_t dyn[];
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the wave's number is made scalar, so that its slots' address is: in a
+  // vector register it was spilled, and reloaded five times a tile (one star
+  // program over four dimensions, 200M rows: 766 us, now 730)
+  const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t nacc = a.acc_words;   // min(nprogs, kBatchMaxProgs)
   uint32_t* acc = dyn;
