@@ -501,3 +501,63 @@ def test_short_runs_compact_like_long_ones(sel, ctx):
         ctx.enable_timing(False)
     say("compaction of runs", best)
     assert best[700] < 1.5 * best[5000]
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2048 * 13 + 5, 2048 * 30])
+def test_leaf_batch_sparse_lists(sel, ctx, monkeypatch, n):
+    """Sparse IN lists in the leaf-major kernel: every column type, 1 to 700 values, first and last rows of steps
+    and tiles among them, alone and under OR and NOT, NULLs."""
+    monkeypatch.setenv("SEL_BATCH_KERNEL", "leaf")
+    rng = np.random.default_rng(n)
+    t = datagen.Table("lists", n)
+    lims = {"i8": 2 ** 7, "i16": 2 ** 15, "i32": 2 ** 31, "i64": 2 ** 62}
+    for ty, lim in lims.items():
+        valid = datagen.words_from_codes([i for i in range(n) if i % 5], n) if ty in ("i16", "i64") else None
+        t.columns.append(datagen.Column(ty, ty, rng.integers(-lim, lim, n).astype("int" + ty[1:]), valid))
+    t.columns.append(datagen.Column("f", "i8", rng.integers(-9, 9, n).astype(np.int8),
+                                    datagen.words_from_codes([i for i in range(n) if i % 3], n)))
+    dt = sel.device_table(ctx, t)
+    orc = oracle.Oracle(t)
+    trees = []
+    for k, lim in enumerate(lims.values()):
+        x = t.columns[k].data
+        edges = x[[i for i in (0, 3, 4, 255, 256, 259, 1023, 2046, 2047, n - 1) if i < n]]
+        for m in (0, 2, 30, 690):
+            vals = tuple(int(v) for v in np.concatenate([edges, rng.integers(-lim, lim, m)]))[: max(1, m + 10)]
+            known = ("not", ("isunknown", ("cmp", 4, "<", 3)))
+            trees += [("and", known, ("in", k, vals)), ("or", ("isunknown", ("cmp", 4, ">", 5)), ("not", ("in", k, vals)))]
+    for j in range(0, len(trees), 8):
+        got = ctx.count_batch([(dt, ctx.program(dt, x)) for x in trees[j:j + 8]])
+        assert got == [orc.count(x) for x in trees[j:j + 8]], j
+
+
+def test_leaf_batch_lists_against_counts(sel, ctx, monkeypatch):
+    """Six sparse int64 lists in one leaf-major batch take less than 2.6 times
+    the counts of the lists one by one."""
+    n = 60_000_000
+    x = torch.randint(-2 ** 40, 2 ** 40, (n,), device="cuda", dtype=torch.int64)
+    torch.cuda.synchronize()
+    dt = ctx.table(n, [("i64", 0, x.data_ptr(), None)], [x])
+    rng = np.random.default_rng(5)
+    monkeypatch.setenv("SEL_BATCH_KERNEL", "leaf")
+    lists = [("in", 0, tuple(int(v) for v in rng.integers(-2 ** 40, 2 ** 40, 3))) for _ in range(6)]
+    one = [ctx.program(dt, t) for t in lists]
+    batch = ctx.batch([(dt, p) for p in one])
+    want = [ctx.count(dt, p) for p in one]
+    ctx.enable_timing(True)
+    try:
+        best = {sel.K_COUNT: [], sel.K_BATCH: []}
+        for _ in range(12):
+            ctx.read_timing(reset=True)
+            assert [ctx.count(dt, p) for p in one] == want
+            assert batch.run() == want
+            ms, launches = ctx.read_timing(reset=True)
+            assert launches[sel.K_COUNT] == 6 and launches[sel.K_BATCH] == 1
+            for kind in best:
+                best[kind].append(ms[kind])
+    finally:
+        ctx.enable_timing(False)
+        batch.destroy()
+    count, together = min(best[sel.K_COUNT]), min(best[sel.K_BATCH])
+    say("counts", count, "batch", together)
+    assert together < 2.6 * count
