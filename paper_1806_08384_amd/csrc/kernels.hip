@@ -336,7 +336,9 @@ __device__ __forceinline__ uint32_t partial_leaf(const Ins& I, uint32_t ty, uint
       case T_I32: load8<T_I32, false, true>(data, tb, lane, nrows, q, x); break;
       default: load8<T_I64, false, true>(data, tb, lane, nrows, q, x); break;
     }
-    if (I.op == D_RANGE) {
+    // the ranges' code stays beside the loads': where each wave takes one tile,
+    // this one's instruction fetches end the scan
+    if (__builtin_expect(I.op == D_RANGE, 1)) {
 #pragma unroll
       for (int k = 7; k >= 0; --k) P = (P << 1) + (uint32_t)((uint64_t)x[k] - (uint64_t)I.lo <= I.span);
     } else if (SCAN && I.lds_word < sv.words) {
